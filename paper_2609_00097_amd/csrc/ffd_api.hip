@@ -393,13 +393,13 @@ int ffd_quantize_keys(const void* k, void* k_codes, void* k_absmax, void* k_resi
         return FFD_ERR_INVALID_ARGUMENT;
     QuantArgs a{static_cast<const uint16_t*>(k), static_cast<uint32_t*>(k_codes),
                 static_cast<uint16_t*>(k_absmax), static_cast<int8_t*>(k_resid), Hkv, Lcap, t_begin, t_end};
-    const dim3 grid((unsigned)((t_end - (t_begin & ~63) + 63) / 64), (unsigned)Hkv, (unsigned)B);
+    const dim3 grid((unsigned)((t_end + 63) / 64 - t_begin / 64), (unsigned)Hkv, (unsigned)B);
     if (thumb_bits == 2)
-        hipLaunchKernelGGL(quantize_keys_kernel<2>, grid, dim3(kThreads), 0, stream, a);
+        hipLaunchKernelGGL(quantize_keys_kernel<2>, grid, dim3(kQuantThreads), 0, stream, a);
     else if (thumb_bits == 4)
-        hipLaunchKernelGGL(quantize_keys_kernel<4>, grid, dim3(kThreads), 0, stream, a);
+        hipLaunchKernelGGL(quantize_keys_kernel<4>, grid, dim3(kQuantThreads), 0, stream, a);
     else
-        hipLaunchKernelGGL(quantize_keys_kernel<8>, grid, dim3(kThreads), 0, stream, a);
+        hipLaunchKernelGGL(quantize_keys_kernel<8>, grid, dim3(kQuantThreads), 0, stream, a);
     return launch_status();
 }
 

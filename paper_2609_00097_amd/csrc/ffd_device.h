@@ -37,6 +37,7 @@ constexpr int kDppXor1 = 0xB1;     // quad_perm [1,0,3,2]
 constexpr int kDppXor2 = 0x4E;     // quad_perm [2,3,0,1]
 constexpr int kDppRor4 = 0x124;    // row_ror:4
 constexpr int kDppRor8 = 0x128;    // row_ror:8
+constexpr int kDppHalfMirror = 0x141;    // row_half_mirror: lane i of each 8 reads lane 7 - i
 
 __device__ __forceinline__ float row16_max(float x) {
     x = fmaxf(x, dpp_f<kDppXor1>(x));

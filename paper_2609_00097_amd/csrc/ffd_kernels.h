@@ -118,6 +118,8 @@ struct QuantArgs {
     int Hkv, Lcap, t_begin, t_end;
 };
 
+constexpr int kQuantThreads = 64;              // one wave, one 64-token block per quantizer workgroup
+
 struct AppendArgs {
     const uint16_t* k_new;      // bf16 [B, Hkv, 128]
     const uint16_t* v_new;      // bf16 [B, Hkv, 128]

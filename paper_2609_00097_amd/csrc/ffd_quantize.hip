@@ -3,21 +3,31 @@
 // ties to the upper level), the absmax M, and an int8 residual r = rint(254 Lv k / M) - 254 c + 254 Lv.
 // b = 2 is App. A's codebook {-1.5, -0.5, 0.5, 1.5} with the residual rint(381 k / M) - 254 c + 381.
 //
-// Exactness:
-//  * code: x/s = Lv k / M has the integers as bin edges, so c = floor((2^b - 1) k / (2M)) + 2^(b-1).
-//    The quotient is taken as a product with the token's reciprocal 1/(2M) (off by at most one in
-//    the floor); (2^b - 1) k and i * 2M are products of 8-bit significands, exact in fp32 while
-//    2^-100 < M < 2^100 (no overflow, reciprocals normal), so exact comparisons then settle the
-//    floor. For b = 2 this is App. A's rule as three exact comparisons of 3k with -2M, 0, 2M.
-//  * residual: 254 Lv k is exact; q = 254 Lv k * (1/M) is within 2^-23 |q| of the true quotient, so
-//    rint(q) is the exact round-half-even result whenever q lies further than 2^-21 |q| from every
-//    half-integer. Otherwise (a tie or a near-tie), and for M outside (2^-100, 2^100), the element
-//    is redone in fp64, where nothing overflows and a quotient that is not a tie lies at least
-//    2^-24 Q from every half-integer (254 Lv < 2^15, k has 8 significant bits) while the division
-//    moves it by at most 2^-53 Q.
+// Exactness. With F = 254 Lv and Q = F k / M, the code is c = i + 2^(b-1), i = floor(Q / 254), and
+// the residual rint(Q) - 254 i - 127. For 2^-100 < M < 2^100:
+//  * F / M is held as hi + lo (lo from the exact remainder of the division), so q = fma(k, hi, k lo)
+//    is Q rounded to fp32: where Q itself is an fp32 value (every tie of the rounding, every bin edge
+//    254 i) q == Q exactly.
+//  * 254 j * fl(1/254) rounds to j exactly for every bin edge, and a Q that is no edge lies at least
+//    2^-17 Q from every edge (|(2^b - 1) k - 2 M j| is a multiple of the smaller ulp), so
+//    floor(q * fl(1/254)) is the exact floor.
+//  * a Q that is no tie lies at least 2^-18 Q (b = 2) or 2^-20 Q (b = 4) from every half-integer, so
+//    rint(q), half to even, is the exact rounding. For b = 8 that distance is 2^-24 Q, so q can land
+//    on a half-integer that Q only comes near: there the exact remainder F k - q M decides.
+// Other tokens (M outside that range, infinities or NaN among the dims) are redone in fp64, where
+// nothing overflows and a quotient that is not a tie lies at least 2^-24 Q from every half-integer
+// while the division moves it by at most 2^-53 Q.
 //
-// Mapping: 16 lanes per token, each lane owns 8 consecutive dims (one 16-byte load); the absmax is
-// a 16-lane max reduction. Writes go straight into the storage layouts documented in ffd.h.
+// Bound: HBM (2D bytes read, 16b + 2 + D written per token), as long as the arithmetic stays near a
+// dozen VALU instructions per element. At 8 x 131072 tokens, b = 2 (438 MB) a call takes 80 us,
+// 5.5 TB/s, about what a device copy reaches; with three edge comparisons, integer packing and an fp64
+// redo of every near-tie (a quarter percent of N(0, 1) keys are exactly +- M / 2, a tie, so most waves
+// took it) it took 138 us. One-wave workgroups: 80 us; four waves: 84 us.
+//
+// Mapping: one wave per 64-token block; lane l = n + 16 g holds token n's 16-dim slices 16 g (both
+// 64-dim halves) of each 16-token tile, which is the slice that the storage layouts of ffd.h give to
+// lane l: codes and residuals are assembled in the lane and leave as 16-byte stores, 1 KiB contiguous
+// over the wave, and the absmax takes two lane swaps per tile.
 #include "ffd_device.h"
 #include "ffd_kernels.h"
 
@@ -25,174 +35,299 @@ namespace ffd {
 
 namespace {
 
-// One token's quantization by 16 lanes: lane j16 holds dims 8*j16 .. 8*j16 + 7 as one 16-byte
-// chunk of bf16 (raw). The 16 lanes must be one aligned DPP row (lanes 16r .. 16r + 15), all active. Returns the token's absmax M in every lane, the
-// lane's code words and its 8 int8 residuals (rlo/rhi). Code words: b = 2, the 16 codes of the lane
-// pair's 16-dim group (identical in both lanes of the pair); b = 4, the lane's 8 codes; b = 8, its 8
-// code bytes c - 128.
-template <int BITS>
-struct QuantToken {
-    float m;
-    uint32_t word[BITS == 8 ? 2 : 1];
-    uint32_t rlo, rhi;
+typedef unsigned short v2u16 __attribute__((ext_vector_type(2)));
+
+// A token's absmax and 254 Lv / M as hi + lo (zero for M = 0).
+struct TokenScale {
+    float m, hi, lo;
+    bool special;       // M outside (2^-100, 2^100), infinities or NaN: the fp64 path
 };
 
+// One 16-dim slice: its code words (those of lane l in ffd.h) and residual bytes.
 template <int BITS>
-__device__ __forceinline__ QuantToken<BITS> quantize_token(uint4 raw, int j16) {
-#pragma clang fp contract(off)          // the rounding arguments above assume no fused products
-    constexpr int kLevels = 1 << BITS;
-    constexpr double kTwoLv = kLevels - 1;                 // 2 Lv
-    constexpr double kFull = 127.0 * (kLevels - 1);        // 254 Lv
-    float x[8];
-    x[0] = bf16_lo(raw.x); x[1] = bf16_hi(raw.x);
-    x[2] = bf16_lo(raw.y); x[3] = bf16_hi(raw.y);
-    x[4] = bf16_lo(raw.z); x[5] = bf16_hi(raw.z);
-    x[6] = bf16_lo(raw.w); x[7] = bf16_hi(raw.w);
-    float m = 0.f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) m = fmaxf(m, fabsf(x[e]));
-    m = row16_max(m);                      // the token's 16 lanes are one DPP row
+struct QuantSlice {
+    uint32_t code[BITS / 2];
+    uint32_t res[4];
+};
 
-    QuantToken<BITS> qt;
-    qt.m = m;
-    const bool fast = m < 0x1p100f && m > 0x1p-100f;
-    const float two_m = 2.f * m, r_two_m = 1.f / two_m, r_m = 1.f / m;
-#pragma unroll
-    for (int w = 0; w < (BITS == 8 ? 2 : 1); ++w) qt.word[w] = 0;
-    qt.rlo = qt.rhi = 0;
-    // fp32 pass over the 8 elements; the rare ones it cannot settle are redone in fp64 below
-    int cs[8], ns[8];
-    uint32_t slow = fast || m == 0.f ? 0u : 0xffu;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        if constexpr (BITS == 2) {
-            // the three bin edges 3k = -2M, 0, 2M, ties up (a branch-free count of edges passed)
-            const float x3 = 3.f * x[e];
-            cs[e] = (int)(x3 >= two_m) + (int)(x[e] >= 0.f) + (int)(x3 >= -two_m);
-        } else {
-            const float u = (float)kTwoLv * x[e];
-            float i = floorf(u * r_two_m);
-            i += (i + 1.f) * two_m <= u ? 1.f : 0.f;
-            i -= i * two_m > u ? 1.f : 0.f;
-            cs[e] = (int)i + kLevels / 2;
-        }
-        const float q = ((float)kFull * x[e]) * r_m;
-        const bool near_tie = !(fabsf(q - floorf(q) - 0.5f) > fabsf(q) * 0x1p-21f);
-        slow |= (uint32_t)(fast & near_tie) << e;
-        ns[e] = (int)rintf(q);
-    }
-    if (slow) {
-        const double md = m, two_md = 2.0 * md;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            if (slow & (1u << e)) {
-                const double xv = x[e], u = kTwoLv * xv;
-                double i = floor(u / two_md);
-                if ((i + 1.0) * two_md <= u) i += 1.0;
-                if (i * two_md > u) i -= 1.0;
-                cs[e] = (int)i + kLevels / 2;
-                ns[e] = (int)rint((kFull * xv) / md);
-            }
-        }
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        int c = kLevels / 2, r = 0;                        // M = 0: level +0.5, residual 0
-        if (m != 0.f) {
-            c = min(max(cs[e], 0), kLevels - 1);
-            r = ns[e] - 254 * c + (int)kFull;
-        }
-        if constexpr (BITS == 2) {
-            const int e16 = 8 * (j16 & 1) + e;             // position inside the 16-dim group
-            qt.word[0] |= (uint32_t)c << (8 * (e16 & 3) + 2 * (e16 >> 2));
-        } else if constexpr (BITS == 4) {
-            qt.word[0] |= (uint32_t)c << (8 * (e & 3) + 4 * (e >> 2));
-        } else {
-            qt.word[e >> 2] |= (uint32_t)((c - 128) & 0xff) << (8 * (e & 3));
-        }
-        const uint32_t rb = (uint32_t)(r & 0xff);
-        if (e < 4) qt.rlo |= rb << (8 * e); else qt.rhi |= rb << (8 * (e - 4));
-    }
-    if constexpr (BITS == 2)                                           // the lane pair's 16 dims
-        qt.word[0] |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)qt.word[0], kDppXor1, 0xf, 0xf, false);
-    return qt;
+__device__ __forceinline__ uint32_t pk_max_u16(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(v2u16, a), __builtin_bit_cast(v2u16, b)));
 }
 
-// Store token t of (b, kvh) = row bh into the codes / absmax / residual layouts (lane j16's share).
-// Codes: lane l = n16 + 16g of block t/64 holds the (t4, cc) group's b/2 words from (2 t4 + cc) b/2;
-// its word w sits at [w / 4][l][w % 4] of the block's 4b x 64 words.
+// Largest |k| bit patterns of the slice, even and odd dims in the two halves.
+__device__ __forceinline__ uint32_t slice_absmax(const uint4 (&raw)[2]) {
+    uint32_t m = raw[0].x & 0x7fff7fffu;
+    const uint32_t w[7] = {raw[0].y, raw[0].z, raw[0].w, raw[1].x, raw[1].y, raw[1].z, raw[1].w};
+#pragma unroll
+    for (int i = 0; i < 7; ++i) m = pk_max_u16(m, w[i] & 0x7fff7fffu);
+    return m;
+}
+
+// The token's constants from the largest bit pattern of all its dims (bf16 magnitudes order as
+// integers, NaN above infinity).
 template <int BITS>
-__device__ __forceinline__ void store_token(const QuantToken<BITS>& qt, int j16, size_t bh, int t, int Lcap,
-                                            uint32_t* codes, uint16_t* absmax, int8_t* resid) {
-    const int n16 = t & 15, t4 = (t >> 4) & 3;
-    const int w16 = j16 >> 1;                              // 16-dim group 0..7
-    const int cc = w16 >> 2, g = w16 & 3;
-    const int w = (2 * t4 + cc) * (BITS / 2) + (BITS == 2 ? 0 : (BITS / 4) * (j16 & 1));   // first word
-    uint32_t* dst = codes + (bh * (size_t)(Lcap / 64) + (t >> 6)) * (64 * 4 * BITS) + (w >> 2) * 256 +
-                    (n16 + 16 * g) * 4 + (w & 3);
-    if constexpr (BITS == 2) {
-        if ((j16 & 1) == 0) dst[0] = qt.word[0];
-    } else if constexpr (BITS == 4) {
-        dst[0] = qt.word[0];
-    } else {
-        *reinterpret_cast<uint2*>(dst) = make_uint2(qt.word[0], qt.word[1]);   // words w, w + 1 (w even)
+__device__ __forceinline__ TokenScale token_scale(uint32_t absmax2) {
+    const uint32_t bits = max(absmax2 & 0xffffu, absmax2 >> 16);
+    constexpr float kFull = 127.f * ((1 << BITS) - 1);      // 254 Lv
+    TokenScale s;
+    s.m = bf16_to_f32((uint16_t)bits);
+    s.special = !(s.m < 0x1p100f && s.m > 0x1p-100f) && bits != 0;
+    const float r = 1.f / s.m, hi = kFull / s.m;
+    s.hi = bits == 0 ? 0.f : hi;
+    s.lo = bits == 0 ? 0.f : fmaf(-hi, s.m, kFull) * r;
+    return s;
+}
+
+// Byte I of a word from a float in [0, 255], rounded half to even by the conversion.
+template <int I>
+__device__ __forceinline__ uint32_t put_u8(float x, uint32_t word) {
+    return __builtin_amdgcn_cvt_pk_u8_f32(x, I, word);
+}
+
+template <int BITS>
+__device__ __forceinline__ void unpack_slice(const uint4 (&raw)[2], float (&x)[16]) {
+    const uint32_t w[8] = {raw[0].x, raw[0].y, raw[0].z, raw[0].w, raw[1].x, raw[1].y, raw[1].z, raw[1].w};
+#pragma unroll
+    for (int i = 0; i < 8; ++i) { x[2 * i] = bf16_lo(w[i]); x[2 * i + 1] = bf16_hi(w[i]); }
+}
+
+// Word and bit position of dim e's code in a slice's code words.
+template <int BITS> __device__ constexpr int code_word(int e) { return (e >> 2) / (8 / BITS); }
+template <int BITS> __device__ constexpr int code_shift(int e) { return 8 * (e & 3) + BITS * ((e >> 2) % (8 / BITS)); }
+
+// The fp64 path; m is the absmax over the dims that are not NaN (0: no dim but zeros and NaN, residual 0).
+template <int BITS>
+__device__ __forceinline__ QuantSlice<BITS> quantize_slice_f64(uint4 raw0, uint4 raw1, float m) {
+#pragma clang fp contract(off)
+    constexpr int kLevels = 1 << BITS;
+    constexpr double kTwoLv = kLevels - 1, kFull = 127.0 * (kLevels - 1);
+    const uint4 raw[2] = {raw0, raw1};
+    float x[16];
+    unpack_slice<BITS>(raw, x);
+    QuantSlice<BITS> qs = {};
+    const double md = m, two_md = 2.0 * md;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        const double xv = x[e], u = kTwoLv * xv;
+        double i = floor(u / two_md);
+        if ((i + 1.0) * two_md <= u) i += 1.0;
+        if (i * two_md > u) i -= 1.0;
+        const int c = min(max((int)i + kLevels / 2, 0), kLevels - 1);
+        const int r = m == 0.f ? 0 : (int)rint((kFull * xv) / md) - 254 * c + (int)kFull;
+        qs.code[code_word<BITS>(e)] |= (uint32_t)(BITS == 8 ? (c - 128) & 0xff : c) << code_shift<BITS>(e);
+        qs.res[e >> 2] |= (uint32_t)(r & 0xff) << (8 * (e & 3));
     }
-    {
-        const int rc = j16 >> 3, rg = (j16 & 7) >> 1, e0 = 8 * (j16 & 1);
-        int8_t* dst = resid + (((bh * (size_t)(Lcap / 16) + (t >> 4)) * 2 + rc) * 64 + n16 + 16 * rg) * 16 + e0;
-        *reinterpret_cast<uint2*>(dst) = make_uint2(qt.rlo, qt.rhi);
+    return qs;
+}
+
+template <int BITS>
+__device__ __forceinline__ QuantSlice<BITS> quantize_slice(const uint4 (&raw)[2], const TokenScale& s) {
+#pragma clang fp contract(off)          // the rounding arguments above name every fused product
+    constexpr float kFull = 127.f * ((1 << BITS) - 1);
+    float x[16], t[16], fi[16];
+    unpack_slice<BITS>(raw, x);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        const float q = fmaf(x[e], s.hi, x[e] * s.lo);
+        fi[e] = floorf(q * (1.f / 254.f));
+        if constexpr (BITS == 8) {
+            float n = rintf(q);
+            const float d = q - n, rem = fmaf(-q, s.m, kFull * x[e]);   // exact: |d| = 1/2 has q in 16 bits
+            n += fabsf(d) == 0.5f && d * rem > 0.f ? 2.f * d : 0.f;
+            t[e] = fmaf(-254.f, fi[e], n);
+        } else {
+            t[e] = fmaf(-254.f, fi[e], q);                              // exact difference in [0, 254]
+        }
     }
-    if (j16 == 0)
-        absmax[bh * (size_t)Lcap + (size_t)(t >> 6) * 64 + n16 * 4 + t4] = (uint16_t)(__float_as_uint(qt.m) >> 16);
+    QuantSlice<BITS> qs;
+    const uint32_t any = s.m != 0.f ? 0xffffffffu : 0u;                 // M = 0: residual 0
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        uint32_t r = put_u8<0>(t[4 * w], 0u);
+        r = put_u8<1>(t[4 * w + 1], r);
+        r = put_u8<2>(t[4 * w + 2], r);
+        r = put_u8<3>(t[4 * w + 3], r);
+        // bytes rint(Q) - 254 i in [0, 254] to rint(Q) - 254 i - 127: + 1 without a carry, - 128
+        qs.res[w] = ((r + 0x01010101u) ^ 0x80808080u) & any;
+    }
+    // the codes of one byte as a float sum of i * 2^(bit), biased by 2^(b-1) per code, at most 255
+    constexpr int kPer = 8 / BITS;
+    constexpr float kBias = (1 << (BITS - 1)) * (255.f / ((1 << BITS) - 1));
+#pragma unroll
+    for (int w = 0; w < BITS / 2; ++w) {
+        float a[4] = {kBias, kBias, kBias, kBias};
+#pragma unroll
+        for (int k = 0; k < kPer; ++k)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) a[i] = fmaf(fi[4 * (w * kPer + k) + i], (float)(1 << (BITS * k)), a[i]);
+        uint32_t c = put_u8<0>(a[0], 0u);
+        c = put_u8<1>(a[1], c);
+        c = put_u8<2>(a[2], c);
+        c = put_u8<3>(a[3], c);
+        qs.code[w] = BITS == 8 ? c ^ 0x80808080u : c;
+    }
+    return qs;
+}
+
+__device__ __forceinline__ uint16_t bf16_bits(float m) { return (uint16_t)(__float_as_uint(m) >> 16); }
+
+// Store the slice of 64-dim half cc, group g, of token n16 of tile t4 of a (b, kvh)'s block blk.
+template <int BITS>
+__device__ __forceinline__ void store_slice(const QuantSlice<BITS>& qs, float m, size_t blk, int t4, int n16, int cc,
+                                            int g, uint32_t* codes, uint16_t* absmax, int8_t* resid) {
+    const int w = (2 * t4 + cc) * (BITS / 2), l = n16 + 16 * g;
+    uint32_t* dst = codes + blk * (64 * 4 * BITS) + (w >> 2) * 256 + l * 4 + (w & 3);
+    if constexpr (BITS == 2) dst[0] = qs.code[0];
+    else if constexpr (BITS == 4) *reinterpret_cast<uint2*>(dst) = make_uint2(qs.code[0], qs.code[1]);
+    else *reinterpret_cast<uint4*>(dst) = make_uint4(qs.code[0], qs.code[1], qs.code[2], qs.code[3]);
+    reinterpret_cast<uint4*>(resid)[blk * 512 + t4 * 128 + cc * 64 + l] =
+        make_uint4(qs.res[0], qs.res[1], qs.res[2], qs.res[3]);
+    if (cc == 0 && g == 0) absmax[blk * 64 + n16 * 4 + t4] = bf16_bits(m);
+}
+
+// max over the four lanes n, n + 16, n + 32, n + 48 (one token's slices), every lane receiving it
+__device__ __forceinline__ uint32_t token_max4(uint32_t m) {
+    const auto a = __builtin_amdgcn_permlane32_swap(m, m, false, false);
+    m = pk_max_u16(a[0], a[1]);
+    const auto b = __builtin_amdgcn_permlane16_swap(m, m, false, false);
+    return pk_max_u16(b[0], b[1]);
+}
+
+// max of |x| over the dims of a slice that are not NaN
+__device__ __forceinline__ float slice_fmax(uint4 raw0, uint4 raw1) {
+    const uint4 raw[2] = {raw0, raw1};
+    float x[16], m = 0.f;
+    unpack_slice<2>(raw, x);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) m = fmaxf(m, fabsf(x[e]));
+    return m;
 }
 
 }  // namespace
 
-// Workgroup x covers the 64-token block t0 = 64 * (t_begin / 64 + x) of one (b, kvh): 16 tokens per
-// pass, the four loads issued first, so the block's code words, absmaxes and residual tiles are all
-// written by this workgroup (whole cache lines); only tokens in [t_begin, t_end) are stored.
+// Workgroup x, one wave, covers block t_begin / 64 + x of one (b, kvh); only tokens in [t_begin,
+// t_end) are stored. The four tiles' loads are issued first.
 template <int BITS>
-__global__ __launch_bounds__(kThreads) void quantize_keys_kernel(QuantArgs a) {
-    const int tid = threadIdx.x, j16 = tid & 15;
-    const int t0 = (a.t_begin & ~63) + blockIdx.x * 64 + (tid >> 4);
-    const int kvh = blockIdx.y, b = blockIdx.z;
-    const size_t bh = (size_t)b * a.Hkv + kvh;
-
-    uint4 raw[4];
+__global__ __launch_bounds__(kQuantThreads) void quantize_keys_kernel(QuantArgs a) {
+    const int lane = threadIdx.x, g = lane >> 4, n = lane & 15;
+    const int j = (a.t_begin >> 6) + blockIdx.x;
+    const size_t bh = (size_t)blockIdx.z * a.Hkv + blockIdx.y;
+    const bool whole = 64 * j >= a.t_begin && 64 * j + 64 <= a.t_end;       // uniform in the wave
+    const uint4* kp = reinterpret_cast<const uint4*>(a.k) + bh * a.Lcap * (kD / 8) + 2 * g;
+    uint4 raw[4][2][2];
+    bool in[4];
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        const int t = t0 + 16 * p;
-        raw[p] = make_uint4(0, 0, 0, 0);
-        if (t >= a.t_begin && t < a.t_end)
-            raw[p] = *reinterpret_cast<const uint4*>(a.k + (bh * a.Lcap + t) * kD + 8 * j16);
+    for (int t4 = 0; t4 < 4; ++t4) {
+        const int t = 64 * j + 16 * t4 + n;
+        in[t4] = t >= a.t_begin && t < a.t_end;
+        // a token outside the range reads one inside it (no branch around the loads) and stores nothing
+        const uint4* tok = kp + (size_t)min(max(t, a.t_begin), a.t_end - 1) * (kD / 8);
+#pragma unroll
+        for (int cc = 0; cc < 2; ++cc)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) raw[t4][cc][h] = tok[8 * cc + h];
     }
+    const size_t blk = bh * (size_t)(a.Lcap / 64) + j;
+    uint4* cdst = reinterpret_cast<uint4*>(a.codes) + blk * (64 * BITS) + lane;
+    uint4* rdst = reinterpret_cast<uint4*>(a.resid) + blk * 512 + lane;
+    uint16_t* mdst = a.absmax + blk * 64 + n * 4;
+    uint32_t m4[4], w2[4];                          // absmaxes of the lane's tokens; b = 2: words of two tiles
+    int special = 0;                                // tiles in which the lane's token needs the fp64 path
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        const int t = t0 + 16 * p;
-        const QuantToken<BITS> qt = quantize_token<BITS>(raw[p], j16);
-        if (t >= a.t_begin && t < a.t_end) store_token<BITS>(qt, j16, bh, t, a.Lcap, a.codes, a.absmax, a.resid);
+    for (int t4 = 0; t4 < 4; ++t4) {
+        const TokenScale s = token_scale<BITS>(token_max4(pk_max_u16(slice_absmax(raw[t4][0]), slice_absmax(raw[t4][1]))));
+        QuantSlice<BITS> qs[2];
+#pragma unroll
+        for (int cc = 0; cc < 2; ++cc) qs[cc] = quantize_slice<BITS>(raw[t4][cc], s);
+        special |= (int)s.special << t4;
+        m4[t4] = bf16_bits(s.m);
+        if (whole || in[t4]) {
+#pragma unroll
+            for (int cc = 0; cc < 2; ++cc) {
+                const QuantSlice<BITS>& v = qs[cc];
+                rdst[t4 * 128 + cc * 64] = make_uint4(v.res[0], v.res[1], v.res[2], v.res[3]);
+                if constexpr (BITS == 8) cdst[(2 * t4 + cc) * 64] = make_uint4(v.code[0], v.code[1], v.code[2], v.code[3]);
+            }
+            if constexpr (BITS == 4) cdst[t4 * 64] = make_uint4(qs[0].code[0], qs[0].code[1], qs[1].code[0], qs[1].code[1]);
+        }
+        if constexpr (BITS == 2) {
+            w2[2 * (t4 & 1)] = qs[0].code[0];
+            w2[2 * (t4 & 1) + 1] = qs[1].code[0];
+            if (whole) {
+                if (t4 & 1) cdst[(t4 >> 1) * 64] = make_uint4(w2[0], w2[1], w2[2], w2[3]);
+            } else if (in[t4]) {
+                reinterpret_cast<uint2*>(cdst + (t4 >> 1) * 64)[t4 & 1] = make_uint2(qs[0].code[0], qs[1].code[0]);
+            }
+        }
+    }
+    if (g == 0) {
+        if (whole) {
+            *reinterpret_cast<uint2*>(mdst) = make_uint2(m4[0] | (m4[1] << 16), m4[2] | (m4[3] << 16));
+        } else {
+#pragma unroll
+            for (int t4 = 0; t4 < 4; ++t4)
+                if (in[t4]) mdst[t4] = (uint16_t)m4[t4];
+        }
+    }
+    if (special == 0) return;
+#pragma unroll 1
+    for (int t4 = 0; t4 < 4; ++t4) {                // rare: these tokens again, over what was stored
+        const int t = 64 * j + 16 * t4 + n;
+        if (!(special >> t4 & 1) || t < a.t_begin || t >= a.t_end) continue;      // a token's four lanes together
+        const uint4* tok = kp + (size_t)t * (kD / 8);
+        float m = fmaxf(slice_fmax(tok[0], tok[1]), slice_fmax(tok[8], tok[9]));
+        m = fmaxf(m, __shfl_xor(m, 16));
+        m = fmaxf(m, __shfl_xor(m, 32));
+#pragma unroll 1
+        for (int cc = 0; cc < 2; ++cc)
+            store_slice<BITS>(quantize_slice_f64<BITS>(tok[8 * cc], tok[8 * cc + 1], m), m, blk, t4, n, cc, g, a.codes,
+                              a.absmax, a.resid);
     }
 }
 
 // Decode-step append: workgroup b writes the new token of every KV head of sequence b at position
 // L = seq_lens[b] (bf16 K/V rows when the caches are given, and its quantized key), then sets
-// seq_lens[b] = L + 1. 16 lanes per KV head; a sequence already at capacity is left unchanged.
+// seq_lens[b] = L + 1. 8 lanes per KV head, one 16-dim slice each; a sequence already at capacity is
+// left unchanged.
 template <int BITS>
 __global__ __launch_bounds__(kThreads) void append_kv_kernel(AppendArgs a) {
-    const int tid = threadIdx.x, j16 = tid & 15;
+    const int tid = threadIdx.x, s8 = tid & 7, cc = s8 >> 2, g = s8 & 3;
     const int b = blockIdx.x;
     const int L = a.seq_lens[b];
     const bool room = L >= 0 && L < a.Lcap;
-    for (int kvh = tid >> 4; kvh < a.Hkv; kvh += kThreads / 16) {
+    for (int kvh = tid >> 3; kvh < a.Hkv; kvh += kThreads / 8) {
         const size_t bh = (size_t)b * a.Hkv + kvh;
-        const uint4 kraw = *reinterpret_cast<const uint4*>(a.k_new + bh * kD + 8 * j16);
-        const uint4 vraw = *reinterpret_cast<const uint4*>(a.v_new + bh * kD + 8 * j16);
-        const QuantToken<BITS> qt = quantize_token<BITS>(kraw, j16);
+        const uint4* kp = reinterpret_cast<const uint4*>(a.k_new + bh * kD) + 2 * s8;
+        const uint4* vp = reinterpret_cast<const uint4*>(a.v_new + bh * kD) + 2 * s8;
+        const uint4 raw[2] = {kp[0], kp[1]};
+        const uint4 v0 = vp[0], v1 = vp[1];
+        uint32_t m2 = slice_absmax(raw);            // then over the head's eight lanes
+        m2 = pk_max_u16(m2, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m2, kDppXor1, 0xf, 0xf, false));
+        m2 = pk_max_u16(m2, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m2, kDppXor2, 0xf, 0xf, false));
+        m2 = pk_max_u16(m2, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m2, kDppHalfMirror, 0xf, 0xf, false));
+        const TokenScale s = token_scale<BITS>(m2);
         if (room) {
-            const size_t row = (bh * a.Lcap + L) * kD + 8 * j16;
-            if (a.k_cache) *reinterpret_cast<uint4*>(a.k_cache + row) = kraw;
-            if (a.v_cache) *reinterpret_cast<uint4*>(a.v_cache + row) = vraw;
-            store_token<BITS>(qt, j16, bh, L, a.Lcap, a.codes, a.absmax, a.resid);
+            const size_t row = (bh * a.Lcap + L) * (kD / 8) + 2 * s8;
+            if (a.k_cache) {
+                reinterpret_cast<uint4*>(a.k_cache)[row] = raw[0];
+                reinterpret_cast<uint4*>(a.k_cache)[row + 1] = raw[1];
+            }
+            if (a.v_cache) {
+                reinterpret_cast<uint4*>(a.v_cache)[row] = v0;
+                reinterpret_cast<uint4*>(a.v_cache)[row + 1] = v1;
+            }
+            const int n16 = L & 15, t4 = (L >> 4) & 3;
+            const size_t blk = bh * (size_t)(a.Lcap / 64) + (L >> 6);
+            if (s.special) {                        // the head's eight lanes together
+                float m = slice_fmax(raw[0], raw[1]);
+                m = fmaxf(m, __shfl_xor(m, 1));
+                m = fmaxf(m, __shfl_xor(m, 2));
+                m = fmaxf(m, __shfl_xor(m, 4));
+                store_slice<BITS>(quantize_slice_f64<BITS>(raw[0], raw[1], m), m, blk, t4, n16, cc, g, a.codes, a.absmax,
+                                  a.resid);
+            } else {
+                store_slice<BITS>(quantize_slice<BITS>(raw, s), s.m, blk, t4, n16, cc, g, a.codes, a.absmax, a.resid);
+            }
         }
     }
     __syncthreads();                    // every thread has read L before it moves

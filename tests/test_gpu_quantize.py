@@ -79,3 +79,27 @@ def test_partial_range_leaves_other_tokens_untouched(bits):
     got1 = _gpu_quantize(c.k, 200, 201, fill=0, bits=bits)
     ref1 = O.quantize_cache(c.k, 200, 201, bits=bits)
     _assert_equal_packed(got1, ref1, "append one token")
+
+
+@pytest.mark.parametrize("bits", [2, 4, 8])
+def test_ties_and_edges_of_every_absmax_mantissa(bits):
+    """Each of the 128 bf16 mantissas of M as a token of its own, at exponents on both sides of the
+    fp32 path's range (so that a tile mixes both paths) and in a range that starts and ends inside a
+    block: values nearest to rounding ties (h + 1/2) M / (254 Lv) and bin edges j M / Lv, +-M/2 (always
+    a tie), +-M, tiny values and zeros of either sign. Bit-exact."""
+    rng = np.random.default_rng(17 + bits)
+    Lv, Lcap, t0, t1 = (2 ** bits - 1) / 2, 192, 7, 7 + 128
+    vals = np.zeros((Lcap, 128))
+    for i, mant in enumerate(range(128, 256)):
+        M = mant / 128 * 2.0 ** (0, 3, -20, 99, 101, -99, -101)[i % 7]
+        h = rng.integers(0, int(254 * Lv), size=60)
+        edges = rng.integers(-int(Lv), int(Lv) + 1, size=40) * M / Lv
+        ties = (h + 0.5) * M / (254 * Lv) * rng.choice([-1.0, 1.0], size=60)
+        fixed = [M, -M, M / 2, -M / 2, M * 2.0 ** -24, -M * 2.0 ** -24, 0.0, -0.0]
+        row = np.concatenate([fixed, ties, edges, rng.uniform(-M, M, 20)])
+        row = O.bf16_to_f64(O.f64_to_bf16_bits(row))
+        vals[t0 + i] = rng.permutation(np.where(np.abs(row) > M, M, row))
+    k_bits = O.f64_to_bf16_bits(vals).reshape(1, 1, Lcap, 128)
+    print(f"case ties and edges bits={bits}", flush=True)
+    _assert_equal_packed(_gpu_quantize(k_bits, t0, t1, bits=bits), O.quantize_cache(k_bits, t0, t1, bits=bits),
+                         f"ties bits={bits}")
