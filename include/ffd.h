@@ -134,10 +134,10 @@ int ffd_append_kv(const void* k_new, const void* v_new, void* k_cache, void* v_c
  *                All scores carry softmax_scale. With n_sink = n_local = 0, m~ = -inf and every
  *                block is kept.
  *   num_splits   refinement workgroups per KV group on average (1..FFD_MAX_SPLITS), or 0 for
- *                automatic: the call uses W = num_splits * B * Hkv refinement workgroups in all,
- *                given to the KV groups in proportion to their kept blocks (at least one each),
- *                each refining an equal run of its group's kept blocks in block order; their
- *                partial states are merged by log-sum-exp.
+ *                automatic: the call uses W = num_splits * B * Hkv refinement workgroups (a few less
+ *                where their partial states would not fit the workspace), each refining an equal run
+ *                of the kept blocks of all KV groups in (group, block) order, and writing one partial
+ *                state per group it meets; the partial states are merged by log-sum-exp.
  *   softmax_scale  > 0, or 0 for 1/sqrt(D).
  *   out          bf16  [B, Hq, D]  softmax(z over kept tokens) . V, z the refined logits;
  *                                   0 for a head with no kept token (empty sequence).
@@ -145,7 +145,7 @@ int ffd_append_kv(const void* k_new, const void* v_new, void* k_cache, void* v_c
  *   block_mask   uint8 [B, Hq, Lcap/64] or NULL: 1 iff head h kept block j; 0 at/after the end.
  *   workspace    device scratch of at least ffd_workspace_bytes(B, Hq, Hkv, Lcap, D, num_splits)
  *                bytes: the partials, a per-KV-group table locating them, the scan's kept-block
- *                lists and counts, and the per-head block scores the top-k rule selects from
+ *                lists and their records, and the per-head block scores the top-k rule selects from
  *                (4 * G bytes per block of the capacity). It needs no initialisation and is
  *                clobbered. Calls that overlap in time (different streams) need separate workspaces.
  *  Limits: B * Hkv <= 2^20 and Lcap <= 2^24 tokens, else FFD_ERR_UNSUPPORTED.
@@ -250,7 +250,7 @@ int ffd_dense_decode_attention(const void* q, const void* k, const void* v, cons
                                void* workspace, size_t workspace_bytes, hipStream_t stream);
 
 /* Number of splits an ffd_decode_attention call with this num_splits (0 = automatic) will use: the
- * automatic count gives the refinement (S + 1) * B * Hkv workgroups, at most one per compute unit of
+ * automatic count gives the refinement up to (S + 1) * B * Hkv workgroups, at most one per compute unit of
  * the current device (its CU count is queried once per device and cached; 256, an MI355X's, if the
  * query fails). The workspace size depends on it, so size and call on the same device.
  * 0 on invalid input. */

@@ -54,11 +54,9 @@ void* device_scratch() {
     return p;
 }
 
-// Automatic split counts. The FFD refinement grid has W + B*Hkv = (S + 1) * B*Hkv workgroups of
-// equal work; it should not exceed one per CU, because a CU serves its older workgroup's memory
-// requests first, so a second workgroup on a CU finishes its share about 3 us later (at 4 x 128K on
-// 256 CUs, delta 5: S = 7 (256 workgroups) 60.0 us per step; S = 8 (288) 65.2 us; S = 15 (512)
-// 62.2 us; S = 6 (224) 62.3 us). The dense path keeps two workgroups per CU for up to 63 KV groups
+// Automatic split counts. The FFD refinement grid has at most (S + 1) * B*Hkv workgroups of equal work
+// and at most one per CU, because a CU serves its older workgroup's memory requests first, so a second
+// workgroup on a CU finishes its share about 3 us later. The dense path keeps two workgroups per CU for up to 63 KV groups
 // (4 x 128K: S = 15, 512 workgroups, against S = 23 or 31 about 2 % slower; B = 1: more splits are
 // slower still) and three from 64 groups on (the ragged batch of 16 sequences, 128 groups: 512
 // workgroups 873 us, 768 workgroups 833 us, 1024 workgroups 832 us).
@@ -123,7 +121,6 @@ Partials carve(void* ws, int B, int Hq, int S) {
     return Partials{base, base + rows, base + 2 * rows};
 }
 
-int head_tiles(int G) { return G <= 4 ? 1 : 2; }
 
 // Workgroups of the scan kernel per (sequence, KV head): about one per CU in all (one 8-wave
 // workgroup per CU: 8 waves x 4 blocks of 2 KiB in flight cover a CU's share of the HBM bandwidth at
@@ -205,10 +202,11 @@ int auto_kernels(int B, int Hkv, int Lcap, int S1f) {
                ? FFD_KERNELS_FUSED : FFD_KERNELS_SPLIT;
 }
 
-// FFD workspace: partial states (for the fused top-delta kernel's B * Hq * S1f rows, or for the
-// top-k path's W + B*Hkv refinement workgroups (W = S * B * Hkv) of G heads each), and for the
-// top-k path the per-group (first workgroup, count) table, the scan's per-split kept counts and
-// kept lists, and the block scores [P, C, G] it selects from.
+// FFD workspace: partial states (for the fused top-delta kernel's B * Hq * S1f rows, or for the split
+// path's refinement units, one row of G heads per unit and group it meets), the per-group (first row,
+// last row) table, the refinement's unit counter (the region called counts), the kept lists, and the
+// block scores [P, C, G] the top-k rule selects from; the records of the kept lists take the block
+// scores' place or the end of the partials.
 struct FfdWorkspace {
     size_t rows;                      // partial rows
     size_t table_off, counts_off, lists_off, sigma_off, total;
@@ -218,7 +216,7 @@ FfdWorkspace ffd_layout(int B, int Hq, int Hkv, int Lcap, int D, int S, int S1f)
     FfdWorkspace w;
     const size_t pairs = (size_t)B * Hkv;
     const size_t nblk_cap = (size_t)(Lcap / FFD_BLOCK);
-    // the top-k path's refinement rows, or the fused kernel's [B, Hq, S1f] rows
+    // the split path's refinement rows, or the fused kernel's [B, Hq, S1f] rows
     w.rows = std::max(((size_t)S * pairs + pairs) * (size_t)(Hq / Hkv), (size_t)B * Hq * (size_t)S1f);
     w.table_off = round_up(w.rows * (D + 2) * sizeof(float), kAlign);
     w.counts_off = w.table_off + round_up(pairs * 2 * sizeof(int), kAlign);
@@ -450,27 +448,43 @@ int ffd_decode_attention_ex(const void* q, const void* k_codes, const void* k_ab
     const int S1f = decode_splits(B, Hkv, Lcap, num_splits);
     const FfdWorkspace W = ffd_layout(B, Hq, Hkv, Lcap, D, S, S1f);
     uint8_t* ws = static_cast<uint8_t*>(workspace);
-    float* part_m = reinterpret_cast<float*>(ws);
-    float* part_l = part_m + W.rows;
-    float* part_acc = part_l + W.rows;
     int2* table = reinterpret_cast<int2*>(ws + W.table_off);
-    int* counts = reinterpret_cast<int*>(ws + W.counts_off);
     uint32_t* lists = reinterpret_cast<uint32_t*>(ws + W.lists_off);
     float* sigma = reinterpret_cast<float*>(ws + W.sigma_off);
     const int S1 = scan_splits(B, Hkv, Lcap);
     const int npairs = B * Hkv;
-    const int Wr = S * npairs;
+    const int nent = top_k > 0 ? npairs : npairs * S1;                  // kept lists, one record each
+    // The records take the block scores' place (unused by top-delta), or, where those are in use or too
+    // few (a group of less than four scores), the end of the partials' region; there is one record per
+    // group then, and the refinement gets as many workgroups fewer as they need (2 * npairs rows of G
+    // heads at least: one remains).
+    const bool in_scores = top_k == 0 && (size_t)(Lcap / FFD_BLOCK) * G >= 4 * (size_t)S1;
+    const size_t row_bytes = (size_t)G * (D + 2) * sizeof(float), info_bytes = (size_t)nent * sizeof(int4);
+    const size_t part_bytes = W.rows * (D + 2) * sizeof(float);
+    const size_t info_off = in_scores ? W.sigma_off : (part_bytes - info_bytes) & ~(size_t)15;
+    int4* info = reinterpret_cast<int4*>(ws + info_off);
+    const long long max_rows = (long long)((in_scores ? part_bytes : info_off) / row_bytes);
+    // refinement workgroups: num_splits per group on average, or one per CU; their W + npairs - 1 rows
+    // of partials have to fit
+    long long Wr = num_splits > 0 ? (long long)S * npairs : std::min((long long)(S + 1) * npairs, (long long)device_cus());
+    const long long max_units = max_rows - npairs + 1;
+    Wr = std::max(1LL, std::min(Wr, max_units));
+    const size_t rows = (size_t)(max_units + npairs - 1) * G;
+    int* ticket = reinterpret_cast<int*>(ws + W.counts_off);
+    float* part_m = reinterpret_cast<float*>(ws);
+    float* part_l = part_m + rows;
+    float* part_acc = part_l + rows;
     ScanArgs sa{static_cast<const uint16_t*>(q), static_cast<const uint32_t*>(k_codes),
                 static_cast<const uint16_t*>(k_absmax), static_cast<const int8_t*>(k_resid), seq_lens, lists,
-                counts, sigma, block_mask, m_tilde, Hq, Hkv, Lcap, G, S1, delta, scale, n_sink, n_local};
+                info, table, ticket, sigma, block_mask, m_tilde, Hq, Hkv, Lcap, G, S1, delta, scale, n_sink, n_local};
     RefineArgs ra{static_cast<const uint16_t*>(q), static_cast<const uint32_t*>(k_codes),
-                  static_cast<const uint16_t*>(k_absmax),
-                  static_cast<const int8_t*>(k_resid), static_cast<const uint16_t*>(v), seq_lens, lists,
-                  counts, table, part_m, part_l, part_acc, Hq, Hkv, Lcap, G, S1, Wr, npairs, scale,
-                  thumb_top_level(thumb_bits)};
-    TopkArgs ta{sigma, seq_lens, lists, counts, block_mask, Hq, Hkv, Lcap, S1, top_k};
+                  static_cast<const uint16_t*>(k_absmax), static_cast<const int8_t*>(k_resid),
+                  static_cast<const uint16_t*>(v), lists, info, table, ticket, part_m, part_l, part_acc, Lcap, G, (int)Wr,
+                  num_splits > 0 ? (int)Wr : (int)std::min(max_units, 1LL << 20), nent,
+                  scale, thumb_top_level(thumb_bits)};
+    TopkArgs ta{sigma, seq_lens, lists, info, table, ticket, block_mask, Hq, Hkv, Lcap, top_k};
     const dim3 scan_grid((unsigned)S1, (unsigned)Hkv, (unsigned)B);
-    const dim3 refine_grid((unsigned)(Wr + npairs));
+    const dim3 refine_grid((unsigned)Wr);
     auto mark = [&](int i) {
         return stage_events && hipEventRecord(stage_events[i], stream) != hipSuccess ? FFD_ERR_HIP : FFD_OK;
     };
@@ -482,16 +496,20 @@ int ffd_decode_attention_ex(const void* q, const void* k_codes, const void* k_ab
         // top-delta, fused: one kernel, then the merge of its S1f partial states per head (none when
         // S1f == 1: the kernel writes the outputs itself)
         const bool direct = S1f == 1;
+        const size_t frows = (size_t)B * Hq * S1f;
+        float* fpart_m = reinterpret_cast<float*>(ws);
+        float* fpart_l = fpart_m + frows;
+        float* fpart_acc = fpart_l + frows;
         FusedArgs fa{static_cast<const uint16_t*>(q), static_cast<const uint32_t*>(k_codes),
                      static_cast<const uint16_t*>(k_absmax), static_cast<const int8_t*>(k_resid),
-                     static_cast<const uint16_t*>(v), seq_lens, block_mask, m_tilde, part_m, part_l, part_acc,
+                     static_cast<const uint16_t*>(v), seq_lens, block_mask, m_tilde, fpart_m, fpart_l, fpart_acc,
                      direct ? static_cast<uint16_t*>(out) : nullptr, direct ? lse : nullptr,
                      Hq, Hkv, Lcap, G, S1f, delta, scale, n_sink, n_local};
         launch_fused(thumb_bits, G <= 4 ? 1 : 2, mode, dim3((unsigned)S1f, (unsigned)Hkv, (unsigned)B), stream, fa);
         if ((st = launch_status()) != FFD_OK || (st = mark(1)) != FFD_OK || (st = mark(2)) != FFD_OK) return st;
         if (!direct) {
-            hipLaunchKernelGGL(lse_merge_kernel, dim3((unsigned)(B * Hq)), dim3(kThreads), 0, stream, part_m,
-                               part_l, part_acc, S1f, nullptr, 1, static_cast<uint16_t*>(out), lse);
+            hipLaunchKernelGGL(lse_merge_kernel, dim3((unsigned)(B * Hq)), dim3(kThreads), 0, stream, fpart_m,
+                               fpart_l, fpart_acc, S1f, nullptr, 1, static_cast<uint16_t*>(out), lse);
             if ((st = launch_status()) != FFD_OK) return st;
         }
         return mark(3);
@@ -505,6 +523,10 @@ int ffd_decode_attention_ex(const void* q, const void* k_codes, const void* k_ab
         else if (G == 2) hipLaunchKernelGGL(ffd_topk_select_kernel<2>, grid, block, 0, stream, ta);
         else if (G == 4) hipLaunchKernelGGL(ffd_topk_select_kernel<4>, grid, block, 0, stream, ta);
         else hipLaunchKernelGGL(ffd_topk_select_kernel<8>, grid, block, 0, stream, ta);
+        if ((st = launch_status()) != FFD_OK) return st;
+    }
+    if (nent > kRefineRecords) {
+        hipLaunchKernelGGL(ffd_offsets_kernel, dim3(1), dim3(kOffsetThreads), 0, stream, info, nent);
         if ((st = launch_status()) != FFD_OK) return st;
     }
     if ((st = mark(1)) != FFD_OK) return st;

@@ -31,15 +31,17 @@
 //      done, takes the keep decision per (head, block): the kept blocks, with their per-head keep
 //      bits, form its workgroup's kept list (in block order) in the workspace, plus the list's
 //      length;
-//    - ffd_refine_kernel gives each (sequence, KV head) a number of workgroups proportional to its
-//      kept blocks (every workgroup computes the same allocation from the scan's counts, so no
-//      cross-workgroup synchronisation is needed); each 8-wave workgroup refines an equal share of
-//      its group's kept blocks, wave w taking 16-token tile w % 4 of every other block, with
-//      several tiles' residual and value loads in flight, and writes one partial (m, l, acc) per
-//      head; lse_merge_kernel combines the partials of each head through a small per-group table.
+//    - ffd_refine_kernel lays the kept blocks of all groups on one line and gives each 8-wave
+//      workgroup an equal share of it (every workgroup computes the same line from the scan's
+//      records, so no cross-workgroup synchronisation is needed), wave w taking 16-token tile w % 4
+//      of every other block, with several tiles' residual and value loads in flight; it writes one
+//      partial (m, l, acc) per head of every group in its share, and lse_merge_kernel combines the
+//      partials of each head through a small per-group table.
 // Both recompute the scan scores s_hat of each kept tile from its codes (Eq. 4's reuse term: the
 // same integer MFMA and fp32 operations as the scan, so the same values; storing them would cost
 // as many bytes, written then read).
+#include <type_traits>
+
 #include "ffd_device.h"
 #include "ffd_kernels.h"
 
@@ -55,7 +57,6 @@ namespace {
 #endif
 constexpr int kRing2 = FFD_SCAN_RING;         // 2-bit scan loads in flight per wave (blocks)
 constexpr int kRefineRing = FFD_REFINE_RING;  // refinement tiles in flight per wave
-constexpr int kChunk = kFfdChunk;             // list entries staged per pass of the refinement kernel
 
 __device__ __forceinline__ int limb_of(int Q, int which) {
     const int l0 = ((Q + 128) & 255) - 128;
@@ -103,31 +104,26 @@ struct QueryLds {
     float kap2[4 * NT];
 };
 
-// This lane's dword (dims 2*lane, 2*lane + 1) of the queries of heads wave + 4t of the group.
+// Wave w < 4 NT: this lane's dword (dims 2*lane, 2*lane + 1) of head min(w, G - 1) of the group whose
+// first query row is row0.
 template <int NT>
-__device__ __forceinline__ void load_query_words(const uint16_t* __restrict__ q, int b, int Hq, int hq0,
-                                                 int G, int wave, int lane, uint32_t (&qw)[NT]) {
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-        qw[t] = reinterpret_cast<const uint32_t*>(q + ((size_t)b * Hq + hq0 + min(wave + 4 * t, G - 1)) * kD)[lane];
+__device__ __forceinline__ uint32_t load_query_word(const uint16_t* __restrict__ q, size_t row0, int G, int wave, int lane) {
+    return reinterpret_cast<const uint32_t*>(q + (row0 + min(wave, G - 1)) * kD)[lane];
 }
 
-// Queries -> fixed-point limbs in LDS and this lane's per-head constants. Head h (wave h % 4): E with
-// max|q| < 2^E, Q = rint(q 2^(22-E)) split into three signed bytes stored as limbs[limb][h][d]; the
-// fourth limb row and heads past G stay zero. lv is the thumbnail's outer level Lv. Contains two
-// workgroup barriers.
+// Queries -> fixed-point limbs in LDS and this lane's per-head constants, by the workgroup's eight
+// waves. Head h (wave h): E with max|q| < 2^E, Q = rint(q 2^(22-E)) split into three signed bytes
+// stored as limbs[limb][h][d]; the fourth limb row and heads past G are zero. lv is the thumbnail's
+// outer level Lv. One workgroup barrier, before the constants are read; the caller sees to it that no
+// wave still reads those of an earlier group.
 template <int NT>
-__device__ __forceinline__ void build_query_consts(QueryLds<NT>& sm, const uint32_t (&qw)[NT], int G,
-                                                   float scale, float lv, int tid, HeadConsts<NT>& hc) {
-    const int wave = tid >> 6, lane = tid & 63, g = lane >> 4, n = lane & 15;
-    for (int i = tid; i < 4 * 4 * NT * kD / 4; i += kThreads) reinterpret_cast<int*>(sm.limbs)[i] = 0;
-    __syncthreads();
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        const int h = wave + 4 * t;
-        if (h >= G) continue;
-        const float x0 = bf16_lo(qw[t]), x1 = bf16_hi(qw[t]);         // dims 2*lane, 2*lane + 1
-        const float mx = wave_max(fmaxf(fabsf(x0), fabsf(x1)));
+__device__ __forceinline__ void build_query_consts(QueryLds<NT>& sm, uint32_t qw, int G, float scale, float lv, int wave,
+                                                   int lane, HeadConsts<NT>& hc) {
+    const int g = lane >> 4, n = lane & 15;
+    if (wave < 4 * NT) {
+        const bool live = wave < G;
+        const float x0 = live ? bf16_lo(qw) : 0.f, x1 = live ? bf16_hi(qw) : 0.f;     // dims 2*lane, 2*lane + 1
+        const float mx = wave_max_dpp(fmaxf(fabsf(x0), fabsf(x1)));
         int E = 0;
         (void)frexpf(mx, &E);                       // mx < 2^E (mx == 0 -> E = 0)
         const int Q0 = (int)rintf(ldexpf(x0, 22 - E));
@@ -135,13 +131,14 @@ __device__ __forceinline__ void build_query_consts(QueryLds<NT>& sm, const uint3
 #pragma unroll
         for (int li = 0; li < 3; ++li) {
             const uint32_t pair = ((uint32_t)limb_of(Q0, li) & 0xffu) | (((uint32_t)limb_of(Q1, li) & 0xffu) << 8);
-            reinterpret_cast<uint16_t*>(&sm.limbs[li][h][0])[lane] = (uint16_t)pair;
+            reinterpret_cast<uint16_t*>(&sm.limbs[li][wave][0])[lane] = (uint16_t)pair;
         }
-        const int sum = wave_sum_i(Q0 + Q1);
+        reinterpret_cast<uint16_t*>(&sm.limbs[3][wave][0])[lane] = 0;
+        const int sum = wave_sum_dpp(Q0 + Q1);
         if (lane == 0) {
-            sm.sumq[h] = sum;
-            sm.kap[h] = ldexpf(scale / lv, E - 23);
-            sm.kap2[h] = ldexpf(scale / (254.f * lv), E - 22);
+            sm.sumq[wave] = sum;
+            sm.kap[wave] = ldexpf(scale / lv, E - 23);
+            sm.kap2[wave] = ldexpf(scale / (254.f * lv), E - 22);
         }
     }
     __syncthreads();
@@ -153,52 +150,6 @@ __device__ __forceinline__ void build_query_consts(QueryLds<NT>& sm, const uint3
         for (int cc = 0; cc < 2; ++cc)
             hc.A[t][cc] = *reinterpret_cast<const v4i*>(&sm.limbs[limb][hrow][64 * cc + 16 * g]);
         const int hh = 4 * t + g;      // this lane's output head
-        hc.live[t] = hh < G;
-        hc.sumq[t] = hc.live[t] ? sm.sumq[hh] : 0;
-        hc.kap[t] = hc.live[t] ? sm.kap[hh] : 0.f;
-        hc.kap2[t] = hc.live[t] ? sm.kap2[hh] : 0.f;
-    }
-}
-
-// The same constants built by one wave alone, with no workgroup barrier: the wave computes every
-// head (qa[h]: this lane's dword of head h, any value for h >= G) and writes the whole limb table;
-// every wave of a workgroup writes identical values, so each may read back what it wrote itself
-// (one wave's LDS operations execute in order) without waiting for the others. Bit for bit the
-// values of build_query_consts.
-template <int NT>
-__device__ __forceinline__ void build_query_consts_wave(QueryLds<NT>& sm, const uint32_t (&qa)[4 * NT], int G,
-                                                        float scale, float lv, int lane, HeadConsts<NT>& hc) {
-    const int g = lane >> 4, n = lane & 15;
-#pragma unroll
-    for (int h = 0; h < 4 * NT; ++h) {
-        const bool live = h < G;
-        const float x0 = live ? bf16_lo(qa[h]) : 0.f, x1 = live ? bf16_hi(qa[h]) : 0.f;
-        const float mx = wave_max_dpp(fmaxf(fabsf(x0), fabsf(x1)));
-        int E = 0;
-        (void)frexpf(mx, &E);                       // mx < 2^E (mx == 0 -> E = 0)
-        const int Q0 = (int)rintf(ldexpf(x0, 22 - E));
-        const int Q1 = (int)rintf(ldexpf(x1, 22 - E));
-#pragma unroll
-        for (int li = 0; li < 3; ++li) {
-            const uint32_t pair = ((uint32_t)limb_of(Q0, li) & 0xffu) | (((uint32_t)limb_of(Q1, li) & 0xffu) << 8);
-            reinterpret_cast<uint16_t*>(&sm.limbs[li][h][0])[lane] = (uint16_t)pair;
-        }
-        reinterpret_cast<uint16_t*>(&sm.limbs[3][h][0])[lane] = 0;
-        const int sum = wave_sum_dpp(Q0 + Q1);
-        if (lane == 0) {
-            sm.sumq[h] = sum;
-            sm.kap[h] = ldexpf(scale / lv, E - 23);
-            sm.kap2[h] = ldexpf(scale / (254.f * lv), E - 22);
-        }
-    }
-    wave_lds_fence();
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        const int hrow = 4 * t + (n >> 2), limb = n & 3;
-#pragma unroll
-        for (int cc = 0; cc < 2; ++cc)
-            hc.A[t][cc] = *reinterpret_cast<const v4i*>(&sm.limbs[limb][hrow][64 * cc + 16 * g]);
-        const int hh = 4 * t + g;
         hc.live[t] = hh < G;
         hc.sumq[t] = hc.live[t] ? sm.sumq[hh] : 0;
         hc.kap[t] = hc.live[t] ? sm.kap[hh] : 0.f;
@@ -370,22 +321,14 @@ __device__ __forceinline__ RefineTile<NT, RBITS> load_refine_tile(const int8_t* 
     return r;
 }
 
-constexpr int kPairChunk = 4 * kThreads;     // KV groups allocated per pass (4 per thread)
-constexpr int kCountCache = 4096;            // scan counts kept in LDS when they all fit
-
 template <int NT>
 struct RefineLds {
     QueryLds<NT> qs;
-    int wsum[2][kRefineWaves];           // wg_exclusive_scan scratch, alternating halves
-    int sel[4];                          // this workgroup's KV group: pair, first workgroup, workgroups, kept
-    int pn[kPairChunk];                  // kept blocks per KV group of the current pass (large inputs)
-    int cnt[kCountCache + 1];            // exclusive prefix of all scan counts, when they fit
-    int pref[kFfdMaxScanSplits + 1];     // exclusive prefix of the group's per-split counts (large inputs)
+    int4 rec[kRefineRecords + 1];        // the scan's records, .x their prefix on the line
+    int unit[2];                         // the next unit, by turns
+    int4 list[kRefineChunk];             // staged kept blocks: j | keep bits << 24, group, sequence length
     TileP<NT> tp[kRefineWaves];
-    union {
-        uint32_t list[kChunk];           // kept blocks of the share: j | keep bits << 24
-        EpilogueLds<NT, kRefineWaves> epi;
-    } u;
+    EpilogueLds<NT, kRefineWaves> epi;
 };
 
 }  // namespace
@@ -446,9 +389,16 @@ __global__ __launch_bounds__(kScanThreads, scan_occupancy<BITS>()) void ffd_scan
     const int nblk_cap = a.Lcap / kBlock;
     const int bps = (nblk + a.S1 - 1) / a.S1;
     const int jb = min(s * bps, nblk), je = min(jb + bps, nblk);
+    // this workgroup's record for the refinement, and the group's entry of the merge table (no rows
+    // until the refinement meets a kept block)
+    auto write_record = [&](int kept) {
+        if (tid == 0) a.info[bh * a.S1 + s] = make_int4(kept, L, (int)bh, s | (a.S1 << kInfoSplitBits));
+        if (tid == 0 && s == 0) a.table[bh] = make_int2(0, -1);
+        if (tid == 0 && s == 0 && bh == 0) *a.ticket = 0;
+    };
     if (jb >= je && (kTopK || !a.mask)) {       // nothing to scan (short sequence), nothing to clear
         if constexpr (!kTopK) {
-            if (tid == 0) a.counts[bh * a.S1 + s] = 0;
+            write_record(0);
             if (a.m_tilde && s == 0 && tid < G) a.m_tilde[(size_t)b * a.Hq + hq0 + tid] = -INFINITY;   // L = 0
         }
         return;
@@ -482,8 +432,7 @@ __global__ __launch_bounds__(kScanThreads, scan_occupancy<BITS>()) void ffd_scan
     // workgroup-wide window pass before the stream held every wave until the slowest one's window
     // blocks had arrived behind the whole chip's first round: 6 us at the median, 20 us at worst at
     // 4 x 128K). Until then a block costs G floats of LDS.
-    uint32_t qw[NT];
-    load_query_words<NT>(a.q, b, a.Hq, hq0, G, wave, lane, qw);
+    const uint32_t qw = load_query_word<NT>(a.q, (size_t)b * a.Hq + hq0, G, wave, lane);
     const int jlast = max(nblk, 1) - 1;
     const int sink_end = min(a.n_sink, L);
     const int loc_beg = max(0, L - a.n_local);
@@ -503,7 +452,7 @@ __global__ __launch_bounds__(kScanThreads, scan_occupancy<BITS>()) void ffd_scan
     if constexpr (MODE == kSelRefinedPM) load_window(0);
 
     HeadConsts<NT> hc;
-    build_query_consts<NT>(sm.qs, qw, G, a.scale, thumb_top_level(BITS), tid, hc);
+    build_query_consts<NT>(sm.qs, qw, G, a.scale, thumb_top_level(BITS), wave, lane, hc);
 
     // ---- scan (Alg. 1): block maxima sigma per head, and the pseudo-max's window maxima -------
     float pm[NT];
@@ -625,7 +574,7 @@ __global__ __launch_bounds__(kScanThreads, scan_occupancy<BITS>()) void ffd_scan
         total += c;
     }
     if (bits != 0) a.lists[bh * (size_t)nblk_cap + jb + before + below] = (uint32_t)jl | (bits << 24);
-    if (tid == 0) a.counts[bh * a.S1 + s] = total;
+    write_record(total);
 
     // Mask entries past the end of the sequence are zero (spread over the scan workgroups).
     if (a.mask) {
@@ -717,8 +666,7 @@ __global__ __launch_bounds__(kScanThreads, 1) void ffd_decode_kernel(FusedArgs a
     for (int r = 0; r < kRing; ++r) is[r] = kRing * wave + r;
 
     // Requests: queries, the first window blocks, the first ring round.
-    uint32_t qw[NT];
-    load_query_words<NT>(a.q, b, a.Hq, hq0, G, wave, lane, qw);
+    const uint32_t qw = load_query_word<NT>(a.q, (size_t)b * a.Hq + hq0, G, wave, lane);
     const int jlast = nblk - 1;
     const int sink_end = min(a.n_sink, L);
     const int loc_beg = max(0, L - a.n_local);
@@ -738,7 +686,7 @@ __global__ __launch_bounds__(kScanThreads, 1) void ffd_decode_kernel(FusedArgs a
     if constexpr (MODE == kSelRefinedPM) load_window(0);
 
     HeadConsts<NT> hc;
-    build_query_consts<NT>(sm.qs, qw, G, a.scale, thumb_top_level(BITS), tid, hc);
+    build_query_consts<NT>(sm.qs, qw, G, a.scale, thumb_top_level(BITS), wave, lane, hc);
 
     // ---- scan (Alg. 1): block maxima per head, and the window maxima of the pseudo-max ---------
     float pm[NT];
@@ -905,304 +853,171 @@ __global__ __launch_bounds__(kScanThreads, 1) void ffd_decode_kernel(FusedArgs a
 }
 
 // ================================================================================================
-// Refinement: Eq. 4 on the kept blocks, online softmax and PV, one partial state per workgroup.
-// Grid (W + B*Hkv). With N kept blocks in all and n_x in KV group x, group x gets
-// W_x = ceil(n_x * min(W', N) / N) workgroups (1 if n_x = 0) in group order, W' = W or, with few
-// splits, the largest W' found whose allocation still fits the grid (fill_grid); workgroup p of the
-// group refines its kept blocks of rank [p n_x / W_x, (p + 1) n_x / W_x). Workgroups past the last
-// group's exit.
+// Refinement: Eq. 4 on the kept blocks, online softmax and PV, one partial state per workgroup and
+// KV group it meets. The kept blocks of all groups, in (group, block) order, form one line on which
+// every group is preceded by kGroupCost positions that hold no block (the price of beginning a group:
+// its query constants and one more partial state); workgroup w of W takes the positions
+// [w T / W, (w + 1) T / W) of the T in all, so shares are equal whatever the groups hold and cross
+// group boundaries where they must. Its partial of group x goes to row w + x: along the line w + x
+// grows with every change of w or x, so no two partials share a row and a group's rows are consecutive.
+// Bound: HBM (the gather of the kept blocks arrives at 5.2 to 5.8 TB/s). A whole number of workgroups
+// per group, and one fixed share each, took 397 us where half of 16 sequences of 8K to 128K tokens is
+// kept (2.1 GB; the step 477 us); equal shares and units from a counter take 372 us (446 us). At 4 x
+// 128K, 6 % kept, the step went from 58.5 to 56.9 us.
 // ================================================================================================
+// Exclusive prefix, on the line, of the scan's records in front of the refinement when there are more
+// than a workgroup keeps in LDS: one workgroup; info[i].x becomes the prefix of record i, info[0].x
+// (whose prefix is 0) the line's length.
+__global__ __launch_bounds__(kOffsetThreads) void ffd_offsets_kernel(int4* info, int nent) {
+    __shared__ int wsum[2][kOffsetThreads / 64];
+    int run = 0, half = 0;
+    for (int i0 = 0; i0 < nent; i0 += kOffsetThreads) {
+        const int i = i0 + (int)threadIdx.x;
+        int cost = 0;
+        if (i < nent) {
+            const int4 e = info[i];
+            cost = e.x + ((e.w & kInfoSplitMask) == 0 ? kGroupCost : 0);
+        }
+        int tot = 0;
+        const int before = wg_exclusive_scan<kOffsetThreads / 64>(cost, wsum[half], &tot);
+        half ^= 1;
+        if (i > 0 && i < nent) info[i].x = run + before;
+        run += tot;
+    }
+    if (threadIdx.x == 0) info[0].x = run;
+}
+
 template <int NT, int RBITS>
 __global__ __launch_bounds__(kRefineThreads, 1) void ffd_refine_kernel(RefineArgs a) {
     __shared__ RefineLds<NT> sm;
-    const int wg = blockIdx.x;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int g = lane >> 4, n = lane & 15;
     constexpr int kPar = kRefineWaves / 4;          // waves per tile index
-    const int T4 = wave & 3, par = wave >> 2;       // tile T4 of the share's entries par, par + kPar, ...
-    const int G = a.G, S1 = a.S1, npairs = a.npairs;
+    const int T4 = wave & 3, par = wave >> 2;       // tile T4 of the staged entries par, par + kPar, ...
+    const int G = a.G, nent = a.nent;
+    const int nblk_cap = a.Lcap / kBlock;
 
-    // ---- allocation: total kept N, then this workgroup's KV group ---------------------------
-    // Usual case (at most 1024 scan counts and 256 KV groups): every wave computes the whole
-    // allocation on its own, with no workgroup barrier. Lane l loads counts [16l, 16l + 16), one
-    // wave prefix gives their exclusive prefix in (group, split) order, which every wave writes to
-    // LDS (identical values, so each reads back its own writes), then lane l allocates groups
-    // 4l .. 4l + 3 and a second wave prefix numbers their workgroups. Larger inputs: all scan counts
-    // kept in LDS with workgroup scans (up to 4096), else summed per group in passes of kPairChunk
-    // groups with LDS atomics.
-    const int total = npairs * S1;
-    const bool fast = total <= 16 * 64 && npairs <= 4 * 64;
-    const bool cached = total <= kCountCache && npairs <= kPairChunk;
-    int N = 0, running = 0, half = 0;
-    auto scan = [&](int v, int* tot) {
-        const int e = wg_exclusive_scan<kRefineWaves>(v, sm.wsum[half], tot);
-        half ^= 1;
-        return e;
-    };
-    const long long W = a.W;
-    // ceil(n_x * We / N) workgroups for n_x > 0, We = min(W, N) or the grid-filling W' below; exact
-    // in fp64 (the numerator stays below 2^52, and fl(u / N) cannot round up to an integer when
-    // u < 2^52)
-    auto alloc = [&](int nx, long long Weff) {
-        return nx > 0 ? (int)floor(((double)nx * (double)Weff + (double)(N - 1)) / (double)N) : 1;
-    };
-    // The rounding up in alloc leaves up to one workgroup per group of the grid's W + B*Hkv unused.
-    // When that can be a third of the grid or more (W <= 2 B*Hkv: many groups, few splits), grow
-    // the effective W by the unused count while the allocation still fits the grid (at most three
-    // steps, each halved once if it overshoots), so fewer CUs idle and the largest share shrinks
-    // (the ragged batch of 16 sequences, 128 groups on 256 workgroups: refinement 422 -> 397 us).
-    // With more splits the slack is small and the extra evaluations cost more than they save (4 x
-    // 128K, delta 5: +2 us), so W is used as it is. total(We) is the allocation's workgroup count
-    // for an effective We, the same value in every thread; the result depends only on the counts,
-    // like the allocation itself.
-    auto fill_grid = [&](auto total) {
-        const long long grid = W + npairs;
-        const long long cap = (long long)max(N, 1);
-        long long We = min(W, cap);
-        if (W > 2LL * npairs) return We;
-        int used = total(We);
-        for (int it = 0; it < 3 && used < grid && We < cap; ++it) {
-            long long cand = min(We + (grid - used), cap);
-            int uc = total(cand);
-            if (uc > grid) {
-                cand = We + (cand - We) / 2;
-                if (cand == We) break;
-                uc = total(cand);
-                if (uc > grid) break;
-            }
-            We = cand;
-            used = uc;
-        }
-        return We;
-    };
-    int x = 0, Qx = 0, Wx = 1, nx = 0;
-    if (fast) {
-        const int i0 = 16 * lane;
-        int c[16], sum = 0;
+    // ---- the line: records and their prefix. Every wave loads all records (lane l: kPer of them from
+    // kPer l on) and writes them to LDS with their prefix: identical values, so each wave reads back its
+    // own writes and no workgroup barrier is needed.
+    const bool cached = nent <= kRefineRecords;
+    int T = 0;
+    auto load_records = [&](auto per) {
+        constexpr int kPer = decltype(per)::value;
+        int4 e[kPer];
+        int sum = 0;
 #pragma unroll
-        for (int k = 0; k < 16; k += 4) {
-            // the counts region is padded to 256 bytes, so the last int4 stays inside it
-            int4 v = make_int4(0, 0, 0, 0);
-            if (i0 + k < total) v = *reinterpret_cast<const int4*>(a.counts + i0 + k);
-            c[k] = v.x; c[k + 1] = v.y; c[k + 2] = v.z; c[k + 3] = v.w;
-        }
+        for (int k = 0; k < kPer; ++k) e[k] = kPer * lane + k < nent ? a.info[kPer * lane + k] : make_int4(0, 0, 0, 1);
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            if (i0 + k >= total) c[k] = 0;
-            sum += c[k];
+        for (int k = 0; k < kPer; ++k) {
+            const int cost = e[k].x + ((e[k].w & kInfoSplitMask) == 0 ? kGroupCost : 0);
+            e[k].x = sum;
+            sum += cost;
         }
         const int incl = wave_inclusive_scan(sum);
-        N = __builtin_amdgcn_readlane(incl, 63);
-        int run = incl - sum;
+        T = __builtin_amdgcn_readlane(incl, 63);
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            if (i0 + k < total) sm.cnt[i0 + k] = run;
-            run += c[k];
+        for (int k = 0; k < kPer; ++k) {
+            e[k].x += incl - sum;
+            if (kPer * lane + k < nent) sm.rec[kPer * lane + k] = e[k];
         }
-        if (lane == 0) sm.cnt[total] = N;
+        if (lane == 0) sm.rec[nent].x = T;
         wave_lds_fence();
-        int w4[4], n4[4], s4 = 0;                      // lane l: groups 4l .. 4l + 3
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int xi = 4 * lane + k;
-            n4[k] = xi < npairs ? sm.cnt[(xi + 1) * S1] - sm.cnt[xi * S1] : 0;
-        }
-        const long long Weff = fill_grid([&](long long We) {
-            int t = 0;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) t += 4 * lane + k < npairs ? alloc(n4[k], We) : 0;
-            return __builtin_amdgcn_readlane(wave_inclusive_scan(t), 63);
-        });
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            w4[k] = 4 * lane + k < npairs ? alloc(n4[k], Weff) : 0;
-            s4 += w4[k];
-        }
-        const int winc = wave_inclusive_scan(s4);
-        running = __builtin_amdgcn_readlane(winc, 63);
-        int q0 = winc - s4, hit = -1;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if (hit < 0 && wg >= q0 && wg < q0 + w4[k]) hit = k;
-            if (hit < 0) q0 += w4[k];
-        }
-        const uint64_t hb = __ballot(hit >= 0);
-        if (hb != 0) {                              // uniform; else wg >= running
-            const int src = __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(hb));
-            const int kk = __builtin_amdgcn_readlane(hit, src);
-            x = 4 * src + kk;
-            Qx = __builtin_amdgcn_readlane(q0, src);
-            int wsel = w4[0], nsel = n4[0];
-#pragma unroll
-            for (int k = 1; k < 4; ++k) if (kk == k) { wsel = w4[k]; nsel = n4[k]; }
-            Wx = __builtin_amdgcn_readlane(wsel, src);
-            nx = __builtin_amdgcn_readlane(nsel, src);
-        }
-    } else if (cached) {
-        const int i0 = 16 * tid;
-        int c[16], sum = 0;
-#pragma unroll
-        for (int k = 0; k < 16; k += 4) {
-            int4 v = make_int4(0, 0, 0, 0);
-            if (i0 + k < total) v = *reinterpret_cast<const int4*>(a.counts + i0 + k);
-            c[k] = v.x; c[k + 1] = v.y; c[k + 2] = v.z; c[k + 3] = v.w;
-        }
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            if (i0 + k >= total) c[k] = 0;
-            sum += c[k];
-        }
-        int run = scan(sum, &N);
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            if (i0 + k < total) sm.cnt[i0 + k] = run;
-            run += c[k];
-        }
-        if (tid == 0) sm.cnt[total] = N;
-        __syncthreads();
-        int w4[4], n4[4], s4 = 0;                      // thread t: groups 4t .. 4t + 3
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int xi = 4 * tid + k;
-            n4[k] = xi < npairs ? sm.cnt[(xi + 1) * S1] - sm.cnt[xi * S1] : 0;
-        }
-        const long long Weff = fill_grid([&](long long We) {
-            int t = 0, tot = 0;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) t += 4 * tid + k < npairs ? alloc(n4[k], We) : 0;
-            (void)scan(t, &tot);
-            return tot;
-        });
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            w4[k] = 4 * tid + k < npairs ? alloc(n4[k], Weff) : 0;
-            s4 += w4[k];
-        }
-        int q0 = scan(s4, &running);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if (4 * tid + k < npairs && wg >= q0 && wg < q0 + w4[k]) {
-                sm.sel[0] = 4 * tid + k;
-                sm.sel[1] = q0;
-                sm.sel[2] = w4[k];
-                sm.sel[3] = n4[k];
-            }
-            q0 += w4[k];
-        }
-    } else {
-        int part = 0;
-        for (int i = tid; i < total; i += kRefineThreads) part += a.counts[i];
-        (void)scan(part, &N);
-        const long long Weff = min(W, (long long)max(N, 1));
-        for (int c0 = 0; c0 < npairs; c0 += kPairChunk) {
-            const int np = min(kPairChunk, npairs - c0);
-            for (int i = tid; i < np; i += kRefineThreads) sm.pn[i] = 0;
-            __syncthreads();
-            for (int i = tid; i < np * S1; i += kRefineThreads) {
-                const int c = a.counts[(size_t)c0 * S1 + i];
-                if (c) atomicAdd(&sm.pn[i / S1], c);
-            }
-            __syncthreads();
-            int w4[4], n4[4], s4 = 0;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int xi = 4 * tid + k;
-                n4[k] = xi < np ? sm.pn[xi] : 0;
-                w4[k] = xi < np ? alloc(n4[k], Weff) : 0;
-                s4 += w4[k];
-            }
-            int tot = 0;
-            int q0 = running + scan(s4, &tot);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                if (4 * tid + k < np && wg >= q0 && wg < q0 + w4[k]) {
-                    sm.sel[0] = c0 + 4 * tid + k;
-                    sm.sel[1] = q0;
-                    sm.sel[2] = w4[k];
-                    sm.sel[3] = n4[k];
-                }
-                q0 += w4[k];
-            }
-            running += tot;
-            __syncthreads();                           // pn is rewritten by the next pass
-        }
-    }
-    if (wg >= running) return;                      // uniform: beyond the last group's workgroups
-    if (!fast) {
-        __syncthreads();
-        x = sm.sel[0]; Qx = sm.sel[1]; Wx = sm.sel[2]; nx = sm.sel[3];
-    }
-    // uniform by construction; said explicitly so that the group's base addresses stay in scalar
-    // registers
-    x = __builtin_amdgcn_readfirstlane(x);
-    Qx = __builtin_amdgcn_readfirstlane(Qx);
-    Wx = __builtin_amdgcn_readfirstlane(Wx);
-    nx = __builtin_amdgcn_readfirstlane(nx);
-    const int b = x / a.Hkv, kvh = x % a.Hkv, hq0 = kvh * G;
-    const int p = wg - Qx;
-    const int r0 = (int)((long long)p * nx / Wx), r1 = (int)((long long)(p + 1) * nx / Wx);
-    const size_t bh = (size_t)x;
-    const int L = min(max(a.seq_lens[b], 0), a.Lcap);
-    const int nblk = (L + kBlock - 1) / kBlock;
-    const int nblk_cap = a.Lcap / kBlock;
-    const int bps = (nblk + S1 - 1) / S1;
-    if (p == 0 && tid == 0) a.table[x] = make_int2(Qx, Wx);
-
-    const uint16_t* absmax_bh = a.absmax + bh * (size_t)a.Lcap;
-    const int8_t* resid_bh = a.resid + bh * (size_t)a.Lcap * kD;
-    const uint16_t* v_bh = a.v + bh * (size_t)a.Lcap * kD;
-    const uint32_t* codes_bh = a.codes + bh * (size_t)a.Lcap * (4 * RBITS);
-    const uint32_t* list_bh = a.lists + bh * (size_t)nblk_cap;
-
-    // A share of at most kFastShare blocks (with the fast allocation) is staged by every wave on its
-    // own, like the allocation; a longer one in chunks with workgroup barriers.
-    constexpr int kFastShare = 256;
-    const bool fast_share = fast && r1 - r0 <= kFastShare;
-    uint32_t qw[NT];
-    uint32_t qa[4 * NT];
-    if (fast_share) {
-#pragma unroll
-        for (int h = 0; h < 4 * NT; ++h)
-            qa[h] = reinterpret_cast<const uint32_t*>(a.q + ((size_t)b * a.Hq + hq0 + min(h, G - 1)) * kD)[lane];
-    } else {
-        load_query_words<NT>(a.q, b, a.Hq, hq0, G, wave, lane, qw);
-    }
-    // exclusive prefix of the group's per-split counts: rank r lies in split s with
-    // pref(s) <= r < pref(s + 1), at list position s * bps + r - pref(s)
-    if (!cached) {
-        int run = 0;
-        for (int c0 = 0; c0 < S1; c0 += kRefineThreads) {
-            const int sidx = c0 + tid;
-            const int c = sidx < S1 ? a.counts[bh * S1 + sidx] : 0;
-            int tot = 0;
-            const int e = scan(c, &tot);
-            if (sidx < S1) sm.pref[sidx] = run + e;
-            run += tot;
-        }
-        if (tid == 0) sm.pref[S1] = run;
-        __syncthreads();
-    }
-    const int* pref = cached ? sm.cnt + x * S1 : sm.pref;
-    const int pref0 = cached ? pref[0] : 0;
-    auto list_entry = [&](int r) {                 // the kept block of rank r: j | keep bits << 24
-        int lo = 0, hi = S1;                        // largest split with pref(split) <= r
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (pref[mid] - pref0 <= r) lo = mid; else hi = mid;
-        }
-        return list_bh[lo * bps + (r - (pref[lo] - pref0))];
     };
-    HeadConsts<NT> hc;
+    if (nent <= 64 * 4) load_records(std::integral_constant<int, 4>{});
+    else if (cached) load_records(std::integral_constant<int, kRefineRecords / 64>{});
+    else T = __builtin_amdgcn_readfirstlane(a.info[0].x);
+    auto prefix = [&](int i) { return cached ? sm.rec[i].x : (i == 0 ? 0 : (i == nent ? T : a.info[i].x)); };
+    // U units on the line, usually one of equal length per workgroup (fewer where the line is shorter
+    // than that). Long shares are worked as units from a counter: the chip's memory serves its XCDs at
+    // rates that differ by up to a fifth (workgroups of equal shares of 310 blocks ended between 324 and
+    // 411 us), and a fixed share ends with the slowest. The first W units, one per workgroup, then cover
+    // kFirstShare of the line, and the rest shrinks linearly to a ninth of its first length, so that the
+    // workgroups end together. Which workgroup takes a unit does not enter the results.
+    if (T == 0) return;                             // uniform
+    const int U1 = min(a.W, T);
+    const bool queue = T / a.W >= 2 * kUnitBlocks && a.max_units >= 2 * a.W;
+    const int U = queue ? min(a.max_units, T / kUnitBlocks) : U1;
+    const double T1 = queue ? floor((double)T * kFirstShare) : (double)T;
+    // first position of unit u <= U; every unit has at least one (queued ones: at least 0.2 (1 -
+    // kFirstShare) kUnitBlocks). Products stay below 2^52, so that whole results are exact.
+    auto first_of = [&](int u) {
+        if (u <= U1) return (int)floor((double)u * T1 / (double)U1);
+        const double v = (double)(u - U1) / (double)(U - U1);
+        return u >= U ? T : (int)(T1 + floor(((double)T - T1) * v * (1.8 - 0.8 * v)));
+    };
+    int unit = blockIdx.x;
+    uint32_t qw = 0;
+    int qx = -1;                                    // the group whose queries qw holds
+    auto load_query = [&](int x) {
+        qw = load_query_word<NT>(a.q, (size_t)x * G, G, wave, lane);
+        qx = x;
+    };
 
-    PvAcc<NT> pv;
-    pv.zero();
-    float m_run[NT], l_part[NT];
+    // Stage the blocks at positions [c0, c1), at most kRefineChunk, in LDS (by every wave, as above);
+    // returns their number. The lanes that meet a group's first and last block write the group's first
+    // and last row into the table.
+    // Requests the queries of the first position's group on the way (usually the first block's).
+    auto stage = [&](int c0, int c1, bool want_query) {
+        int m = 0;
+        for (int q0 = c0; q0 < c1; q0 += 4 * 64) {
+            int4 st[4];
+            bool real[4];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) { m_run[t] = -INFINITY; l_part[t] = 0.f; }
-    TileP<NT>& tp = sm.tp[wave];
+            for (int k = 0; k < 4; ++k) {
+                const int pos = q0 + 64 * k + lane;
+                real[k] = false;
+                st[k] = make_int4(0, 0, 0, 0);
+                if (q0 + 64 * k < c1 && pos < c1) {
+                    int lo = 0, hi = nent;              // the largest record with prefix <= pos
+                    while (hi - lo > 1) {
+                        const int mid = (lo + hi) >> 1;
+                        if (prefix(mid) <= pos) lo = mid; else hi = mid;
+                    }
+                    const int4 r = cached ? sm.rec[lo] : a.info[lo];
+                    const int L = r.y, x = r.z, s = r.w & kInfoSplitMask, S = r.w >> kInfoSplitBits;
+                    if (want_query && k == 0 && q0 == c0) load_query(__builtin_amdgcn_readfirstlane(x));
+                    const int at = pos - prefix(lo) - (s == 0 ? kGroupCost : 0);
+                    real[k] = at >= 0;
+                    if (real[k]) {
+                        const int nblk = (L + kBlock - 1) / kBlock;
+                        st[k] = make_int4((int)a.lists[(size_t)x * nblk_cap + s * ((nblk + S - 1) / S) + at], x, L, 0);
+                        if (wave == 0 && pos == prefix(lo - s) + kGroupCost) a.table[x].x = unit + x;
+                        if (wave == 0 && pos == prefix(lo - s + S) - 1) a.table[x].y = unit + x;
+                    }
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const uint64_t b = __ballot(real[k]);
+                if (real[k])
+                    sm.list[m + __builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u))] = st[k];
+                m += __popcll(b);
+            }
+        }
+        wave_lds_fence();
+        return m;
+    };
 
-    // refine (Eq. 4) and attend tile T4 of one kept block
-    auto attend = [&](const RefineTile<NT, RBITS>& rt, int j, uint32_t bits) {
+    HeadConsts<NT> hc;
+    PvAcc<NT> pv;
+    float m_run[NT], l_part[NT];
+    TileP<NT>& tp = sm.tp[wave];
+    auto begin_group = [&] {                        // of the group whose queries qw holds; a barrier inside
+        build_query_consts<NT>(sm.qs, qw, G, a.scale, a.top_level, wave, lane, hc);
+        pv.zero();
+#pragma unroll
+        for (int t = 0; t < NT; ++t) { m_run[t] = -INFINITY; l_part[t] = 0.f; }
+    };
+    auto end_group = [&](int x) {                   // the barrier inside separates the groups' use of sm.qs
+        write_partials<NT, kRefineWaves>(sm.epi, pv, m_run, l_part, wave, lane, G, (size_t)(unit + x) * G, 1, a.part_m,
+                                         a.part_l, a.part_acc);
+    };
+
+    // refine (Eq. 4) and attend tile T4 of one kept block (j | keep bits << 24) of a sequence of length L
+    auto attend = [&](const RefineTile<NT, RBITS>& rt, uint32_t entry, int L) {
+        const int j = (int)(entry & 0xffffffu);
+        const uint32_t bits = entry >> 24;
         float z[NT];
         bool keep[NT];
         const float Mt = bf16_to_f32((uint16_t)rt.m);
@@ -1224,75 +1039,89 @@ __global__ __launch_bounds__(kRefineThreads, 1) void ffd_refine_kernel(RefineArg
         wave_lds_fence();
     };
 
-    // the m list entries staged in LDS: this wave takes tile T4 of entries par, par + kPar, ... with
-    // kRefineRing tiles in flight. The refill of the last round re-reads the wave's last tile
-    // (clamped): it is still cached, and a conditional refill would cost more registers than it
-    // saves. fast_consts: the query constants are built by this wave while its first tiles are in
-    // flight.
-    auto refine_entries = [&](int m, bool fast_consts) {
-        const int mine = m > par ? (m - par + kPar - 1) / kPar : 0;
-        if (mine == 0) {                            // wave-uniform
-            if (fast_consts) build_query_consts_wave<NT>(sm.qs, qa, G, a.scale, a.top_level, lane, hc);
-            return;
-        }
-        auto entry = [&](int k) { return sm.u.list[par + kPar * min(k, mine - 1)]; };
-        RefineTile<NT, RBITS> ring[kRefineRing];
-#pragma unroll
-        for (int r = 0; r < kRefineRing; ++r)
-            ring[r] = load_refine_tile<NT, RBITS>(resid_bh, v_bh, codes_bh, absmax_bh,
-                                                  (int)(entry(r) & 0xffffffu), T4, lane, L);
-        if (fast_consts) build_query_consts_wave<NT>(sm.qs, qa, G, a.scale, a.top_level, lane, hc);
-        for (int k0 = 0; k0 < mine; k0 += kRefineRing) {
-#pragma unroll
-            for (int r = 0; r < kRefineRing; ++r) {
-                const int k = k0 + r;
-                if (k < mine) {
-                    const uint32_t e = entry(k);
-                    attend(ring[r], (int)(e & 0xffffffu), e >> 24);
+    bool written = false;                           // partials were written: their LDS may still be read
+    for (int turn = 0; unit < U; turn ^= 1) {
+        int ticket = 0;
+        if (queue && tid == 0) ticket = atomicAdd(a.ticket, 1);        // arrives while the unit is worked on
+        const int pl = first_of(unit + (lane & 1));
+        const int p0 = __builtin_amdgcn_readlane(pl, 0), p1 = __builtin_amdgcn_readlane(pl, 1);
+        int cur = -1;                               // the group being attended
+        for (int c0 = p0; c0 < p1; c0 += kRefineChunk) {
+            if (c0 > p0) __syncthreads();           // every wave is done with the staged entries
+            const int m = __builtin_amdgcn_readfirstlane(stage(c0, min(c0 + kRefineChunk, p1), cur < 0));
+            if (m == 0) continue;                   // uniform in the workgroup
+            auto group_at = [&](int e) { return __builtin_amdgcn_readfirstlane(sm.list[e].y); };
+            auto group_end = [&](int e) {           // first entry after e of another group, or m
+                const int x = group_at(e);
+                for (; e < m; e += 64) {
+                    const uint64_t other = __ballot(e + lane < m && sm.list[min(e + lane, m - 1)].y != x);
+                    if (other) return e + (int)__builtin_ctzll(other);
                 }
-                ring[r] = load_refine_tile<NT, RBITS>(resid_bh, v_bh, codes_bh, absmax_bh,
-                                                      (int)(entry(k + kRefineRing) & 0xffffffu), T4, lane, L);
+                return m;
+            };
+            // this wave's tiles of the staged entries par, par + kPar, ..., kRefineRing of them in flight; the
+            // refill of the last round re-reads the wave's last tile (clamped): it is still cached, and a
+            // conditional refill would cost more registers than it saves
+            const int last = m - 1 - ((m - 1 - par) & (kPar - 1));     // the wave's last entry; -1: it has none
+            RefineTile<NT, RBITS> ring[kRefineRing];
+            uint32_t word[kRefineRing];
+            int rL[kRefineRing];
+            auto refill = [&](int r, int e) {
+                const int4 ent = sm.list[max(min(e, last), 0)];
+                word[r] = __builtin_amdgcn_readfirstlane((uint32_t)ent.x);
+                const size_t bh = (size_t)__builtin_amdgcn_readfirstlane(ent.y);
+                rL[r] = __builtin_amdgcn_readfirstlane(ent.z);
+                ring[r] = load_refine_tile<NT, RBITS>(a.resid + bh * a.Lcap * kD, a.v + bh * a.Lcap * kD,
+                                                      a.codes + bh * a.Lcap * (4 * RBITS), a.absmax + bh * a.Lcap,
+                                                      (int)(word[r] & 0xffffffu), T4, lane, rL[r]);
+            };
+            // a group's queries are requested ahead: the first one's before the tiles (its constants are
+            // built while they are in flight), the next one's when its predecessor begins
+            if (group_at(0) != cur && group_at(0) != qx) load_query(group_at(0));
+#pragma unroll
+            for (int r = 0; r < kRefineRing; ++r) refill(r, par + kPar * r);
+            int next = 0;                           // first staged entry of the next group
+            if (cur < 0 || group_at(0) == cur) {
+                if (cur < 0) {
+                    cur = group_at(0);
+                    begin_group();
+                }
+                next = group_end(0);
+                if (next < m) load_query(group_at(next));
+            }
+            for (int e0 = 0; e0 < m; e0 += kPar * kRefineRing) {       // uniform in the workgroup
+                const int e1 = min(e0 + kPar * kRefineRing, m);
+                for (int sb = e0;;) {               // the round's entries, group by group
+#pragma unroll
+                    for (int r = 0; r < kRefineRing; ++r) {
+                        const int e = e0 + kPar * r + par;
+                        if (e >= sb && e < min(next, e1)) {
+                            attend(ring[r], word[r], rL[r]);
+                            refill(r, e + kPar * kRefineRing);
+                        }
+                    }
+                    if (next >= e1) break;
+                    if (written) __syncthreads();
+                    end_group(cur);
+                    written = true;
+                    cur = group_at(next);
+                    begin_group();
+                    sb = next;
+                    next = group_end(next);
+                    if (next < m) load_query(group_at(next));
+                }
             }
         }
-    };
-
-    if (fast_share) {
-        // every wave loads the whole share's entries (lane i: ranks r0 + i + 64k) and writes them to
-        // LDS: identical values, read back by the same wave
-        const int m = r1 - r0;
-        uint32_t ent[kFastShare / 64];
-#pragma unroll
-        for (int k = 0; k < kFastShare / 64; ++k) {
-            const int i = lane + 64 * k;
-            ent[k] = i < m ? list_entry(r0 + i) : 0u;
+        if (cur >= 0) {
+            if (written) __syncthreads();
+            end_group(cur);
+            written = true;
         }
-#pragma unroll
-        for (int k = 0; k < kFastShare / 64; ++k) {
-            const int i = lane + 64 * k;
-            if (i < m) sm.u.list[i] = ent[k];
-        }
-        wave_lds_fence();
-        if (m > 0) refine_entries(m, true);
-        else build_query_consts_wave<NT>(sm.qs, qa, G, a.scale, a.top_level, lane, hc);
-        __syncthreads();                            // the list area becomes the epilogue's
-    } else {
-        bool consts_ready = false;
-        for (int c = r0; c < r1; c += kChunk) {
-            const int m = min(kChunk, r1 - c);
-            for (int i = tid; i < m; i += kRefineThreads) sm.u.list[i] = list_entry(c + i);
-            if (!consts_ready) {                    // the query loads and the list loads overlap
-                build_query_consts<NT>(sm.qs, qw, G, a.scale, a.top_level, tid, hc);
-                consts_ready = true;
-            }
-            __syncthreads();
-            refine_entries(m, false);
-            __syncthreads();                // the list is rewritten by the next chunk / the epilogue
-        }
-        if (!consts_ready) __syncthreads();
+        if (!queue) break;
+        if (tid == 0) sm.unit[turn] = (int)gridDim.x + ticket;
+        __syncthreads();                            // also: every wave is done with the staged entries
+        unit = __builtin_amdgcn_readfirstlane(sm.unit[turn]);
     }
-
-    write_partials<NT, kRefineWaves>(sm.u.epi, pv, m_run, l_part, wave, lane, G, (size_t)wg * G, 1,
-                                     a.part_m, a.part_l, a.part_acc);
 }
 
 template __global__ void ffd_scan_kernel<1, 2, kSelThumbnailPM>(ScanArgs);

@@ -85,7 +85,7 @@ __device__ __forceinline__ bool dense_balanced_share(const DenseArgs& a, int wg,
     jb = (int)((long long)p * n / Wb);
     je = (int)((long long)(p + 1) * n / Wb);
     if (p == 0 && lane == 0 && threadIdx.x == 0)
-        a.table[(size_t)b * a.Hkv + kvh] = make_int2(Qb + kvh * Wb, Wb);
+        a.table[(size_t)b * a.Hkv + kvh] = make_int2(Qb + kvh * Wb, Qb + kvh * Wb + Wb - 1);
     return true;
 }
 

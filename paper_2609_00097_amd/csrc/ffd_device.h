@@ -82,14 +82,15 @@ __device__ __forceinline__ int wave_sum_dpp(int x) {
            __builtin_amdgcn_readlane(x, 32) + __builtin_amdgcn_readlane(x, 48);
 }
 
-// Inclusive prefix sum over the 64 lanes of a wave (lane order).
+// Inclusive prefix sum over the 64 lanes of a wave (lane order): shifts within each 16-lane row, then
+// the last lane of row 0 (2) into row 1 (3) and lane 31 into rows 2 and 3.
 __device__ __forceinline__ int wave_inclusive_scan(int x) {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(x, o);
-        if (lane >= o) x += y;
-    }
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);     // row_shr:1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);     // row_bcast:15 into rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);     // row_bcast:31 into rows 2 and 3
     return x;
 }
 
@@ -107,12 +108,7 @@ __device__ __forceinline__ void wave_lds_fence() {
 template <int NW = kWaves>
 __device__ __forceinline__ int wg_exclusive_scan(int x, int* wsum, int* total) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int incl = x;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(incl, o);
-        if (lane >= o) incl += y;
-    }
+    const int incl = wave_inclusive_scan(x);
     if (lane == 63) wsum[wave] = incl;
     __syncthreads();
     int before = 0, tot = 0;

@@ -6,8 +6,23 @@
 
 namespace ffd {
 
-// Kept-block list entries staged in LDS per pass of the refinement kernel.
-constexpr int kFfdChunk = 1024;
+// Refinement: line positions whose blocks are staged in LDS at a time, and scan records kept in LDS
+// (more go through ffd_offsets_kernel).
+constexpr int kRefineChunk = 256;
+constexpr int kRefineRecords = 1024;
+constexpr int kOffsetThreads = 1024;
+// Line positions that a group's beginning counts for, in blocks: at 4 x 128K, 15 blocks per workgroup,
+// a step takes 59.0 us with 0, 57.8 with 2, 56.8 with 5 and 6, 57.1 with 8, 57.4 with 12.
+constexpr int kGroupCost = 6;
+// Units where workgroups take several: blocks per unit on average, at least, and the share of all blocks
+// in the workgroups' first units. Ragged batch of 16, 310 blocks per workgroup, 897 units: 446 us per
+// step; first share 0.7: 448, 0.9: 448; at least 96 blocks per unit: 450.
+constexpr int kUnitBlocks = 48;
+constexpr double kFirstShare = 0.82;
+// A record int4 describes one kept list: (kept blocks, sequence length, KV group, split | splits <<
+// kInfoSplitBits); the list of split s of S starts at the group's block s * ceil(blocks / S).
+constexpr int kInfoSplitBits = 11;
+constexpr int kInfoSplitMask = (1 << kInfoSplitBits) - 1;
 // Most blocks one scan workgroup covers (its kept list is staged in LDS), most scan workgroups per
 // (sequence, KV head).
 constexpr int kFfdMaxScanBlocks = 256;
@@ -18,7 +33,7 @@ constexpr int kScanThreads = 64 * kScanWaves;
 // blocks are kept: 430 us of refinement against 503 us with 4 waves) and costs nothing at 4 x 128K.
 constexpr int kRefineWaves = 8;
 constexpr int kRefineThreads = 64 * kRefineWaves;
-constexpr int kFfdMaxScanSplits = 1024;
+constexpr int kFfdMaxScanSplits = 1024;        // below 2^kInfoSplitBits
 
 // Thumbnail depth b (App. C: 2+8, 4+8, 8+8): 2^b levels c - Lv, Lv = (2^b - 1) / 2; a token's codes
 // take 4b words.
@@ -31,7 +46,9 @@ struct ScanArgs {
     const int8_t* resid;        // [B, Hkv, Lcap/16, 2, 64, 16]: read for the refined pseudo-max only
     const int32_t* seq_lens;    // [B]
     uint32_t* lists;            // [B*Hkv, Lcap/64]: kept blocks j | keep bits << 24, per scan split
-    int* counts;                // [B*Hkv, S1]: kept blocks per scan split
+    int4* info;                 // [B*Hkv, S1]: one record per kept list
+    int2* table;                // [B*Hkv]: set to (0, -1)
+    int* ticket;                // the refinement's unit counter: set to 0
     float* sigma;               // top-k selection: block scores [B*Hkv, Lcap/64, G]
     uint8_t* mask;              // [B, Hq, Lcap/64] or null
     float* m_tilde;             // [B, Hq] or null: the pseudo-max of each head
@@ -46,14 +63,14 @@ struct RefineArgs {
     const uint16_t* absmax;     // bf16 [B, Hkv, Lcap/64, 16, 4]
     const int8_t* resid;        // [B, Hkv, Lcap/16, 2, 64, 16]
     const uint16_t* v;          // bf16 [B, Hkv, Lcap, 128]
-    const int32_t* seq_lens;    // [B]
-    const uint32_t* lists;      // written by ffd_scan_kernel
-    const int* counts;          // written by ffd_scan_kernel
-    int2* table;                // [B*Hkv]: (first workgroup, workgroups) of each KV group
-    float* part_m;              // [(W + B*Hkv) * G]
+    const uint32_t* lists;      // written by ffd_scan_kernel or ffd_topk_select_kernel
+    const int4* info;           // their records, in (group, split) order
+    int2* table;                // [B*Hkv]: (first row, last row) of each KV group, rows in units of G heads
+    int* ticket;                // units taken from the counter
+    float* part_m;              // [(max_units + B*Hkv - 1) * G]
     float* part_l;
-    float* part_acc;            // [(W + B*Hkv) * G, 128]
-    int Hq, Hkv, Lcap, G, S1, W, npairs;
+    float* part_acc;            // [(max_units + B*Hkv - 1) * G, 128]
+    int Lcap, G, W, max_units, nent;       // W workgroups, as many units or up to max_units of them
     float scale;
     float top_level;            // Lv of the thumbnail depth: the residual step is M / (254 Lv)
 };
@@ -80,21 +97,23 @@ struct FusedArgs {
 };
 
 // Fixed-budget (top-k) selection over the block scores the scan kernel wrote; its output takes the
-// place of the scan's kept lists and counts (each group's whole list in split 0).
+// place of the scan's kept lists and records (each group's whole list as one split).
 struct TopkArgs {
     const float* sigma;         // [B*Hkv, Lcap/64, G]
     const int32_t* seq_lens;    // [B]
     uint32_t* lists;            // [B*Hkv, Lcap/64]: kept blocks j | keep bits << 24, in block order
-    int* counts;                // [B*Hkv, S1]: the list length in split 0, zero elsewhere
+    int4* info;                 // [B*Hkv]: the group's record (one split)
+    int2* table;                // [B*Hkv]: set to (0, -1)
+    int* ticket;                // the refinement's unit counter: set to 0
     uint8_t* mask;              // [B, Hq, Lcap/64] or null
-    int Hq, Hkv, Lcap, S1, k;
+    int Hq, Hkv, Lcap, k;
 };
 
 // Dense decode. Balanced mode (table != null, B <= kDenseBalanceMaxSeqs): a 1-D grid of
 // (S + 1) * B * Hkv workgroups; sequence b (n_b blocks) gets W_b = ceil(n_b * min(W, N) / N)
 // workgroups per KV head (W = S * B * Hkv, N = Hkv * sum n_b; 1 for an empty sequence), numbered in
 // (sequence, KV head) order, each taking an equal run of the sequence's blocks and writing its
-// partial rows at its own index (table[b * Hkv + kvh] = first workgroup, count). Otherwise a grid
+// partial rows at its own index (table[b * Hkv + kvh] = first and last workgroup). Otherwise a grid
 // (S, Hkv, B) of equal runs per sequence with rows [B, Hq, S].
 constexpr int kDenseBalanceMaxSeqs = 256;
 struct DenseArgs {
@@ -105,7 +124,7 @@ struct DenseArgs {
     float* part_m;
     float* part_l;
     float* part_acc;
-    int2* table;                // balanced mode: [B * Hkv] (first workgroup, workgroups); else null
+    int2* table;                // balanced mode: [B * Hkv] (first, last workgroup); else null
     int B, Hq, Hkv, Lcap, G, S;
     float scale;
 };
@@ -136,7 +155,7 @@ struct AppendArgs {
 //  kSelThumbnailPM  top-delta against the pseudo-max of the window tokens' thumbnail scores (Alg. 1);
 //  kSelRefinedPM    top-delta against the pseudo-max of their refined logits (Eq. 3's reading);
 //  kSelTopK         no decision: the block scores go to the workspace for ffd_topk_select_kernel.
-// The first two write the kept lists and counts; no mode stores the scan scores.
+// The first two write the kept lists and records; no mode stores the scan scores.
 enum ScanMode { kSelThumbnailPM = 0, kSelRefinedPM = 1, kSelTopK = 2 };
 template <int NT, int BITS, int MODE> __global__ void ffd_scan_kernel(ScanArgs a);
 // MODE kSelThumbnailPM or kSelRefinedPM; the scan scores of the kept tiles are recomputed from the
@@ -145,6 +164,7 @@ template <int NT, int BITS, int MODE> __global__ void ffd_decode_kernel(FusedArg
 // The scan scores of the kept tiles (Eq. 4's first term) are recomputed from the RBITS-bit codes with
 // the scan kernel's own integer MFMA and fp32 operations, so they equal the scan's bit for bit.
 template <int NT, int RBITS> __global__ void ffd_refine_kernel(RefineArgs a);
+__global__ void ffd_offsets_kernel(int4* info, int nent);
 template <int G> __global__ void ffd_topk_select_kernel(TopkArgs a);
 constexpr int kTopkSelectThreads = 1024;
 template <int NT> __global__ void dense_decode_kernel(DenseArgs a);

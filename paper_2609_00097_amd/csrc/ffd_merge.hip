@@ -3,9 +3,8 @@
 // lse = M* + ln l*. Splits that kept nothing carry m = -inf and are skipped; a head with no split
 // gets out = 0 and lse = -inf.
 //
-// Partial rows of head bh = b * Hq + h: without a table, rows bh * S + s for s < S (the dense path's
-// fixed splits); with a table (the FFD path), rows (first + i) * G + bh % G for i < count, where
-// (first, count) = table[bh / G] describes the refinement workgroups given to that KV group.
+// Partial rows of head bh = b * Hq + h: without a table, rows bh * S + s for s < S; with a table, rows
+// i * G + bh % G for i = first .. last, (first, last) = table[bh / G] (last < first: none).
 //
 // Mapping: one workgroup per (sequence, query head), running merge_partial_rows.
 #include "ffd_device.h"
@@ -20,10 +19,10 @@ __global__ __launch_bounds__(kThreads) void lse_merge_kernel(const float* __rest
                                                              uint16_t* __restrict__ out, float* __restrict__ lse) {
     size_t row0 = (size_t)blockIdx.x * S, stride = 1;      // blockIdx.x = b * Hq + h
     if (table) {
-        const int2 fc = table[blockIdx.x / G];
-        row0 = (size_t)fc.x * G + blockIdx.x % G;
+        const int2 fl = table[blockIdx.x / G];
+        row0 = (size_t)fl.x * G + blockIdx.x % G;
         stride = (size_t)G;
-        S = fc.y;
+        S = fl.y - fl.x + 1;
     }
     merge_partial_rows(part_m, part_l, part_acc, row0, stride, S, out + (size_t)blockIdx.x * kD,
                        lse ? lse + blockIdx.x : nullptr);

@@ -291,8 +291,11 @@ __global__ __launch_bounds__(kSelThreads) void ffd_topk_select_kernel(TopkArgs a
         }
         __syncthreads();                                // the maps are rewritten for the next tile
     }
-    int* counts_x = a.counts + (size_t)x * a.S1;
-    for (int s = tid; s < a.S1; s += kSelThreads) counts_x[s] = s == 0 ? list_run : 0;
+    if (tid == 0) {
+        a.info[x] = make_int4(list_run, L, x, 1 << kInfoSplitBits);
+        a.table[x] = make_int2(0, -1);
+        if (x == 0) *a.ticket = 0;
+    }
     if (mask_x) {
         for (int j = nblk + tid; j < nblk_cap; j += kSelThreads)
 #pragma unroll

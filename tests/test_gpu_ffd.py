@@ -326,3 +326,28 @@ def test_share_longer_than_the_per_wave_staging():
     out, lse, mask = _ffd(up, qk, float("inf"), num_splits=1, kernels="split")
     assert mask.cpu().numpy()[:, :, :1094].all()
     compare_ffd(c, float("inf"), out, lse, mask)
+
+
+def test_refinement_units_from_the_counter():
+    """Long shares are worked as units from a device counter (at least 96 kept blocks per workgroup and
+    room for their partials: 128 groups of 200 blocks in a capacity of 1280, every block kept), an empty
+    and a one-token sequence among them. Against one fixed share per workgroup (num_splits = 1): the
+    fp32 states differ in summation order only, so the bf16 outputs by at most one step (2^-7 of the
+    value) and lse by fp32 rounding; repeated calls are identical whichever workgroup takes a unit."""
+    from paper_2609_00097_amd import ffd
+    B, Hkv, G, Lcap = 16, 8, 4, 81920
+    gen = torch.Generator("cuda").manual_seed(5)
+    q = torch.randn(B, Hkv * G, 128, dtype=torch.bfloat16, device="cuda", generator=gen)
+    k = torch.randn(B, Hkv, Lcap, 128, dtype=torch.bfloat16, device="cuda", generator=gen)
+    qk = ffd.quantize_keys(k)
+    v = k.normal_(generator=gen)
+    lens = torch.tensor([0, 1] + [13600 + 61 * b for b in range(B - 2)], dtype=torch.int32, device="cuda")
+    ws = ffd.new_workspace(B, Hkv * G, Hkv, Lcap)
+    print("case refinement units", flush=True)
+    runs = [ffd.decode_attention(q, *qk, v, lens, delta=float("inf"), workspace=ws, kernels="split") for _ in range(3)]
+    ref, ref_lse, _ = ffd.decode_attention(q, *qk, v, lens, delta=float("inf"), num_splits=1, kernels="split")
+    torch.cuda.synchronize()
+    for out, lse, _ in runs:
+        assert torch.equal(out, runs[0][0]) and torch.equal(lse, runs[0][1])
+    np.testing.assert_allclose(bf16_to_f64(runs[0][0]), bf16_to_f64(ref), rtol=2 ** -7, atol=1e-6)
+    np.testing.assert_allclose(runs[0][1].cpu().numpy(), ref_lse.cpu().numpy(), rtol=0, atol=1e-5)
