@@ -476,14 +476,14 @@ int ffd_decode_attention_ex(const void* q, const void* k_codes, const void* k_ab
     float* part_acc = part_l + rows;
     ScanArgs sa{static_cast<const uint16_t*>(q), static_cast<const uint32_t*>(k_codes),
                 static_cast<const uint16_t*>(k_absmax), static_cast<const int8_t*>(k_resid), seq_lens, lists,
-                info, table, ticket, sigma, block_mask, m_tilde, Hq, Hkv, Lcap, G, S1, delta, scale, n_sink, n_local};
+                info, table, ticket, sigma, block_mask, m_tilde, B, Hq, Hkv, Lcap, G, S1, delta, scale, n_sink, n_local};
     RefineArgs ra{static_cast<const uint16_t*>(q), static_cast<const uint32_t*>(k_codes),
                   static_cast<const uint16_t*>(k_absmax), static_cast<const int8_t*>(k_resid),
                   static_cast<const uint16_t*>(v), lists, info, table, ticket, part_m, part_l, part_acc, Lcap, G, (int)Wr,
                   num_splits > 0 ? (int)Wr : (int)std::min(max_units, 1LL << 20), nent,
                   scale, thumb_top_level(thumb_bits)};
     TopkArgs ta{sigma, seq_lens, lists, info, table, ticket, block_mask, Hq, Hkv, Lcap, top_k};
-    const dim3 scan_grid((unsigned)S1, (unsigned)Hkv, (unsigned)B);
+    const dim3 scan_grid((unsigned)B * (unsigned)S1, (unsigned)Hkv);
     const dim3 refine_grid((unsigned)Wr);
     auto mark = [&](int i) {
         return stage_events && hipEventRecord(stage_events[i], stream) != hipSuccess ? FFD_ERR_HIP : FFD_OK;
@@ -500,16 +500,17 @@ int ffd_decode_attention_ex(const void* q, const void* k_codes, const void* k_ab
         float* fpart_m = reinterpret_cast<float*>(ws);
         float* fpart_l = fpart_m + frows;
         float* fpart_acc = fpart_l + frows;
+        int2* ftable = !direct && B > 1 && B <= kBalanceMaxSeqs ? table : nullptr;      // rows follow the lengths
         FusedArgs fa{static_cast<const uint16_t*>(q), static_cast<const uint32_t*>(k_codes),
                      static_cast<const uint16_t*>(k_absmax), static_cast<const int8_t*>(k_resid),
                      static_cast<const uint16_t*>(v), seq_lens, block_mask, m_tilde, fpart_m, fpart_l, fpart_acc,
-                     direct ? static_cast<uint16_t*>(out) : nullptr, direct ? lse : nullptr,
-                     Hq, Hkv, Lcap, G, S1f, delta, scale, n_sink, n_local};
-        launch_fused(thumb_bits, G <= 4 ? 1 : 2, mode, dim3((unsigned)S1f, (unsigned)Hkv, (unsigned)B), stream, fa);
+                     ftable, direct ? static_cast<uint16_t*>(out) : nullptr, direct ? lse : nullptr,
+                     B, Hq, Hkv, Lcap, G, S1f, delta, scale, n_sink, n_local};
+        launch_fused(thumb_bits, G <= 4 ? 1 : 2, mode, dim3((unsigned)B * (unsigned)S1f, (unsigned)Hkv), stream, fa);
         if ((st = launch_status()) != FFD_OK || (st = mark(1)) != FFD_OK || (st = mark(2)) != FFD_OK) return st;
         if (!direct) {
             hipLaunchKernelGGL(lse_merge_kernel, dim3((unsigned)(B * Hq)), dim3(kThreads), 0, stream, fpart_m,
-                               fpart_l, fpart_acc, S1f, nullptr, 1, static_cast<uint16_t*>(out), lse);
+                               fpart_l, fpart_acc, S1f, ftable, G, static_cast<uint16_t*>(out), lse);
             if ((st = launch_status()) != FFD_OK) return st;
         }
         return mark(3);

@@ -247,6 +247,60 @@ __device__ __forceinline__ void block_scores(const BlockScan<BITS>& ld, int j, i
     }
 }
 
+// The scan's workgroups of one KV head, B * S1 slots, and the sequences. A sequence of n blocks gets S =
+// max(1, ceil(n / T)) slots, T the smallest number of blocks per slot for which all sequences fit, so
+// that a ragged batch's workgroups end together: with S1 slots for every sequence the longest one sets
+// the end (16 sequences of 8K to 128K tokens, S1 = 8: scan 79 us, now 73; the search itself is not
+// seen in a batch of four equal lengths, 28.8 us before and after). Every wave computes the same for itself, lane b holding sequence b; batches of more than
+// kBalanceMaxSeqs keep S1 slots per sequence. Slots past the last one used have b = -1.
+struct Slot {
+    int b;              // sequence
+    int s, S;           // the slot's number among the sequence's S slots
+    int base;           // slots of the sequences before it
+    int L;              // sequence length, clamped to the capacity
+};
+
+// ceil(n / T) for 0 <= n <= 2^18, 1 <= T <= 2^18, with 1 / T given to fp32
+__device__ __forceinline__ int ceil_div(int n, int T, float rT) {
+    const int m = n + T - 1;
+    int q = (int)((float)m * rT);                   // off by at most one
+    q -= q * T > m ? 1 : 0;
+    q += (q + 1) * T <= m ? 1 : 0;
+    return q;
+}
+
+__device__ __forceinline__ Slot slot_of(const int32_t* __restrict__ seq_lens, int B, int S1, int Lcap, int t, int lane) {
+    if (B == 1 || S1 == 1 || B > kBalanceMaxSeqs) { // uniform
+        const int b = B == 1 ? 0 : t / S1;
+        return Slot{b, t - b * S1, S1, b * S1, min(max(seq_lens[b], 0), Lcap)};
+    }
+    const int L = lane < B ? min(max(seq_lens[lane], 0), Lcap) : 0;
+    const int n = (L + kBlock - 1) / kBlock;
+    const int N = wave_sum_dpp(n), longest = (int)wave_max_dpp((float)n);
+    const int slots = B * S1;
+    // T lies between N / slots and longest / S1 (where S1 slots each are enough); candidates lo + i step
+    // per lane i, from coarse to fine
+    int lo = max(max((N + slots - 1) / slots, (longest + kFfdMaxScanSplits - 1) / kFfdMaxScanSplits), 1);
+    int hi = max((longest + S1 - 1) / S1, lo);
+    while (lo < hi) {
+        const int step = (hi - lo + 63) / 64, T = min(lo + lane * step, hi);
+        const float rT = 1.f / (float)T;
+        int need = 0;
+        for (int b = 0; b < B; ++b) need += max(ceil_div(__builtin_amdgcn_readlane(n, b), T, rT), 1);
+        const uint64_t fits = __ballot(need <= slots);      // monotonic in the lane; hi fits
+        const int first = fits ? (int)__builtin_ctzll(fits) : 64;
+        hi = min(lo + first * step, hi);
+        lo = first > 0 ? min(lo + (first - 1) * step + 1, hi) : hi;
+    }
+    const int S = lane < B ? max(ceil_div(n, hi, 1.f / (float)hi), 1) : 0;
+    const int incl = wave_inclusive_scan(S);
+    const uint64_t after = __ballot(incl > t);
+    if (after == 0) return Slot{-1, 0, 1, 0, 0};
+    const int b = (int)__builtin_ctzll(after);
+    const int Sb = __builtin_amdgcn_readlane(S, b), base = __builtin_amdgcn_readlane(incl, b) - Sb;
+    return Slot{b, t - base, Sb, base, __builtin_amdgcn_readlane(L, b)};
+}
+
 template <int NT>
 struct ScanLds {
     QueryLds<NT> qs;
@@ -336,9 +390,9 @@ struct RefineLds {
 // ================================================================================================
 // Scan: b-bit thumbnail scan and pseudo-max, then the keep decisions; the kept list (or, for the
 // top-k rule, every block's scores) to the workspace.
-// Grid (S1, Hkv, B) of kScanWaves-wave workgroups; workgroup s1 scans blocks [s1 * bps, (s1 + 1) *
-// bps) of one (sequence, KV head), bps = ceil(nblk / S1) <= kFfdMaxScanBlocks; its waves take the
-// blocks one at a time from an LDS counter and keep kRing blocks in flight each.
+// Grid (B * S1, Hkv) of kScanWaves-wave workgroups; slot s of the S given to a sequence (slot_of) scans
+// blocks [s * bps, (s + 1) * bps) of one (sequence, KV head), bps = ceil(nblk / S) <= kFfdMaxScanBlocks;
+// its waves take the blocks one at a time from an LDS counter and keep kRing blocks in flight each.
 // ================================================================================================
 // Blocks in flight per wave, fewer for the wider thumbnails (whose blocks are 2x and 4x larger).
 template <int BITS> constexpr int scan_ring() { return BITS == 2 ? kRing2 : 2; }
@@ -379,20 +433,29 @@ __global__ __launch_bounds__(kScanThreads, scan_occupancy<BITS>()) void ffd_scan
     constexpr bool kTopK = MODE == kSelTopK;
     constexpr int kRing = scan_ring<BITS>();
     __shared__ ScanLds<NT> sm;
-    const int s = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
+    const int kvh = blockIdx.y;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int g = lane >> 4, n = lane & 15;
+    const Slot sl = slot_of(a.seq_lens, a.B, a.S1, a.Lcap, blockIdx.x, lane);
+    const int b = sl.b, s = sl.s, S = sl.S, L = sl.L;
+    // records in (group, split) order; a slot that is not used holds no block and begins no group
+    const size_t rec = b < 0 ? (size_t)blockIdx.x * a.Hkv + kvh : (size_t)sl.base * a.Hkv + (size_t)kvh * S + s;
+    if (b < 0) {                                    // uniform
+        if constexpr (!kTopK) {
+            if (tid == 0) a.info[rec] = make_int4(0, 0, 0, 1 | (1 << kInfoSplitBits));
+        }
+        return;
+    }
     const int G = a.G, hq0 = kvh * G;
     const size_t bh = (size_t)b * a.Hkv + kvh;
-    const int L = min(max(a.seq_lens[b], 0), a.Lcap);
     const int nblk = (L + kBlock - 1) / kBlock;
     const int nblk_cap = a.Lcap / kBlock;
-    const int bps = (nblk + a.S1 - 1) / a.S1;
+    const int bps = (nblk + S - 1) / S;
     const int jb = min(s * bps, nblk), je = min(jb + bps, nblk);
     // this workgroup's record for the refinement, and the group's entry of the merge table (no rows
     // until the refinement meets a kept block)
     auto write_record = [&](int kept) {
-        if (tid == 0) a.info[bh * a.S1 + s] = make_int4(kept, L, (int)bh, s | (a.S1 << kInfoSplitBits));
+        if (tid == 0) a.info[rec] = make_int4(kept, L, (int)bh, s | (S << kInfoSplitBits));
         if (tid == 0 && s == 0) a.table[bh] = make_int2(0, -1);
         if (tid == 0 && s == 0 && bh == 0) *a.ticket = 0;
     };
@@ -578,14 +641,15 @@ __global__ __launch_bounds__(kScanThreads, scan_occupancy<BITS>()) void ffd_scan
 
     // Mask entries past the end of the sequence are zero (spread over the scan workgroups).
     if (a.mask) {
-        for (int j = nblk + s * kScanThreads + tid; j < nblk_cap; j += a.S1 * kScanThreads)
+        for (int j = nblk + s * kScanThreads + tid; j < nblk_cap; j += S * kScanThreads)
             for (int h = 0; h < G; ++h) a.mask[((size_t)b * a.Hq + hq0 + h) * nblk_cap + j] = 0;
     }
 }
 
 // ================================================================================================
-// Fused top-delta decode: one workgroup per (sequence, KV head, split s) of kScanWaves waves.
-// Workgroup s owns the blocks j = s + S1 i (i < cnt) of its group, an interleaved share, so the kept
+// Fused top-delta decode: one workgroup per (sequence, KV head, split s) of kScanWaves waves; grid (B *
+// S1, Hkv), the slots given to the sequences by their lengths (slot_of). Workgroup s of a sequence's S1
+// owns the blocks j = s + S1 i (i < cnt) of its group, an interleaved share, so the kept
 // blocks of a group (windows, planted clusters) spread evenly over its S1 workgroups. It
 //  1. streams the thumbnail codes of its blocks (waves take block numbers i from an LDS counter,
 //     kRing blocks in flight each) and keeps each block's per-head maximum score in LDS, while each
@@ -596,7 +660,7 @@ __global__ __launch_bounds__(kScanThreads, scan_occupancy<BITS>()) void ffd_scan
 //     w % 4 of the kept entries w / 4, w / 4 + 2, ..., with kRefineRing tiles in flight; the
 //     thumbnail term of each kept tile is recomputed from its codes with the same integer MFMA and
 //     fp32 operations as in step 1, so it equals the value the decision used;
-//  4. combines the eight waves' states into one partial state per head (rows [B, Hq, S1]), or,
+//  4. combines the eight waves' states into one partial state per head, or,
 //     when it is the group's only workgroup (S1 == 1), writes the bf16 output and lse itself.
 // No workgroup waits for another: each needs only its own blocks, the window blocks (re-read by
 // every workgroup of the group, L2-resident) and the query.
@@ -618,19 +682,23 @@ __global__ __launch_bounds__(kScanThreads, 1) void ffd_decode_kernel(FusedArgs a
     static_assert(MODE == kSelThumbnailPM || MODE == kSelRefinedPM, "top-delta modes only");
     constexpr int kRing = scan_ring<BITS>();
     __shared__ FusedLds<NT> sm;
-    const int s = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
+    const int kvh = blockIdx.y;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int g = lane >> 4, n = lane & 15;
-    const int G = a.G, hq0 = kvh * G, S1 = a.S1;
+    const Slot sl = slot_of(a.seq_lens, a.B, a.S1, a.Lcap, blockIdx.x, lane);
+    if (sl.b < 0) return;                           // uniform: a slot no sequence needs
+    const int b = sl.b, s = sl.s, S1 = sl.S, L = sl.L;
+    const int G = a.G, hq0 = kvh * G;
+    const size_t row = (size_t)sl.base * a.Hkv + (size_t)kvh * S1 + s;       // partials, in rows of G heads
     const size_t bh = (size_t)b * a.Hkv + kvh;
     const size_t hrow0 = (size_t)b * a.Hq + hq0;             // [B, Hq] row of the group's head 0
-    const int L = min(max(a.seq_lens[b], 0), a.Lcap);
     const int nblk = (L + kBlock - 1) / kBlock;
     const int nblk_cap = a.Lcap / kBlock;
     const int cnt = nblk > s ? (nblk - 1 - s) / S1 + 1 : 0;  // blocks of this workgroup
     uint16_t* out_h = a.out ? a.out + hrow0 * kD : nullptr;
     float* lse_h = a.out && a.lse ? a.lse + hrow0 : nullptr;
 
+    if (a.table && s == 0 && tid == 0) a.table[bh] = make_int2((int)row, (int)row + S1 - 1);
     // Mask entries past the end of the sequence are zero (spread over the group's workgroups).
     if (a.mask) {
         for (int j = nblk + s * kScanThreads + tid; j < nblk_cap; j += S1 * kScanThreads)
@@ -641,7 +709,7 @@ __global__ __launch_bounds__(kScanThreads, 1) void ffd_decode_kernel(FusedArgs a
             for (int idx = tid; idx < G * kD; idx += kScanThreads) out_h[idx] = 0;
             if (lse_h && tid < G) lse_h[tid] = -INFINITY;
         } else if (tid < G) {
-            a.part_m[(hrow0 + tid) * S1 + s] = -INFINITY;     // an empty partial state
+            a.part_m[row * G + tid] = -INFINITY;     // an empty partial state
         }
         if (a.m_tilde && s == 0 && tid < G) a.m_tilde[hrow0 + tid] = -INFINITY;   // L = 0
         return;
@@ -848,7 +916,7 @@ __global__ __launch_bounds__(kScanThreads, 1) void ffd_decode_kernel(FusedArgs a
         }
     }
 
-    write_partials<NT, kScanWaves>(sm.epi, pv, m_run, l_part, wave, lane, G, hrow0 * S1 + s, (size_t)S1,
+    write_partials<NT, kScanWaves>(sm.epi, pv, m_run, l_part, wave, lane, G, row * G, 1,
                                    a.part_m, a.part_l, a.part_acc, out_h, lse_h);
 }
 

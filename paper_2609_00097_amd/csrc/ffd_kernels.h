@@ -26,6 +26,7 @@ constexpr int kInfoSplitMask = (1 << kInfoSplitBits) - 1;
 // Most blocks one scan workgroup covers (its kept list is staged in LDS), most scan workgroups per
 // (sequence, KV head).
 constexpr int kFfdMaxScanBlocks = 256;
+constexpr int kBalanceMaxSeqs = 64;            // largest batch whose scan slots follow the lengths
 constexpr int kScanWaves = 8;                  // waves per scan workgroup (one workgroup per CU)
 constexpr int kScanThreads = 64 * kScanWaves;
 // Waves per refinement workgroup (one workgroup per CU): 8 (two per SIMD) overlap one wave's waits
@@ -52,7 +53,7 @@ struct ScanArgs {
     float* sigma;               // top-k selection: block scores [B*Hkv, Lcap/64, G]
     uint8_t* mask;              // [B, Hq, Lcap/64] or null
     float* m_tilde;             // [B, Hq] or null: the pseudo-max of each head
-    int Hq, Hkv, Lcap, G, S1;
+    int B, Hq, Hkv, Lcap, G, S1;
     float delta, scale;
     int n_sink, n_local;
 };
@@ -86,12 +87,13 @@ struct FusedArgs {
     const int32_t* seq_lens;    // [B]
     uint8_t* mask;              // [B, Hq, Lcap/64] or null
     float* m_tilde;             // [B, Hq] or null: the pseudo-max of each head
-    float* part_m;              // [B, Hq, S1] partial states (S1 > 1)
+    float* part_m;              // [B * S1 * Hkv, G] partial states (S1 > 1)
     float* part_l;
-    float* part_acc;            // [B, Hq, S1, 128]
+    float* part_acc;            // [B * S1 * Hkv, G, 128]
+    int2* table;                // [B*Hkv]: (first, last) row of each group, or null: S1 rows per group
     uint16_t* out;              // bf16 [B, Hq, 128], written by the kernel itself when S1 == 1, else null
     float* lse;                 // [B, Hq] or null (S1 == 1 only)
-    int Hq, Hkv, Lcap, G, S1;
+    int B, Hq, Hkv, Lcap, G, S1;
     float delta, scale;
     int n_sink, n_local;
 };

@@ -3,8 +3,8 @@
 // lse = M* + ln l*. Splits that kept nothing carry m = -inf and are skipped; a head with no split
 // gets out = 0 and lse = -inf.
 //
-// Partial rows of head bh = b * Hq + h: without a table, rows bh * S + s for s < S; with a table, rows
-// i * G + bh % G for i = first .. last, (first, last) = table[bh / G] (last < first: none).
+// Partial rows of head bh = b * Hq + h: i * G + bh % G for i = first .. last, (first, last) = table[bh / G]
+// (last < first: none), or, without a table, the S rows from S * (bh / G) on.
 //
 // Mapping: one workgroup per (sequence, query head), running merge_partial_rows.
 #include "ffd_device.h"
@@ -17,14 +17,14 @@ __global__ __launch_bounds__(kThreads) void lse_merge_kernel(const float* __rest
                                                              const float* __restrict__ part_acc, int S,
                                                              const int2* __restrict__ table, int G,
                                                              uint16_t* __restrict__ out, float* __restrict__ lse) {
-    size_t row0 = (size_t)blockIdx.x * S, stride = 1;      // blockIdx.x = b * Hq + h
+    const size_t x = blockIdx.x / G;                        // blockIdx.x = b * Hq + h
+    size_t first = x * S;
     if (table) {
-        const int2 fl = table[blockIdx.x / G];
-        row0 = (size_t)fl.x * G + blockIdx.x % G;
-        stride = (size_t)G;
+        const int2 fl = table[x];
+        first = fl.x;
         S = fl.y - fl.x + 1;
     }
-    merge_partial_rows(part_m, part_l, part_acc, row0, stride, S, out + (size_t)blockIdx.x * kD,
+    merge_partial_rows(part_m, part_l, part_acc, first * G + blockIdx.x % G, G, S, out + (size_t)blockIdx.x * kD,
                        lse ? lse + blockIdx.x : nullptr);
 }
 
