@@ -168,8 +168,9 @@ int ffd_decode_attention(const void* q, const void* k_codes, const void* k_absma
                                  unit), or a sequence fits one workgroup (ffd_select_kernels), else
                                  FFD_KERNELS_SPLIT */
 #define FFD_KERNELS_FUSED 1   /* one kernel: each of S1 = ffd_fused_splits(...) workgroups per
-                                 (sequence, KV head) scans the blocks j = s + S1 i, decides, refines and
-                                 attends its own kept blocks; then the merge of the S1 partial states
+                                 (sequence, KV head) (in a batch of 2 to 64 sequences as many as the
+                                 length's share of B * S1) scans the blocks j = s + S1 i, decides, refines
+                                 and attends its own kept blocks; then the merge of the S1 partial states
                                  per head (no merge when S1 == 1: the kernel writes the outputs) */
 #define FFD_KERNELS_SPLIT 2   /* scan + selection kernel (contiguous block ranges), refinement kernel
                                  (the kept blocks of all groups spread evenly over about one

@@ -187,6 +187,37 @@ int decode_splits(int B, int Hkv, int Lcap, int num_splits) {
     return (int)s;
 }
 
+// The fused kernel's workgroups per (sequence, KV head) as launched, at most decode_splits: with eight
+// query heads per KV head or 8-bit codes its registers (150 and 134 a lane) leave room for one workgroup
+// per CU, so an automatic count of two per CU would run in two rounds; it is one per CU then (2 sequences
+// of 60K, G = 8, b = 4: step 41.3 us with 512 workgroups, 32.3 with 256; 1 x 62K, G = 4, b = 8: 32.9 and
+// 25.9 us).
+int fused_launch_splits(int S1f, int B, int Hkv, int Lcap, int G, int bits, int num_splits) {
+    const long long pairs = (long long)B * Hkv, cus = device_cus();
+    if (num_splits > 0 || (G <= 4 && bits != 8) || S1f * pairs <= cus) return S1f;
+    const long long need = (Lcap / FFD_BLOCK + kFfdMaxScanBlocks - 1) / kFfdMaxScanBlocks;
+    return (int)std::min((long long)S1f, std::max({1LL, need, cus / pairs}));
+}
+
+// Slots (workgroups per KV head) of the scan and of the fused kernel. Where they follow the lengths they
+// are meant to fill the CUs `per_cu` times and no more (shares are equal, so a few workgroups over would
+// double the time: 5 sequences of 87K to 219K x 4 KV heads, all 70 slots = 280 workgroups used: scan 33.9
+// us, 64 slots: 25.4; 14 slots per sequence, as before: 26.5); the grid has as many as the longest
+// sequences of the capacity need.
+struct Slots {
+    int meant, grid;
+};
+Slots slots_of(int B, int Hkv, int Lcap, int S1, int per_cu) {
+    const long long all = (long long)B * S1;
+    if (B == 1 || B > kBalanceMaxSeqs) return Slots{(int)all, (int)all};
+    const long long need = B * (long long)((Lcap / FFD_BLOCK + kFfdMaxScanBlocks - 1) / kFfdMaxScanBlocks);
+    const long long meant = std::min(all, std::max((long long)B, (long long)per_cu * device_cus() / Hkv));
+    return Slots{(int)meant, (int)std::max(need, meant)};
+}
+dim3 slot_grid(int Hkv, int slots) {
+    return dim3((unsigned)Hkv, (unsigned)std::min(slots, kSlotGridY), (unsigned)((slots + kSlotGridY - 1) / kSlotGridY));
+}
+
 // The top-delta kernels FFD_KERNELS_AUTO picks: the fused kernel while its workgroups cover at
 // most kFusedMaxBlocks blocks of the capacity each (or a group fits one workgroup), else scan +
 // refinement + merge, whose refinement spreads the kept blocks over every CU. (The fused kernel
@@ -453,7 +484,8 @@ int ffd_decode_attention_ex(const void* q, const void* k_codes, const void* k_ab
     float* sigma = reinterpret_cast<float*>(ws + W.sigma_off);
     const int S1 = scan_splits(B, Hkv, Lcap);
     const int npairs = B * Hkv;
-    const int nent = top_k > 0 ? npairs : npairs * S1;                  // kept lists, one record each
+    const Slots ss = slots_of(B, Hkv, Lcap, S1, 1);
+    const int nent = top_k > 0 ? npairs : ss.grid * Hkv;             // kept lists, one record each
     // The records take the block scores' place (unused by top-delta), or, where those are in use or too
     // few (a group of less than four scores), the end of the partials' region; there is one record per
     // group then, and the refinement gets as many workgroups fewer as they need (2 * npairs rows of G
@@ -466,7 +498,8 @@ int ffd_decode_attention_ex(const void* q, const void* k_codes, const void* k_ab
     const long long max_rows = (long long)((in_scores ? part_bytes : info_off) / row_bytes);
     // refinement workgroups: num_splits per group on average, or one per CU; their W + npairs - 1 rows
     // of partials have to fit
-    long long Wr = num_splits > 0 ? (long long)S * npairs : std::min((long long)(S + 1) * npairs, (long long)device_cus());
+    long long Wr = num_splits > 0 ? (long long)S * npairs
+                                  : std::min((long long)npairs * (Lcap / FFD_BLOCK / kMinBlocksPerSplit + 1), (long long)device_cus());
     const long long max_units = max_rows - npairs + 1;
     Wr = std::max(1LL, std::min(Wr, max_units));
     const size_t rows = (size_t)(max_units + npairs - 1) * G;
@@ -476,14 +509,14 @@ int ffd_decode_attention_ex(const void* q, const void* k_codes, const void* k_ab
     float* part_acc = part_l + rows;
     ScanArgs sa{static_cast<const uint16_t*>(q), static_cast<const uint32_t*>(k_codes),
                 static_cast<const uint16_t*>(k_absmax), static_cast<const int8_t*>(k_resid), seq_lens, lists,
-                info, table, ticket, sigma, block_mask, m_tilde, B, Hq, Hkv, Lcap, G, S1, delta, scale, n_sink, n_local};
+                info, table, ticket, sigma, block_mask, m_tilde, B, Hq, Hkv, Lcap, G, S1, ss.meant, ss.grid, delta, scale, n_sink, n_local};
     RefineArgs ra{static_cast<const uint16_t*>(q), static_cast<const uint32_t*>(k_codes),
                   static_cast<const uint16_t*>(k_absmax), static_cast<const int8_t*>(k_resid),
                   static_cast<const uint16_t*>(v), lists, info, table, ticket, part_m, part_l, part_acc, Lcap, G, (int)Wr,
                   num_splits > 0 ? (int)Wr : (int)std::min(max_units, 1LL << 20), nent,
                   scale, thumb_top_level(thumb_bits)};
     TopkArgs ta{sigma, seq_lens, lists, info, table, ticket, block_mask, Hq, Hkv, Lcap, top_k};
-    const dim3 scan_grid((unsigned)B * (unsigned)S1, (unsigned)Hkv);
+    const dim3 scan_grid = slot_grid(Hkv, ss.grid);
     const dim3 refine_grid((unsigned)Wr);
     auto mark = [&](int i) {
         return stage_events && hipEventRecord(stage_events[i], stream) != hipSuccess ? FFD_ERR_HIP : FFD_OK;
@@ -493,10 +526,12 @@ int ffd_decode_attention_ex(const void* q, const void* k_codes, const void* k_ab
     if ((st = mark(0)) != FFD_OK) return st;
     const int kernels = kernels_req == FFD_KERNELS_AUTO ? auto_kernels(B, Hkv, Lcap, S1f) : kernels_req;
     if (top_k == 0 && kernels == FFD_KERNELS_FUSED) {
-        // top-delta, fused: one kernel, then the merge of its S1f partial states per head (none when
-        // S1f == 1: the kernel writes the outputs itself)
-        const bool direct = S1f == 1;
-        const size_t frows = (size_t)B * Hq * S1f;
+        // top-delta, fused: one kernel, then the merge of its partial states per head (none with one
+        // workgroup per group: the kernel writes the outputs itself)
+        const int S1l = fused_launch_splits(S1f, B, Hkv, Lcap, G, thumb_bits, num_splits);
+        const Slots fs = num_splits > 0 ? Slots{B * S1l, B * S1l} : slots_of(B, Hkv, Lcap, S1l, 2);
+        const bool direct = S1l == 1;
+        const size_t frows = (size_t)B * Hq * S1l;
         float* fpart_m = reinterpret_cast<float*>(ws);
         float* fpart_l = fpart_m + frows;
         float* fpart_acc = fpart_l + frows;
@@ -505,12 +540,12 @@ int ffd_decode_attention_ex(const void* q, const void* k_codes, const void* k_ab
                      static_cast<const uint16_t*>(k_absmax), static_cast<const int8_t*>(k_resid),
                      static_cast<const uint16_t*>(v), seq_lens, block_mask, m_tilde, fpart_m, fpart_l, fpart_acc,
                      ftable, direct ? static_cast<uint16_t*>(out) : nullptr, direct ? lse : nullptr,
-                     B, Hq, Hkv, Lcap, G, S1f, delta, scale, n_sink, n_local};
-        launch_fused(thumb_bits, G <= 4 ? 1 : 2, mode, dim3((unsigned)B * (unsigned)S1f, (unsigned)Hkv), stream, fa);
+                     B, Hq, Hkv, Lcap, G, S1l, fs.meant, fs.grid, delta, scale, n_sink, n_local};
+        launch_fused(thumb_bits, G <= 4 ? 1 : 2, mode, slot_grid(Hkv, fs.grid), stream, fa);
         if ((st = launch_status()) != FFD_OK || (st = mark(1)) != FFD_OK || (st = mark(2)) != FFD_OK) return st;
         if (!direct) {
             hipLaunchKernelGGL(lse_merge_kernel, dim3((unsigned)(B * Hq)), dim3(kThreads), 0, stream, fpart_m,
-                               fpart_l, fpart_acc, S1f, ftable, G, static_cast<uint16_t*>(out), lse);
+                               fpart_l, fpart_acc, S1l, ftable, G, static_cast<uint16_t*>(out), lse);
             if ((st = launch_status()) != FFD_OK) return st;
         }
         return mark(3);

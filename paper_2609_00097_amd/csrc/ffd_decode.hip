@@ -247,12 +247,13 @@ __device__ __forceinline__ void block_scores(const BlockScan<BITS>& ld, int j, i
     }
 }
 
-// The scan's workgroups of one KV head, B * S1 slots, and the sequences. A sequence of n blocks gets S =
+// The scan's workgroups of one KV head, the slots, and the sequences. A sequence of n blocks gets S =
 // max(1, ceil(n / T)) slots, T the smallest number of blocks per slot for which all sequences fit, so
-// that a ragged batch's workgroups end together: with S1 slots for every sequence the longest one sets
-// the end (16 sequences of 8K to 128K tokens, S1 = 8: scan 79 us, now 73; the search itself is not
-// seen in a batch of four equal lengths, 28.8 us before and after). Every wave computes the same for itself, lane b holding sequence b; batches of more than
-// kBalanceMaxSeqs keep S1 slots per sequence. Slots past the last one used have b = -1.
+// that a ragged batch's workgroups end together: with as many slots for every sequence the longest one
+// sets the end (16 sequences of 8K to 128K tokens, 8 slots each: scan 79 us, now 73). Every wave computes
+// the same for itself, lane b holding sequence b; the divisions go through reciprocals because this
+// chain precedes every load of the kernel. Batches of more than kBalanceMaxSeqs keep S1 slots per
+// sequence. Slots past the last one used have b = -1.
 struct Slot {
     int b;              // sequence
     int s, S;           // the slot's number among the sequence's S slots
@@ -260,31 +261,37 @@ struct Slot {
     int L;              // sequence length, clamped to the capacity
 };
 
-// ceil(n / T) for 0 <= n <= 2^18, 1 <= T <= 2^18, with 1 / T given to fp32
-__device__ __forceinline__ int ceil_div(int n, int T, float rT) {
-    const int m = n + T - 1;
-    int q = (int)((float)m * rT);                   // off by at most one
-    q -= q * T > m ? 1 : 0;
-    q += (q + 1) * T <= m ? 1 : 0;
+// ceil(n / d) for 0 <= n <= 2^18, 1 <= d <= 2^18, r = 1 / d to an ulp or two
+__device__ __forceinline__ int ceil_div(int n, int d, float r) {
+    const int m = n + d - 1;
+    int q = (int)((float)m * r);                    // off by at most one
+    q -= q * d > m ? 1 : 0;
+    q += (q + 1) * d <= m ? 1 : 0;
     return q;
 }
 
-__device__ __forceinline__ Slot slot_of(const int32_t* __restrict__ seq_lens, int B, int S1, int Lcap, int t, int lane) {
+// t: the workgroup's slot. T is chosen for `slots` slots (>= B) and is kFfdMaxScanBlocks at most: the
+// grid has enough slots for that, B * ceil(capacity blocks / kFfdMaxScanBlocks), also where it is larger.
+__device__ __forceinline__ Slot slot_of(const int32_t* __restrict__ seq_lens, int B, int S1, int slots, int Lcap, int t,
+                                        int lane) {
     if (B == 1 || S1 == 1 || B > kBalanceMaxSeqs) { // uniform
-        const int b = B == 1 ? 0 : t / S1;
+        const int b = B == 1 ? 0 : (S1 == 1 ? t : t / S1);
         return Slot{b, t - b * S1, S1, b * S1, min(max(seq_lens[b], 0), Lcap)};
     }
     const int L = lane < B ? min(max(seq_lens[lane], 0), Lcap) : 0;
     const int n = (L + kBlock - 1) / kBlock;
     const int N = wave_sum_dpp(n), longest = (int)wave_max_dpp((float)n);
-    const int slots = B * S1;
-    // T lies between N / slots and longest / S1 (where S1 slots each are enough); candidates lo + i step
-    // per lane i, from coarse to fine
-    int lo = max(max((N + slots - 1) / slots, (longest + kFfdMaxScanSplits - 1) / kFfdMaxScanSplits), 1);
-    int hi = max((longest + S1 - 1) / S1, lo);
+    // T lies between N / slots and what gives every sequence the same number of slots; candidates
+    // lo + i step, one per lane, from coarse to fine
+    int each = (int)((float)slots * __builtin_amdgcn_rcpf((float)B));      // floor(slots / B)
+    each -= each * B > slots ? 1 : 0;
+    each += (each + 1) * B <= slots ? 1 : 0;
+    int hi = max(ceil_div(longest, each, __builtin_amdgcn_rcpf((float)each)), 1);
+    int lo = max(ceil_div(N, slots, __builtin_amdgcn_rcpf((float)slots)), (longest + kFfdMaxScanSplits - 1) / kFfdMaxScanSplits);
+    lo = min(max(lo, 1), hi);
     while (lo < hi) {
-        const int step = (hi - lo + 63) / 64, T = min(lo + lane * step, hi);
-        const float rT = 1.f / (float)T;
+        const int step = (hi - lo + 63) >> 6, T = min(lo + lane * step, hi);
+        const float rT = __builtin_amdgcn_rcpf((float)T);
         int need = 0;
         for (int b = 0; b < B; ++b) need += max(ceil_div(__builtin_amdgcn_readlane(n, b), T, rT), 1);
         const uint64_t fits = __ballot(need <= slots);      // monotonic in the lane; hi fits
@@ -292,7 +299,8 @@ __device__ __forceinline__ Slot slot_of(const int32_t* __restrict__ seq_lens, in
         hi = min(lo + first * step, hi);
         lo = first > 0 ? min(lo + (first - 1) * step + 1, hi) : hi;
     }
-    const int S = lane < B ? max(ceil_div(n, hi, 1.f / (float)hi), 1) : 0;
+    hi = min(hi, kFfdMaxScanBlocks);
+    const int S = lane < B ? max(ceil_div(n, hi, __builtin_amdgcn_rcpf((float)hi)), 1) : 0;
     const int incl = wave_inclusive_scan(S);
     const uint64_t after = __ballot(incl > t);
     if (after == 0) return Slot{-1, 0, 1, 0, 0};
@@ -390,7 +398,9 @@ struct RefineLds {
 // ================================================================================================
 // Scan: b-bit thumbnail scan and pseudo-max, then the keep decisions; the kept list (or, for the
 // top-k rule, every block's scores) to the workspace.
-// Grid (B * S1, Hkv) of kScanWaves-wave workgroups; slot s of the S given to a sequence (slot_of) scans
+// Grid (Hkv, slots) of kScanWaves-wave workgroups (KV heads first, so that slots that are not used come
+// last and a CU is not given two workgroups while another gets an empty one: 5 ragged sequences, 70
+// slots of which 64 are used: scan 25.4 us, with the slots first 34.8); slot s of the S given to a sequence (slot_of) scans
 // blocks [s * bps, (s + 1) * bps) of one (sequence, KV head), bps = ceil(nblk / S) <= kFfdMaxScanBlocks;
 // its waves take the blocks one at a time from an LDS counter and keep kRing blocks in flight each.
 // ================================================================================================
@@ -433,13 +443,14 @@ __global__ __launch_bounds__(kScanThreads, scan_occupancy<BITS>()) void ffd_scan
     constexpr bool kTopK = MODE == kSelTopK;
     constexpr int kRing = scan_ring<BITS>();
     __shared__ ScanLds<NT> sm;
-    const int kvh = blockIdx.y;
+    const int kvh = blockIdx.x, t = blockIdx.y + kSlotGridY * blockIdx.z;
+    if (t >= a.grid_slots) return;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int g = lane >> 4, n = lane & 15;
-    const Slot sl = slot_of(a.seq_lens, a.B, a.S1, a.Lcap, blockIdx.x, lane);
+    const Slot sl = slot_of(a.seq_lens, a.B, a.S1, a.slots, a.Lcap, t, lane);
     const int b = sl.b, s = sl.s, S = sl.S, L = sl.L;
     // records in (group, split) order; a slot that is not used holds no block and begins no group
-    const size_t rec = b < 0 ? (size_t)blockIdx.x * a.Hkv + kvh : (size_t)sl.base * a.Hkv + (size_t)kvh * S + s;
+    const size_t rec = b < 0 ? (size_t)t * a.Hkv + kvh : (size_t)sl.base * a.Hkv + (size_t)kvh * S + s;
     if (b < 0) {                                    // uniform
         if constexpr (!kTopK) {
             if (tid == 0) a.info[rec] = make_int4(0, 0, 0, 1 | (1 << kInfoSplitBits));
@@ -647,8 +658,8 @@ __global__ __launch_bounds__(kScanThreads, scan_occupancy<BITS>()) void ffd_scan
 }
 
 // ================================================================================================
-// Fused top-delta decode: one workgroup per (sequence, KV head, split s) of kScanWaves waves; grid (B *
-// S1, Hkv), the slots given to the sequences by their lengths (slot_of). Workgroup s of a sequence's S1
+// Fused top-delta decode: one workgroup per (sequence, KV head, split s) of kScanWaves waves; grid (Hkv,
+// slots), the slots given to the sequences by their lengths (slot_of). Workgroup s of a sequence's S1
 // owns the blocks j = s + S1 i (i < cnt) of its group, an interleaved share, so the kept
 // blocks of a group (windows, planted clusters) spread evenly over its S1 workgroups. It
 //  1. streams the thumbnail codes of its blocks (waves take block numbers i from an LDS counter,
@@ -682,10 +693,11 @@ __global__ __launch_bounds__(kScanThreads, 1) void ffd_decode_kernel(FusedArgs a
     static_assert(MODE == kSelThumbnailPM || MODE == kSelRefinedPM, "top-delta modes only");
     constexpr int kRing = scan_ring<BITS>();
     __shared__ FusedLds<NT> sm;
-    const int kvh = blockIdx.y;
+    const int kvh = blockIdx.x, t = blockIdx.y + kSlotGridY * blockIdx.z;
+    if (t >= a.grid_slots) return;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int g = lane >> 4, n = lane & 15;
-    const Slot sl = slot_of(a.seq_lens, a.B, a.S1, a.Lcap, blockIdx.x, lane);
+    const Slot sl = slot_of(a.seq_lens, a.B, a.S1, a.slots, a.Lcap, t, lane);
     if (sl.b < 0) return;                           // uniform: a slot no sequence needs
     const int b = sl.b, s = sl.s, S1 = sl.S, L = sl.L;
     const int G = a.G, hq0 = kvh * G;

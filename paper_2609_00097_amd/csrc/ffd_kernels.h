@@ -26,6 +26,7 @@ constexpr int kInfoSplitMask = (1 << kInfoSplitBits) - 1;
 // Most blocks one scan workgroup covers (its kept list is staged in LDS), most scan workgroups per
 // (sequence, KV head).
 constexpr int kFfdMaxScanBlocks = 256;
+constexpr int kSlotGridY = 32768;              // slots along the grid's y (then z)
 constexpr int kBalanceMaxSeqs = 64;            // largest batch whose scan slots follow the lengths
 constexpr int kScanWaves = 8;                  // waves per scan workgroup (one workgroup per CU)
 constexpr int kScanThreads = 64 * kScanWaves;
@@ -53,7 +54,7 @@ struct ScanArgs {
     float* sigma;               // top-k selection: block scores [B*Hkv, Lcap/64, G]
     uint8_t* mask;              // [B, Hq, Lcap/64] or null
     float* m_tilde;             // [B, Hq] or null: the pseudo-max of each head
-    int B, Hq, Hkv, Lcap, G, S1;
+    int B, Hq, Hkv, Lcap, G, S1, slots, grid_slots;    // S1 per sequence, or `slots` by the lengths (slot_of)
     float delta, scale;
     int n_sink, n_local;
 };
@@ -93,7 +94,7 @@ struct FusedArgs {
     int2* table;                // [B*Hkv]: (first, last) row of each group, or null: S1 rows per group
     uint16_t* out;              // bf16 [B, Hq, 128], written by the kernel itself when S1 == 1, else null
     float* lse;                 // [B, Hq] or null (S1 == 1 only)
-    int B, Hq, Hkv, Lcap, G, S1;
+    int B, Hq, Hkv, Lcap, G, S1, slots, grid_slots;    // S1 per sequence, or `slots` by the lengths (slot_of)
     float delta, scale;
     int n_sink, n_local;
 };

@@ -351,3 +351,21 @@ def test_refinement_units_from_the_counter():
         assert torch.equal(out, runs[0][0]) and torch.equal(lse, runs[0][1])
     np.testing.assert_allclose(bf16_to_f64(runs[0][0]), bf16_to_f64(ref), rtol=2 ** -7, atol=1e-6)
     np.testing.assert_allclose(runs[0][1].cpu().numpy(), ref_lse.cpu().numpy(), rtol=0, atol=1e-5)
+
+
+@pytest.mark.parametrize("G,bits", [(4, 2), (8, 4), (1, 8)])
+@pytest.mark.parametrize("B", [2, 64, 65])
+def test_slots_follow_the_lengths(B, G, bits):
+    """Batches whose workgroups are given to the sequences by their lengths (2 and 64 sequences) and the
+    first size that keeps equal counts (65): one long sequence, the others empty, short or one token, so
+    that the long one takes nearly all slots; automatic and given counts, both kernel sets, masks and
+    outputs against the oracle."""
+    from paper_2609_00097_amd import ffd
+    lens = [6001] + [(0, 1, 64, 65, 200, 333)[b % 6] for b in range(B - 1)]
+    c = I.small_case(seed=900 + B + G, B=B, Hq=G, Hkv=1, seq_lens=lens, Lcap=6016, heavy_frac=0.05)
+    print(f"case slots B={B} G={G} bits={bits}", flush=True)
+    up = Uploaded(c)
+    qk = ffd.quantize_keys(up.k, bits=bits)
+    for kernels, num_splits in [("fused", 0), ("fused", 3), ("split", 0), ("split", 2)]:
+        out, lse, mask = _ffd(up, qk, 5.0, num_splits=num_splits, kernels=kernels)
+        compare_ffd(c, 5.0, out, lse, mask, bits=bits)
