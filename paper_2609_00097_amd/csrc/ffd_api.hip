@@ -544,7 +544,7 @@ int ffd_decode_attention_ex(const void* q, const void* k_codes, const void* k_ab
         launch_fused(thumb_bits, G <= 4 ? 1 : 2, mode, slot_grid(Hkv, fs.grid), stream, fa);
         if ((st = launch_status()) != FFD_OK || (st = mark(1)) != FFD_OK || (st = mark(2)) != FFD_OK) return st;
         if (!direct) {
-            hipLaunchKernelGGL(lse_merge_kernel, dim3((unsigned)(B * Hq)), dim3(kThreads), 0, stream, fpart_m,
+            hipLaunchKernelGGL(lse_merge_kernel, dim3((unsigned)(B * Hq), kMergeSlices), dim3(kThreads), 0, stream, fpart_m,
                                fpart_l, fpart_acc, S1l, ftable, G, static_cast<uint16_t*>(out), lse);
             if ((st = launch_status()) != FFD_OK) return st;
         }
@@ -569,7 +569,7 @@ int ffd_decode_attention_ex(const void* q, const void* k_codes, const void* k_ab
     if (G <= 4) launch_refine_nt<1>(thumb_bits, refine_grid, stream, ra);
     else launch_refine_nt<2>(thumb_bits, refine_grid, stream, ra);
     if ((st = launch_status()) != FFD_OK || (st = mark(2)) != FFD_OK) return st;
-    hipLaunchKernelGGL(lse_merge_kernel, dim3((unsigned)(B * Hq)), dim3(kThreads), 0, stream, part_m, part_l,
+    hipLaunchKernelGGL(lse_merge_kernel, dim3((unsigned)(B * Hq), kMergeSlices), dim3(kThreads), 0, stream, part_m, part_l,
                        part_acc, 0, table, G, static_cast<uint16_t*>(out), lse);
     if ((st = launch_status()) != FFD_OK) return st;
     return mark(3);
@@ -631,7 +631,7 @@ int ffd_dense_decode_attention(const void* q, const void* k, const void* v, cons
         hipLaunchKernelGGL(dense_decode_kernel<2>, grid, dim3(kThreads), 0, stream, a);
     st = launch_status();
     if (st != FFD_OK) return st;
-    hipLaunchKernelGGL(lse_merge_kernel, dim3((unsigned)(B * Hq)), dim3(kThreads), 0, stream, P.m, P.l,
+    hipLaunchKernelGGL(lse_merge_kernel, dim3((unsigned)(B * Hq), kMergeSlices), dim3(kThreads), 0, stream, P.m, P.l,
                        P.acc, S, table, balanced ? G : 1, static_cast<uint16_t*>(out), lse);
     return launch_status();
 }

@@ -173,6 +173,7 @@ constexpr int kTopkSelectThreads = 1024;
 template <int NT> __global__ void dense_decode_kernel(DenseArgs a);
 template <int BITS> __global__ void quantize_keys_kernel(QuantArgs a);
 template <int BITS> __global__ void append_kv_kernel(AppendArgs a);
+constexpr int kMergeSlices = 4;                // workgroups per head of the merge, 32 dims each
 __global__ void lse_merge_kernel(const float* part_m, const float* part_l, const float* part_acc, int S,
                                  const int2* table, int G, uint16_t* out, float* lse);
 

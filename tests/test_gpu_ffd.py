@@ -369,3 +369,19 @@ def test_slots_follow_the_lengths(B, G, bits):
     for kernels, num_splits in [("fused", 0), ("fused", 3), ("split", 0), ("split", 2)]:
         out, lse, mask = _ffd(up, qk, 5.0, num_splits=num_splits, kernels=kernels)
         compare_ffd(c, 5.0, out, lse, mask, bits=bits)
+
+
+@pytest.mark.parametrize("num_splits", [31, 33, 64, 65, 256, 300, 700])
+def test_merge_row_counts(num_splits):
+    """Row counts on both sides of the merge's batches (64 rows, then 256 at a time), rows without a kept
+    token among them; outputs and lse of every head against one workgroup per sequence (no merge). The
+    fp32 states differ in summation order: bf16 outputs by at most one step (2^-7 of the value)."""
+    c = I.small_case(seed=131, B=1, Hq=8, Hkv=2, seq_lens=(16300,), heavy_frac=0.1)
+    print(f"case merge rows {num_splits}", flush=True)
+    up = Uploaded(c)
+    qk = _quant(up)
+    ref_out, ref_lse, ref_mask = _ffd(up, qk, 6.0, num_splits=1, kernels="fused")
+    out, lse, mask = _ffd(up, qk, 6.0, num_splits=num_splits, kernels="fused")
+    assert torch.equal(mask, ref_mask)
+    np.testing.assert_allclose(bf16_to_f64(out), bf16_to_f64(ref_out), rtol=2 ** -7, atol=1e-6)
+    np.testing.assert_allclose(lse.cpu().numpy(), ref_lse.cpu().numpy(), rtol=0, atol=1e-5)
