@@ -20,7 +20,7 @@ constexpr int kFallbackCus = 256;
 constexpr int kMaxDevices = 64;
 std::atomic<int> g_cus[kMaxDevices];
 
-int device_cus() {
+int lookup_cus() {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return kFallbackCus;
     int n = g_cus[dev].load(std::memory_order_relaxed);
@@ -30,6 +30,16 @@ int device_cus() {
     g_cus[dev].store(n, std::memory_order_relaxed);
     return n;
 }
+
+// The count, looked up once per call of an entry point (a call's sizes ask for it a dozen times, and the
+// current device can change between calls only).
+thread_local int t_call_cus = 0;
+struct CallScope {
+    const int outer = t_call_cus;
+    CallScope() { if (outer == 0) t_call_cus = lookup_cus(); }
+    ~CallScope() { t_call_cus = outer; }
+};
+int device_cus() { return t_call_cus != 0 ? t_call_cus : lookup_cus(); }
 
 // Device scratch of ffd_decode_attention_noalloc: one array per device, held until the process ends.
 // In host code `scratch` names a host-side stand-in, not device memory: the array is only ever
@@ -463,6 +473,7 @@ int ffd_decode_attention_ex(const void* q, const void* k_codes, const void* k_ab
                             int n_local, int num_splits, float softmax_scale, void* out, float* lse,
                             uint8_t* block_mask, void* workspace, size_t workspace_bytes,
                             hipStream_t stream, const ffd_decode_extras* extras) {
+    CallScope scope;
     hipEvent_t* stage_events = extras ? extras->stage_events : nullptr;
     float* m_tilde = extras ? extras->m_tilde : nullptr;
     const int pm_source = extras ? extras->pseudo_max : FFD_PSEUDO_MAX_THUMBNAIL;
@@ -590,6 +601,7 @@ int ffd_decode_attention_noalloc(const void* q, const void* k_codes, const void*
                                  int Hkv, int Lcap, int D, int thumb_bits, int block_size, float delta,
                                  int n_sink, int n_local, int num_splits, float softmax_scale, void* out,
                                  float* lse, uint8_t* block_mask, hipStream_t stream) {
+    CallScope scope;
     int S = 0;
     const int st = decode_checks(q, k_codes, k_absmax, k_resid, v, seq_lens, B, Hq, Hkv, Lcap, D, thumb_bits,
                                  block_size, delta, n_sink, n_local, num_splits, softmax_scale, out, lse,
@@ -608,6 +620,7 @@ int ffd_dense_decode_attention(const void* q, const void* k, const void* v, cons
                                int Hq, int Hkv, int Lcap, int D, int num_splits, float softmax_scale,
                                void* out, float* lse, void* workspace, size_t workspace_bytes,
                                hipStream_t stream) {
+    CallScope scope;
     int S = 0;
     int st = attention_common_checks(q, v, seq_lens, B, Hq, Hkv, Lcap, D, num_splits, softmax_scale, out,
                                      lse, workspace, workspace_bytes, true, &S);

@@ -100,11 +100,24 @@ def _ptr(t) -> int | None:
     return None if t is None else t.data_ptr()
 
 
-def _stream(device) -> int:
-    return torch.cuda.current_stream(device).cuda_stream
+# A call's checks, allocations and argument conversion cost more than its kernels at short contexts, so
+# each is the cheapest form that keeps its meaning (decode_attention with its defaults: 10 us of host time a
+# call with one launch, 18 us in the plain form): the usual tensor passes one expression, and only one that does not goes through
+# the checks that name what is wrong.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream(t) -> int:
+    """The current stream of the tensor's device."""
+    if _raw_stream is not None:
+        return _raw_stream(t.get_device())
+    return torch.cuda.current_stream(t.device).cuda_stream
 
 
 def _need(t, name, dtype, shape=None):
+    if (type(t) is torch.Tensor and t.is_cuda and t.dtype is dtype and t.is_contiguous()
+            and (shape is None or t.shape == shape)):
+        return
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise ValueError(f"{name} must be a CUDA (HIP) tensor")
     if t.dtype != dtype:
@@ -161,7 +174,8 @@ def quantized_shapes(B: int, Hkv: int, Lcap: int, bits: int = 2):
 
 def thumb_bits(codes: torch.Tensor) -> int:
     """The thumbnail depth of a codes tensor ``[B, Hkv, Lcap/64, b, 64, 4]``."""
-    bits = codes.shape[-3] if codes.dim() == 6 and tuple(codes.shape[-2:]) == (64, 4) else 0
+    shape = codes.shape
+    bits = shape[3] if len(shape) == 6 and shape[4] == 64 and shape[5] == 4 else 0
     if bits not in THUMB_BITS:
         raise ValueError(f"codes must be [B, Hkv, Lcap/64, b, 64, 4] with b in {THUMB_BITS}, "
                          f"got {tuple(codes.shape)}")
@@ -178,10 +192,10 @@ def empty_quantized(B: int, Hkv: int, Lcap: int, device, bits: int = 2):
 def _need_quantized(quantized, B, Hkv, Lcap) -> int:
     codes, absmax, resid = quantized
     bits = thumb_bits(codes)
-    for t, nm, dt, sh in zip((codes, absmax, resid), ("codes", "absmax", "resid"),
-                             (torch.int32, torch.bfloat16, torch.int8),
-                             quantized_shapes(B, Hkv, Lcap, bits)):
-        _need(t, nm, dt, sh)
+    sc, sa, sr = quantized_shapes(B, Hkv, Lcap, bits)
+    _need(codes, "codes", torch.int32, sc)
+    _need(absmax, "absmax", torch.bfloat16, sa)
+    _need(resid, "resid", torch.int8, sr)
     return bits
 
 
@@ -202,7 +216,7 @@ def quantize_keys(k: torch.Tensor, t_begin: int = 0, t_end: int | None = None, o
     codes, absmax, resid = out
     _check("ffd_quantize_keys", lib().ffd_quantize_keys(
         _ptr(k), _ptr(codes), _ptr(absmax), _ptr(resid), B, Hkv, Lcap, D, bits, t_begin, t_end,
-        _stream(k.device)))
+        _stream(k)))
     return codes, absmax, resid
 
 
@@ -222,13 +236,16 @@ def append_kv(k_new, v_new, quantized, seq_lens, *, k_cache=None, v_cache=None):
             _need(t, nm, torch.bfloat16, (B, Hkv, Lcap, D))
     _check("ffd_append_kv", lib().ffd_append_kv(
         _ptr(k_new), _ptr(v_new), _ptr(k_cache), _ptr(v_cache), _ptr(codes), _ptr(absmax), _ptr(resid),
-        _ptr(seq_lens), B, Hkv, Lcap, D, bits, _stream(k_new.device)))
+        _ptr(seq_lens), B, Hkv, Lcap, D, bits, _stream(k_new)))
 
 
 def _attn_outputs(q, B, Hq, Lcap, want_lse, want_mask, out, lse, mask):
-    out = torch.empty((B, Hq, HEAD_DIM), dtype=torch.bfloat16, device=q.device) if out is None else out
+    plain = type(q) is torch.Tensor and q.shape[-1] == HEAD_DIM     # then q, checked before, has out's shape
+    if out is None:
+        out = torch.empty_like(q) if plain else torch.empty((B, Hq, HEAD_DIM), dtype=torch.bfloat16, device=q.device)
     if want_lse and lse is None:
-        lse = torch.empty((B, Hq), dtype=torch.float32, device=q.device)
+        lse = (q.new_empty((B, Hq), dtype=torch.float32) if plain else
+               torch.empty((B, Hq), dtype=torch.float32, device=q.device))
     if want_mask and mask is None:
         mask = torch.empty((B, Hq, Lcap // BLOCK), dtype=torch.uint8, device=q.device)
     return out, lse, mask
@@ -271,13 +288,15 @@ def decode_attention(q, codes, absmax, resid, v, seq_lens, *, delta: float, n_si
         ev = (ctypes.c_void_p * 4)(*[e.cuda_event for e in stage_events])
     if kernels not in KERNELS:
         raise ValueError(f"kernels must be one of {tuple(KERNELS)}")
-    extras = DecodeExtras(ctypes.cast(ev, P) if ev is not None else None, _ptr(m_tilde),
-                          PSEUDO_MAX[pseudo_max], int(top_k), KERNELS[kernels])
+    extras = None               # the library's defaults
+    if ev is not None or m_tilde is not None or pseudo_max != "thumbnail" or top_k or kernels != "auto":
+        extras = ctypes.byref(DecodeExtras(ctypes.cast(ev, P) if ev is not None else None, _ptr(m_tilde),
+                                           PSEUDO_MAX[pseudo_max], int(top_k), KERNELS[kernels]))
     _check("ffd_decode_attention", lib().ffd_decode_attention_ex(
         _ptr(q), _ptr(codes), _ptr(absmax), _ptr(resid), _ptr(v), _ptr(seq_lens), B, Hq, Hkv, Lcap,
         D, bits, BLOCK, float(delta), n_sink, n_local, num_splits, float(softmax_scale), _ptr(out),
         _ptr(lse), _ptr(mask), _ptr(workspace), workspace.numel() * workspace.element_size(),
-        _stream(q.device), ctypes.byref(extras)))
+        _stream(q), extras))
     return out, lse, mask
 
 
@@ -304,7 +323,7 @@ def decode_attention_noalloc(q, codes, absmax, resid, v, seq_lens, *, delta: flo
     _check("ffd_decode_attention_noalloc", lib().ffd_decode_attention_noalloc(
         _ptr(q), _ptr(codes), _ptr(absmax), _ptr(resid), _ptr(v), _ptr(seq_lens), B, Hq, Hkv, Lcap,
         D, bits, BLOCK, float(delta), n_sink, n_local, num_splits, float(softmax_scale), _ptr(out),
-        _ptr(lse), _ptr(mask), _stream(q.device)))
+        _ptr(lse), _ptr(mask), _stream(q)))
     return out, lse, mask
 
 
@@ -323,7 +342,7 @@ def dense_decode_attention(q, k, v, seq_lens, *, num_splits: int = 0, softmax_sc
     _check("ffd_dense_decode_attention", lib().ffd_dense_decode_attention(
         _ptr(q), _ptr(k), _ptr(v), _ptr(seq_lens), B, Hq, Hkv, Lcap, D, num_splits,
         float(softmax_scale), _ptr(out), _ptr(lse), _ptr(workspace),
-        workspace.numel() * workspace.element_size(), _stream(q.device)))
+        workspace.numel() * workspace.element_size(), _stream(q)))
     return out, lse
 
 
