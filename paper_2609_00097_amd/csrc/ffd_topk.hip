@@ -5,12 +5,18 @@
 // comparison with a per-head constant made while the scan streams, this needs every block score of
 // the head first: the scan kernel writes them, and this kernel, one workgroup per (sequence, KV
 // head), holds the group's scores in registers (as the order-preserving integer image of the fp32
-// score; each wave holds whole 64-block runs of one head), finds each head's k-th largest score by a
-// most-significant-digit radix select (four 8-bit digits counted in LDS histograms, stopping early
-// once the digit bucket holds exactly the number still needed), marks the blocks above and equal to
+// score; each wave holds whole 64-block runs of one head), finds each head's k-th largest score in one
+// histogram over the head's score range (512 equal bins in LDS) and an exact ranking of the few keys in
+// the bin where the k-th lies, or, where a bin holds more than 64 (ties, outliers) or scores are not
+// finite, by a most-significant-digit radix select (four 8-bit digits counted in LDS histograms, stopping
+// early once the digit bucket holds exactly the number still needed), marks the blocks above and equal to
 // it in LDS bitmaps, then goes through the blocks in order, keeps those above the threshold and the
 // first ones equal to it, and writes the group's kept list (block | keep bits << 24, the union over
 // the group's heads) and its length in the scan's format, so the refinement kernel runs unchanged.
+//
+// Bound: one workgroup per group works alone on its CU; each digit pass is a chain of LDS atomics, a
+// prefix and two barriers. 32 groups of 2048 blocks x 4 heads, k = 67: 12.0 us, with the digit passes
+// alone 17.8.
 #include <climits>
 
 #include "ffd_device.h"
@@ -25,11 +31,17 @@ constexpr int kSelThreads = kTopkSelectThreads;      // 16 waves: 4 per SIMD hid
 constexpr int kSelWaves = kSelThreads / 64;
 constexpr int kSlots = 8;                            // keys held per thread
 constexpr int kTileKeys = kSlots * kSelThreads;      // (block, head) keys per tile
+constexpr int kFine = 2 * kBins;                     // bins of the range histogram (both digit buffers)
+constexpr int kMaxCand = 64;                         // keys of one bin that are ranked by a wave
 
 // Order-preserving image of a float: larger float, larger key. The scan writes +0 for a zero score.
 __device__ __forceinline__ uint32_t order_key(float x) {
     const uint32_t u = __float_as_uint(x);
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+
+__device__ __forceinline__ float key_value(uint32_t key) {
+    return __uint_as_float((key & 0x80000000u) ? key & 0x7fffffffu : ~key);
 }
 
 // hist[bin] += 1 for every active lane, with one LDS atomic per lane at most. Block scores of a head
@@ -96,6 +108,10 @@ struct TopkLds {
     uint32_t prefix[G];                   // digits of the k-th largest key found so far
     int rem[G];                           // keys still to take at or below the prefix
     int done[G];                          // the prefix's bucket holds exactly rem keys: all are taken
+    int found[G];                         // the prefix is the k-th largest key itself
+    uint32_t lo[kSelWaves], hi[kSelWaves];    // each wave's least and largest key
+    int bin[G], above[G], ncand[G];       // bin of the k-th largest key, keys in higher bins, keys in it
+    uint32_t cand[G][kMaxCand];
     int wsum[2][kSelWaves];
 };
 
@@ -145,17 +161,110 @@ __global__ __launch_bounds__(kSelThreads) void ffd_topk_select_kernel(TopkArgs a
         sm.prefix[tid] = 0;
         sm.rem[tid] = keff;
         sm.done[tid] = 0;
+        sm.found[tid] = 0;
+        sm.ncand[tid] = 0;
     }
-    for (int i = tid; i < G * kBins; i += kSelThreads) (&sm.hist[0][0][0])[i] = 0;
+    for (int i = tid; i < G * kFine; i += kSelThreads) (&sm.hist[0][0][0])[i] = 0;
     __syncthreads();
     const int hw = S::head(wave);                    // this wave's head
     const bool select = keff < nblk;                 // else every block is kept
     if (select) {
+        // ---- one histogram over the head's range of scores. The bin (score - least) * 512 / range grows
+        // with the score (each step is monotonic in fp32), so the k-th largest key lies in the bin where the count
+        // from the top reaches k; the keys of that bin are then compared with each other exactly.
+        uint32_t klo = 0xffffffffu, khi = 0u;
+        for (int ti = 0; ti < ntiles; ++ti) {
+            use_tile(ti);
+#pragma unroll
+            for (int i = 0; i < kSlots; ++i)
+                if (valid(ti, i)) {
+                    klo = min(klo, key[i]);
+                    khi = max(khi, key[i]);
+                }
+        }
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            klo = min(klo, (uint32_t)__shfl_xor((int)klo, o));
+            khi = max(khi, (uint32_t)__shfl_xor((int)khi, o));
+        }
+        if (lane == 0) {
+            sm.lo[wave] = klo;
+            sm.hi[wave] = khi;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < S::WPH; ++w) {
+            klo = min(klo, sm.lo[hw + G * w]);
+            khi = max(khi, sm.hi[hw + G * w]);
+        }
+        const float least = key_value(klo), range = key_value(khi) - least;
+        const float per = (float)kFine / range;
+        // not for scores that are not finite (the extremes show them), nor for an empty or overflowing range
+        const bool fine = __builtin_isfinite(least) && __builtin_isfinite(range) && __builtin_isfinite(per);   // one value per head
+        auto bin_of = [&](uint32_t k) { return min(max((int)((key_value(k) - least) * per), 0), kFine - 1); };
+        int* fhist = &sm.hist[0][0][0] + hw * kFine;
+        for (int ti = 0; ti < ntiles && fine; ++ti) {
+            use_tile(ti);
+#pragma unroll
+            for (int i = 0; i < kSlots; ++i)
+                if (valid(ti, i)) atomicAdd(&fhist[bin_of(key[i])], 1);
+        }
+        __syncthreads();
+        if (wave < G && fine) {                         // wave h: head h; lane l holds bins 8 l .. 8 l + 7
+            constexpr int kPer = kFine / 64;
+            int c[kPer], tot = 0;
+#pragma unroll
+            for (int i = 0; i < kPer; ++i) {
+                c[i] = fhist[kPer * lane + i];
+                tot += c[i];
+            }
+            const int incl = wave_inclusive_scan(tot);
+            int above = __builtin_amdgcn_readlane(incl, 63) - incl;      // keys in the bins of higher lanes
+#pragma unroll
+            for (int i = kPer - 1; i >= 0; --i) {
+                if (above < keff && above + c[i] >= keff) {
+                    sm.bin[wave] = kPer * lane + i;
+                    sm.above[wave] = above;
+                    sm.found[wave] = c[i] <= kMaxCand;
+                }
+                above += c[i];
+            }
+        }
+        __syncthreads();
+        for (int ti = 0; ti < ntiles && sm.found[hw]; ++ti) {
+            use_tile(ti);
+#pragma unroll
+            for (int i = 0; i < kSlots; ++i)
+                if (valid(ti, i) && bin_of(key[i]) == sm.bin[hw]) sm.cand[hw][atomicAdd(&sm.ncand[hw], 1)] = key[i];
+        }
+        __syncthreads();
+        if (wave < G && sm.found[wave]) {
+            const int nc = sm.ncand[wave], r = keff - sm.above[wave];    // the bin's r-th largest key is sought
+            const uint32_t mine = lane < nc ? sm.cand[wave][lane] : 0u;
+            int larger = 0, equal = 0;
+            for (int i = 0; i < nc; ++i) {
+                const uint32_t other = (uint32_t)__builtin_amdgcn_readlane((int)mine, i);
+                larger += other > mine ? 1 : 0;
+                equal += other == mine ? 1 : 0;
+            }
+            if (lane < nc && larger < r && larger + equal >= r) {        // equal keys write the same
+                sm.prefix[wave] = mine;
+                sm.rem[wave] = r - larger;
+            }
+        }
+        __syncthreads();
+        bool all_found = true;
+#pragma unroll
+        for (int h = 0; h < G; ++h) all_found = all_found && sm.found[h];
+        if (!all_found) {                               // uniform
+            for (int i = tid; i < G * kFine; i += kSelThreads) (&sm.hist[0][0][0])[i] = 0;
+            __syncthreads();
+        }
         uint32_t pmask = 0;
-        for (int pass = 0, shift = 24; shift >= 0; ++pass, shift -= 8) {
+        for (int pass = 0, shift = 24; shift >= 0 && !all_found; ++pass, shift -= 8) {
             int (*hist)[kBins] = sm.hist[pass & 1];
             const uint32_t pre = sm.prefix[hw];
-            const bool live = !sm.done[hw];
+            const bool live = !sm.done[hw] && !sm.found[hw];
             for (int ti = 0; ti < ntiles && live; ++ti) {  // uniform in the wave
                 use_tile(ti);
 #pragma unroll
@@ -167,7 +276,7 @@ __global__ __launch_bounds__(kSelThreads) void ffd_topk_select_kernel(TopkArgs a
             // wave w: heads w, w + 4. Lane l holds buckets 4l .. 4l + 3; "above" counts the keys in
             // higher buckets; the bucket where the count reaches rem holds the k-th largest key.
             for (int h = wave; h < G; h += kSelWaves) {
-                if (sm.done[h]) continue;               // uniform in the wave
+                if (sm.done[h] || sm.found[h]) continue;    // uniform in the wave
                 int c[4], tot = 0;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
@@ -199,7 +308,7 @@ __global__ __launch_bounds__(kSelThreads) void ffd_topk_select_kernel(TopkArgs a
             __syncthreads();
             bool all_done = true;
 #pragma unroll
-            for (int h = 0; h < G; ++h) all_done = all_done && sm.done[h];
+            for (int h = 0; h < G; ++h) all_done = all_done && (sm.done[h] || sm.found[h]);
             if (all_done) break;                        // uniform: read after the barrier
         }
     }

@@ -225,3 +225,23 @@ def test_maximum_capacity():
     nb = c.Lcap // 64
     assert not mask[:, :, nb:].any()
     compare_topk(c, 29, out, lse, mask[:, :, :nb].contiguous())
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(8, 2), (16, 2), (2, 2)])
+@pytest.mark.parametrize("k", [1, 2, 90])
+def test_bins_too_full_to_rank(Hq, Hkv, k):
+    """Scores that crowd one bin of the range histogram, which then goes through the digit select: in KV
+    head 0 one block 4096 times the others; in KV head 1 three blocks repeated about 100 times each (exact
+    ties). Sequence 1 is ordinary, so that both ways are taken in one launch."""
+    from paper_2609_00097_amd import ffd
+    c = I.small_case(seed=77 + k, B=2, Hq=Hq, Hkv=Hkv, seq_lens=(20000, 19000), Lcap=20032)
+    scaled = O.f64_to_bf16_bits(4096.0 * O.bf16_to_f64(c.k[0, 0, 64 * 7:64 * 8]))
+    c.k[0, 0, 64 * 7:64 * 8] = scaled
+    tpl = [c.k[0, 1, 64 * (i + 1):64 * (i + 2)].copy() for i in range(3)]
+    for j in range(20000 // 64):
+        c.k[0, 1, 64 * j:64 * j + 64] = tpl[j % 3]
+    print(f"case top-k crowded bins Hq={Hq} k={k}", flush=True)
+    up = Uploaded(c)
+    out, lse, mask = _run(up, ffd.quantize_keys(up.k), k)
+    compare_topk(c, k, out, lse, mask, heads=[(0, 1)], exact=True)
+    compare_topk(c, k, out, lse, mask, heads=[(0, 0), (1, 0), (1, 1)])
