@@ -201,12 +201,15 @@ int decode_splits(int B, int Hkv, int Lcap, int num_splits) {
 // query heads per KV head or 8-bit codes its registers (150 and 134 a lane) leave room for one workgroup
 // per CU, so an automatic count of two per CU would run in two rounds; it is one per CU then (2 sequences
 // of 60K, G = 8, b = 4: step 41.3 us with 512 workgroups, 32.3 with 256; 1 x 62K, G = 4, b = 8: 32.9 and
-// 25.9 us).
+// 25.9 us), as long as that leaves at most kFusedMaxBlocks blocks each: with more, the kept blocks of the
+// workgroups differ too much and two rounds of smaller ones end sooner (32 x 6.7K, 8 KV heads, G = 8,
+// delta 7: 92 us with 512 workgroups of 53 blocks, 108 with 256 of 105).
 int fused_launch_splits(int S1f, int B, int Hkv, int Lcap, int G, int bits, int num_splits) {
     const long long pairs = (long long)B * Hkv, cus = device_cus();
     if (num_splits > 0 || (G <= 4 && bits != 8) || S1f * pairs <= cus) return S1f;
     const long long need = (Lcap / FFD_BLOCK + kFfdMaxScanBlocks - 1) / kFfdMaxScanBlocks;
-    return (int)std::min((long long)S1f, std::max({1LL, need, cus / pairs}));
+    const long long s = std::min((long long)S1f, std::max({1LL, need, cus / pairs}));
+    return (int)((Lcap / FFD_BLOCK + s - 1) / s <= kFusedMaxBlocks ? s : S1f);
 }
 
 // Slots (workgroups per KV head) of the scan and of the fused kernel. Where they follow the lengths they
@@ -331,6 +334,16 @@ void launch_refine_nt(int rbits, dim3 grid, hipStream_t stream, const RefineArgs
     if (rbits == 2) hipLaunchKernelGGL((ffd_refine_kernel<NT, 2>), grid, dim3(kRefineThreads), 0, stream, ra);
     else if (rbits == 4) hipLaunchKernelGGL((ffd_refine_kernel<NT, 4>), grid, dim3(kRefineThreads), 0, stream, ra);
     else hipLaunchKernelGGL((ffd_refine_kernel<NT, 8>), grid, dim3(kRefineThreads), 0, stream, ra);
+}
+
+// The merge of the partial rows located by table (or S rows of G heads per group).
+void launch_merge(int heads, hipStream_t stream, const float* m, const float* l, const float* acc, int S, const int2* table,
+                  int G, uint16_t* out, float* lse) {
+    const dim3 grid((unsigned)heads, kMergeSlices);
+    if (heads >= kMergeOneWaveHeads)
+        hipLaunchKernelGGL(lse_merge_kernel<1>, grid, dim3(64), 0, stream, m, l, acc, S, table, G, out, lse);
+    else
+        hipLaunchKernelGGL(lse_merge_kernel<4>, grid, dim3(256), 0, stream, m, l, acc, S, table, G, out, lse);
 }
 
 // Every argument check of ffd_decode_attention_ex, in its order, with nothing launched; with
@@ -555,8 +568,7 @@ int ffd_decode_attention_ex(const void* q, const void* k_codes, const void* k_ab
         launch_fused(thumb_bits, G <= 4 ? 1 : 2, mode, slot_grid(Hkv, fs.grid), stream, fa);
         if ((st = launch_status()) != FFD_OK || (st = mark(1)) != FFD_OK || (st = mark(2)) != FFD_OK) return st;
         if (!direct) {
-            hipLaunchKernelGGL(lse_merge_kernel, dim3((unsigned)(B * Hq), kMergeSlices), dim3(kThreads), 0, stream, fpart_m,
-                               fpart_l, fpart_acc, S1l, ftable, G, static_cast<uint16_t*>(out), lse);
+            launch_merge(B * Hq, stream, fpart_m, fpart_l, fpart_acc, S1l, ftable, G, static_cast<uint16_t*>(out), lse);
             if ((st = launch_status()) != FFD_OK) return st;
         }
         return mark(3);
@@ -580,8 +592,7 @@ int ffd_decode_attention_ex(const void* q, const void* k_codes, const void* k_ab
     if (G <= 4) launch_refine_nt<1>(thumb_bits, refine_grid, stream, ra);
     else launch_refine_nt<2>(thumb_bits, refine_grid, stream, ra);
     if ((st = launch_status()) != FFD_OK || (st = mark(2)) != FFD_OK) return st;
-    hipLaunchKernelGGL(lse_merge_kernel, dim3((unsigned)(B * Hq), kMergeSlices), dim3(kThreads), 0, stream, part_m, part_l,
-                       part_acc, 0, table, G, static_cast<uint16_t*>(out), lse);
+    launch_merge(B * Hq, stream, part_m, part_l, part_acc, 0, table, G, static_cast<uint16_t*>(out), lse);
     if ((st = launch_status()) != FFD_OK) return st;
     return mark(3);
 }
@@ -644,8 +655,7 @@ int ffd_dense_decode_attention(const void* q, const void* k, const void* v, cons
         hipLaunchKernelGGL(dense_decode_kernel<2>, grid, dim3(kThreads), 0, stream, a);
     st = launch_status();
     if (st != FFD_OK) return st;
-    hipLaunchKernelGGL(lse_merge_kernel, dim3((unsigned)(B * Hq), kMergeSlices), dim3(kThreads), 0, stream, P.m, P.l,
-                       P.acc, S, table, balanced ? G : 1, static_cast<uint16_t*>(out), lse);
+    launch_merge(B * Hq, stream, P.m, P.l, P.acc, S, table, balanced ? G : 1, static_cast<uint16_t*>(out), lse);
     return launch_status();
 }
 

@@ -174,7 +174,11 @@ template <int NT> __global__ void dense_decode_kernel(DenseArgs a);
 template <int BITS> __global__ void quantize_keys_kernel(QuantArgs a);
 template <int BITS> __global__ void append_kv_kernel(AppendArgs a);
 constexpr int kMergeSlices = 4;                // workgroups per head of the merge, 32 dims each
-__global__ void lse_merge_kernel(const float* part_m, const float* part_l, const float* part_acc, int S,
-                                 const int2* table, int G, uint16_t* out, float* lse);
+// NW waves per workgroup: 4, or 1 from kMergeOneWaveHeads heads on (their waves fill the chip alone).
+constexpr int kMergeOneWaveHeads = 256;
+template <int NW>
+__global__ void lse_merge_kernel(const float* __restrict__ part_m, const float* __restrict__ part_l,
+                                 const float* __restrict__ part_acc, int S, const int2* __restrict__ table, int G,
+                                 uint16_t* __restrict__ out, float* __restrict__ lse);
 
 }  // namespace ffd

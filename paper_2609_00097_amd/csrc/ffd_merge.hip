@@ -6,12 +6,14 @@
 // Partial rows of head bh = b * Hq + h: i * G + bh % G for i = first .. last, (first, last) = table[bh / G]
 // (last < first: none), or, without a table, the S rows from S * (bh / G) on.
 //
-// Bound: latency (a table load, the rows, two reductions, the store). One workgroup per head and quarter
-// of its dims, so that few heads still spread over the CUs; thread (r, d4) takes rows r, r + 32, ... of
-// dims 4 d4 .. 4 d4 + 3, all of a batch's rows requested at once (64 rows, or 256 where there are more),
-// their common maximum first and then one rescaling per row. Against one workgroup per head that folded
-// the rows one after the other: 4 heads of 256 rows 6.4 -> 3.9 us, 32 heads of 32 rows 4.0 us both in the
-// kernel trace, and the step at 1 x 256K 25.7 -> 23.9 us.
+// Bound: latency (a table load, the rows, two reductions, the store), and with very many heads the number
+// of waves. One workgroup of NW waves per head and quarter of its dims, so that few heads still spread over
+// the CUs; thread (r, d4) takes rows r, r + 8 NW, ... of dims 4 d4 .. 4 d4 + 3, all of a batch's rows
+// requested at once (16 NW rows, or 64 NW where there are more), their common maximum first and then one
+// rescaling per row. Against one workgroup per head that folded the rows one after the other: 4 heads of
+// 256 rows 6.4 -> 3.9 us (NW = 4), the step at 1 x 256K 25.7 -> 23.9 us;
+// 1024, 2048 and 4096 heads of 2 to 4 rows 5.2, 9.3 and 16.0 -> 4.0, 5.0 and 8.0 us (NW = 1; 6.3, 10.8 and
+// 18.8 us with four waves).
 #include "ffd_device.h"
 #include "ffd_kernels.h"
 
@@ -19,7 +21,6 @@ namespace ffd {
 
 namespace {
 
-constexpr int kRowLanes = kThreads / 8;        // rows in parallel
 constexpr int kSliceDims = kD / kMergeSlices;  // 8 lanes of 4 dims
 
 struct State {
@@ -29,9 +30,9 @@ struct State {
 
 __device__ __forceinline__ float rescale(float m, float M) { return m == -INFINITY ? 0.f : __expf(m - M); }
 
-// Folds rows s0 + kRowLanes u (u < U) below count into st; the row index is clamped, so that the loads are
+// Folds rows s0 + LANES u (u < U) below count into st; the row index is clamped, so that the loads are
 // unconditional.
-template <int U>
+template <int U, int LANES>
 __device__ __forceinline__ void fold_rows(State& st, const float* __restrict__ part_m, const float* __restrict__ part_l,
                                           const float* __restrict__ part_acc, size_t row0, size_t stride, int count,
                                           int s0) {
@@ -39,7 +40,7 @@ __device__ __forceinline__ void fold_rows(State& st, const float* __restrict__ p
     float4 a[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const int s = s0 + u * kRowLanes;
+        const int s = s0 + u * LANES;
         const size_t row = row0 + (size_t)min(s, count - 1) * stride;
         m[u] = part_m[row];
         l[u] = part_l[row];
@@ -85,12 +86,14 @@ __device__ __forceinline__ float rows_sum(float x) {
 }  // namespace
 
 // Grid (B * Hq, kMergeSlices).
-__global__ __launch_bounds__(kThreads) void lse_merge_kernel(const float* __restrict__ part_m,
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void lse_merge_kernel(const float* __restrict__ part_m,
                                                              const float* __restrict__ part_l,
                                                              const float* __restrict__ part_acc, int S,
                                                              const int2* __restrict__ table, int G,
                                                              uint16_t* __restrict__ out, float* __restrict__ lse) {
-    __shared__ float part[kWaves][8][8];            // each wave's state per d4
+    constexpr int kRowLanes = 8 * NW;               // rows in parallel
+    __shared__ float part[NW][8][8];                // each wave's state per d4
     const int tid = threadIdx.x, d4 = tid & 7, r = tid >> 3, wave = tid >> 6, lane = tid & 63;
     const size_t x = blockIdx.x / G;                        // blockIdx.x = b * Hq + h
     size_t first = x * S;
@@ -103,9 +106,9 @@ __global__ __launch_bounds__(kThreads) void lse_merge_kernel(const float* __rest
     const float* acc = part_acc + blockIdx.y * kSliceDims + 4 * d4;
     State st{-INFINITY, 0.f, {0.f, 0.f, 0.f, 0.f}};
     if (S > 2 * kRowLanes) {                                // uniform
-        for (int s0 = 0; s0 < S; s0 += 8 * kRowLanes) fold_rows<8>(st, part_m, part_l, acc, row0, G, S, s0 + r);
+        for (int s0 = 0; s0 < S; s0 += 8 * kRowLanes) fold_rows<8, kRowLanes>(st, part_m, part_l, acc, row0, G, S, s0 + r);
     } else if (S > 0) {
-        fold_rows<2>(st, part_m, part_l, acc, row0, G, S, r);
+        fold_rows<2, kRowLanes>(st, part_m, part_l, acc, row0, G, S, r);
     }
     const float M = rows_max(st.m);
     const float c = rescale(st.m, M);
@@ -117,17 +120,18 @@ __global__ __launch_bounds__(kThreads) void lse_merge_kernel(const float* __rest
         *reinterpret_cast<float4*>(&part[wave][d4][0]) = make_float4(a[0], a[1], a[2], a[3]);
         *reinterpret_cast<float2*>(&part[wave][d4][4]) = make_float2(M, l);
     }
-    __syncthreads();
+    if constexpr (NW > 1) __syncthreads();
+    else wave_lds_fence();
     if (tid >= 8) return;
-    float Mw[kWaves], Mx = -INFINITY, lx = 0.f;
+    float Mw[NW], Mx = -INFINITY, lx = 0.f;
     float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
+    for (int w = 0; w < NW; ++w) {
         Mw[w] = part[w][d4][4];
         Mx = fmaxf(Mx, Mw[w]);
     }
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
+    for (int w = 0; w < NW; ++w) {
         const float cw = rescale(Mw[w], Mx);
         const float4 aw = *reinterpret_cast<const float4*>(&part[w][d4][0]);
         lx = fmaf(cw, part[w][d4][5], lx);
@@ -144,5 +148,8 @@ __global__ __launch_bounds__(kThreads) void lse_merge_kernel(const float* __rest
     *reinterpret_cast<uint2*>(out + (size_t)blockIdx.x * kD + blockIdx.y * kSliceDims + 4 * d4) = packed;
     if (lse && blockIdx.y == 0 && d4 == 0) lse[blockIdx.x] = any ? Mx + logf(lx) : -INFINITY;
 }
+
+template __global__ void lse_merge_kernel<1>(const float*, const float*, const float*, int, const int2*, int, uint16_t*, float*);
+template __global__ void lse_merge_kernel<4>(const float*, const float*, const float*, int, const int2*, int, uint16_t*, float*);
 
 }  // namespace ffd
