@@ -443,7 +443,14 @@ __global__ __launch_bounds__(kScanThreads, scan_occupancy<BITS>()) void ffd_scan
     constexpr bool kTopK = MODE == kSelTopK;
     constexpr int kRing = scan_ring<BITS>();
     __shared__ ScanLds<NT> sm;
-    const int kvh = blockIdx.x, t = blockIdx.y + kSlotGridY * blockIdx.z;
+    // 4-bit codes: eight slots of a KV head, then of the next (at 4 x 128K, where all strides are powers of
+    // two, the scan takes 52 us this way and 56 with the KV heads first; 2 and 8 bits: 29 and 29, 96 and 93)
+    int kvh = blockIdx.x, t = blockIdx.y + kSlotGridY * blockIdx.z;
+    if constexpr (slots_by_eight(BITS)) {
+        const int turn = blockIdx.x / (8 * a.Hkv), at = blockIdx.x - turn * 8 * a.Hkv;
+        kvh = at >> 3;
+        t = 8 * turn + (at & 7);
+    }
     if (t >= a.grid_slots) return;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int g = lane >> 4, n = lane & 15;

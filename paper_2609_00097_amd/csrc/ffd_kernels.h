@@ -26,6 +26,8 @@ constexpr int kInfoSplitMask = (1 << kInfoSplitBits) - 1;
 // Most blocks one scan workgroup covers (its kept list is staged in LDS), most scan workgroups per
 // (sequence, KV head).
 constexpr int kFfdMaxScanBlocks = 256;
+// Whether the scan kernel's grid is one-dimensional, eight slots of each KV head in turn.
+__host__ __device__ constexpr bool slots_by_eight(int bits) { return bits == 4; }
 constexpr int kSlotGridY = 32768;              // slots along the grid's y (then z)
 constexpr int kBalanceMaxSeqs = 64;            // largest batch whose scan slots follow the lengths
 constexpr int kScanWaves = 8;                  // waves per scan workgroup (one workgroup per CU)
