@@ -1026,8 +1026,8 @@ __global__ __launch_bounds__(kRefineThreads, 1) void ffd_refine_kernel(RefineArg
     const bool queue = T / a.W >= 2 * kUnitBlocks && a.max_units >= 2 * a.W;
     const int U = queue ? min(a.max_units, T / kUnitBlocks) : U1;
     const double T1 = queue ? floor((double)T * kFirstShare) : (double)T;
-    // first position of unit u <= U; every unit has at least one (queued ones: at least 0.2 (1 -
-    // kFirstShare) kUnitBlocks). Products stay below 2^52, so that whole results are exact.
+    // first position of unit u <= U; every unit has at least one (queued ones: 0.2 (1 - kFirstShare)
+    // kUnitBlocks = 1.7 or more). Products stay below 2^52, so that whole results are exact.
     auto first_of = [&](int u) {
         if (u <= U1) return (int)floor((double)u * T1 / (double)U1);
         const double v = (double)(u - U1) / (double)(U - U1);
