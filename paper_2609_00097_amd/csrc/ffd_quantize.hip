@@ -4,13 +4,14 @@
 // b = 2 is App. A's codebook {-1.5, -0.5, 0.5, 1.5} with the residual rint(381 k / M) - 254 c + 381.
 //
 // Exactness. With F = 254 Lv and Q = F k / M, the code is c = i + 2^(b-1), i = floor(Q / 254), and
-// the residual rint(Q) - 254 i - 127. For 2^-100 < M < 2^100:
+// the residual rint(Q) - 254 i - 127. For 2^-100 < M < 2^16:
 //  * F / M is held as hi + lo (lo from the exact remainder of the division), so q = fma(k, hi, k lo)
 //    is Q rounded to fp32: where Q itself is an fp32 value (every tie of the rounding, every bin edge
 //    254 i) q == Q exactly.
 //  * 254 j * fl(1/254) rounds to j exactly for every bin edge, and a Q that is no edge lies at least
 //    2^-17 Q from every edge (|(2^b - 1) k - 2 M j| is a multiple of the smaller ulp), so
-//    floor(q * fl(1/254)) is the exact floor.
+//    floor(q * fl(1/254)) is the exact floor. The product has to keep the sign of a k far below M: the
+//    smallest, 2^-133 (2^b - 1) / M, stays above the 2^-150 that would round to 0 while M < 2^17.
 //  * a Q that is no tie lies at least 2^-18 Q (b = 2) or 2^-20 Q (b = 4) from every half-integer, so
 //    rint(q), half to even, is the exact rounding. For b = 8 that distance is 2^-24 Q, so q can land
 //    on a half-integer that Q only comes near: there the exact remainder F k - q M decides.
@@ -40,7 +41,7 @@ typedef unsigned short v2u16 __attribute__((ext_vector_type(2)));
 // A token's absmax and 254 Lv / M as hi + lo (zero for M = 0).
 struct TokenScale {
     float m, hi, lo;
-    bool special;       // M outside (2^-100, 2^100), infinities or NaN: the fp64 path
+    bool special;       // M outside (2^-100, 2^16), infinities or NaN: the fp64 path
 };
 
 // One 16-dim slice: its code words (those of lane l in ffd.h) and residual bytes.
@@ -71,7 +72,7 @@ __device__ __forceinline__ TokenScale token_scale(uint32_t absmax2) {
     constexpr float kFull = 127.f * ((1 << BITS) - 1);      // 254 Lv
     TokenScale s;
     s.m = bf16_to_f32((uint16_t)bits);
-    s.special = !(s.m < 0x1p100f && s.m > 0x1p-100f) && bits != 0;
+    s.special = !(s.m < 0x1p16f && s.m > 0x1p-100f) && bits != 0;
     const float r = 1.f / s.m, hi = kFull / s.m;
     s.hi = bits == 0 ? 0.f : hi;
     s.lo = bits == 0 ? 0.f : fmaf(-hi, s.m, kFull) * r;

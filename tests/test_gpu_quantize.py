@@ -103,3 +103,39 @@ def test_ties_and_edges_of_every_absmax_mantissa(bits):
     print(f"case ties and edges bits={bits}", flush=True)
     _assert_equal_packed(_gpu_quantize(k_bits, t0, t1, bits=bits), O.quantize_cache(k_bits, t0, t1, bits=bits),
                          f"ties bits={bits}")
+
+
+@pytest.mark.parametrize("bits", [2, 4, 8])
+def test_smallest_values_next_to_every_absmax_exponent(bits):
+    """Three mantissas of M at every bf16 exponent, next to values down to the smallest subnormal of
+    either sign: the sign of a value far below M still decides its level (a negative one lies in the bin
+    below 0), also where its quotient by M is no fp32 number. The quantizer, and append_kv with one token
+    per sequence, bit-exact."""
+    from paper_2609_00097_amd import ffd
+    rng = np.random.default_rng(29 + bits)
+    rows = []
+    for e in range(-133, 128):
+        for mant in (1.0, 129 / 128, 255 / 128):
+            M = O.bf16_to_f64(O.f64_to_bf16_bits(np.array([mant * 2.0 ** e])))[0]
+            gaps = np.concatenate([np.arange(140, 166), rng.integers(0, 261, 35)])
+            low = np.maximum(2.0 ** (e - gaps.astype(np.float64)), 2.0 ** -133)
+            low = np.concatenate([low, [2.0 ** -133, 2.0 ** -126]])
+            row = np.minimum(np.concatenate([low, low * 1.9921875]), M)
+            row = O.bf16_to_f64(O.f64_to_bf16_bits(row)) * rng.choice([-1.0, -1.0, 1.0], size=126)
+            rows.append(np.concatenate([[M, -M], row]))
+    vals = np.array(rows)
+    ntok = len(vals)
+    Lcap = -(-ntok // 64) * 64
+    k_bits = np.zeros((1, 1, Lcap, 128), dtype=np.uint16)
+    k_bits[0, 0, :ntok] = O.f64_to_bf16_bits(vals)
+    print(f"case smallest values bits={bits}", flush=True)
+    _assert_equal_packed(_gpu_quantize(k_bits, bits=bits), O.quantize_cache(k_bits, bits=bits), f"bits={bits}")
+    one = np.zeros((ntok, 1, 64, 128), dtype=np.uint16)              # a sequence per token
+    one[:, 0, 0] = k_bits[0, 0, :ntok]
+    qk = ffd.quantize_keys(bits_to_bf16(np.zeros_like(one)), bits=bits)
+    k_new = bits_to_bf16(one[:, :, 0])
+    lens = torch.zeros(ntok, dtype=torch.int32, device="cuda")
+    ffd.append_kv(k_new, k_new, qk, lens)
+    torch.cuda.synchronize()
+    got = (qk[0].cpu().numpy().view(np.uint32), qk[1].cpu().view(torch.int16).numpy().view(np.uint16), qk[2].cpu().numpy())
+    _assert_equal_packed(got, O.quantize_cache(one, bits=bits), f"append bits={bits}")
