@@ -212,20 +212,20 @@ int fused_launch_splits(int S1f, int B, int Hkv, int Lcap, int G, int bits, int 
     return (int)((Lcap / FFD_BLOCK + s - 1) / s <= kFusedMaxBlocks ? s : S1f);
 }
 
-// Slots (workgroups per KV head) of the scan and of the fused kernel. Where they follow the lengths they
-// are meant to fill the CUs `per_cu` times and no more (shares are equal, so a few workgroups over would
-// double the time: 5 sequences of 87K to 219K x 4 KV heads, all 70 slots = 280 workgroups used: scan 33.9
-// us, 64 slots: 25.4; 14 slots per sequence, as before: 26.5); the grid has as many as the longest
-// sequences of the capacity need.
+// Slots (workgroups per KV head) of the scan and of the fused kernel. Where they follow the lengths, a round
+// of them fills the CUs `per_cu` times and no more (shares are equal, so a few workgroups over would double
+// the time: 5 sequences of 87K to 219K x 4 KV heads, all 70 slots = 280 workgroups used: scan 33.9 us, 64
+// slots: 25.4; 14 slots per sequence, as before: 26.5). The grid has as many rounds as the longest sequences
+// of the capacity need, B * S1 slots at most; the kernel uses the rounds that the lengths need.
 struct Slots {
-    int meant, grid;
+    int round, grid;
 };
 Slots slots_of(int B, int Hkv, int Lcap, int S1, int per_cu) {
     const long long all = (long long)B * S1;
     if (B == 1 || B > kBalanceMaxSeqs) return Slots{(int)all, (int)all};
     const long long need = B * (long long)((Lcap / FFD_BLOCK + kFfdMaxScanBlocks - 1) / kFfdMaxScanBlocks);
-    const long long meant = std::min(all, std::max((long long)B, (long long)per_cu * device_cus() / Hkv));
-    return Slots{(int)meant, (int)std::max(need, meant)};
+    const long long round = std::max(1LL, (long long)per_cu * device_cus() / Hkv);
+    return Slots{(int)std::min(all, round), (int)std::min(all, round * ((need + round - 1) / round))};
 }
 dim3 slot_grid(int Hkv, int slots) {
     return dim3((unsigned)Hkv, (unsigned)std::min(slots, kSlotGridY), (unsigned)((slots + kSlotGridY - 1) / kSlotGridY));
@@ -533,7 +533,7 @@ int ffd_decode_attention_ex(const void* q, const void* k_codes, const void* k_ab
     float* part_acc = part_l + rows;
     ScanArgs sa{static_cast<const uint16_t*>(q), static_cast<const uint32_t*>(k_codes),
                 static_cast<const uint16_t*>(k_absmax), static_cast<const int8_t*>(k_resid), seq_lens, lists,
-                info, table, ticket, sigma, block_mask, m_tilde, B, Hq, Hkv, Lcap, G, S1, ss.meant, ss.grid, delta, scale, n_sink, n_local};
+                info, table, ticket, sigma, block_mask, m_tilde, B, Hq, Hkv, Lcap, G, S1, ss.round, ss.grid, delta, scale, n_sink, n_local};
     RefineArgs ra{static_cast<const uint16_t*>(q), static_cast<const uint32_t*>(k_codes),
                   static_cast<const uint16_t*>(k_absmax), static_cast<const int8_t*>(k_resid),
                   static_cast<const uint16_t*>(v), lists, info, table, ticket, part_m, part_l, part_acc, Lcap, G, (int)Wr,
@@ -565,7 +565,7 @@ int ffd_decode_attention_ex(const void* q, const void* k_codes, const void* k_ab
                      static_cast<const uint16_t*>(k_absmax), static_cast<const int8_t*>(k_resid),
                      static_cast<const uint16_t*>(v), seq_lens, block_mask, m_tilde, fpart_m, fpart_l, fpart_acc,
                      ftable, direct ? static_cast<uint16_t*>(out) : nullptr, direct ? lse : nullptr,
-                     B, Hq, Hkv, Lcap, G, S1l, fs.meant, fs.grid, delta, scale, n_sink, n_local};
+                     B, Hq, Hkv, Lcap, G, S1l, fs.round, fs.grid, delta, scale, n_sink, n_local};
         launch_fused(thumb_bits, G <= 4 ? 1 : 2, mode, slot_grid(Hkv, fs.grid), stream, fa);
         if ((st = launch_status()) != FFD_OK || (st = mark(1)) != FFD_OK || (st = mark(2)) != FFD_OK) return st;
         if (!direct) {

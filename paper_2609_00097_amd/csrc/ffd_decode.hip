@@ -270,10 +270,12 @@ __device__ __forceinline__ int ceil_div(int n, int d, float r) {
     return q;
 }
 
-// t: the workgroup's slot. T is chosen for `slots` slots (>= B) and is kFfdMaxScanBlocks at most: the
-// grid has enough slots for that, B * ceil(capacity blocks / kFfdMaxScanBlocks), also where it is larger.
-__device__ __forceinline__ Slot slot_of(const int32_t* __restrict__ seq_lens, int B, int S1, int slots, int Lcap, int t,
-                                        int lane) {
+// t: the workgroup's slot. T is chosen for the fewest rounds of `round` slots (which fill the CUs) that hold
+// the sequences in shares of kFfdMaxScanBlocks, up to the grid's slots (>= B * ceil(capacity blocks /
+// kFfdMaxScanBlocks)): a second round that is begun is then filled with smaller shares (5 sequences of 112K
+// to 150K, 8 KV heads: scan 42.5 us with 42 slots of up to 256 blocks, 38.0 with 50 of up to 210).
+__device__ __forceinline__ Slot slot_of(const int32_t* __restrict__ seq_lens, int B, int S1, int round, int grid_slots,
+                                        int Lcap, int t, int lane) {
     if (B == 1 || S1 == 1 || B > kBalanceMaxSeqs) { // uniform
         const int b = B == 1 ? 0 : (S1 == 1 ? t : t / S1);
         return Slot{b, t - b * S1, S1, b * S1, min(max(seq_lens[b], 0), Lcap)};
@@ -281,12 +283,14 @@ __device__ __forceinline__ Slot slot_of(const int32_t* __restrict__ seq_lens, in
     const int L = lane < B ? min(max(seq_lens[lane], 0), Lcap) : 0;
     const int n = (L + kBlock - 1) / kBlock;
     const int N = wave_sum_dpp(n), longest = (int)wave_max_dpp((float)n);
+    const int least = wave_sum_dpp(lane < B ? max((n + kFfdMaxScanBlocks - 1) / kFfdMaxScanBlocks, 1) : 0);
+    const int slots = min(grid_slots, round * ceil_div(least, round, __builtin_amdgcn_rcpf((float)round)));
     // T lies between N / slots and what gives every sequence the same number of slots; candidates
     // lo + i step, one per lane, from coarse to fine
     int each = (int)((float)slots * __builtin_amdgcn_rcpf((float)B));      // floor(slots / B)
     each -= each * B > slots ? 1 : 0;
     each += (each + 1) * B <= slots ? 1 : 0;
-    int hi = max(ceil_div(longest, each, __builtin_amdgcn_rcpf((float)each)), 1);
+    int hi = min(max(ceil_div(longest, each, __builtin_amdgcn_rcpf((float)each)), 1), kFfdMaxScanBlocks);
     int lo = max(ceil_div(N, slots, __builtin_amdgcn_rcpf((float)slots)), (longest + kFfdMaxScanSplits - 1) / kFfdMaxScanSplits);
     lo = min(max(lo, 1), hi);
     while (lo < hi) {
@@ -299,7 +303,6 @@ __device__ __forceinline__ Slot slot_of(const int32_t* __restrict__ seq_lens, in
         hi = min(lo + first * step, hi);
         lo = first > 0 ? min(lo + (first - 1) * step + 1, hi) : hi;
     }
-    hi = min(hi, kFfdMaxScanBlocks);
     const int S = lane < B ? max(ceil_div(n, hi, __builtin_amdgcn_rcpf((float)hi)), 1) : 0;
     const int incl = wave_inclusive_scan(S);
     const uint64_t after = __ballot(incl > t);
@@ -454,7 +457,7 @@ __global__ __launch_bounds__(kScanThreads, scan_occupancy<BITS>()) void ffd_scan
     if (t >= a.grid_slots) return;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int g = lane >> 4, n = lane & 15;
-    const Slot sl = slot_of(a.seq_lens, a.B, a.S1, a.slots, a.Lcap, t, lane);
+    const Slot sl = slot_of(a.seq_lens, a.B, a.S1, a.round_slots, a.grid_slots, a.Lcap, t, lane);
     const int b = sl.b, s = sl.s, S = sl.S, L = sl.L;
     // records in (group, split) order; a slot that is not used holds no block and begins no group
     const size_t rec = b < 0 ? (size_t)t * a.Hkv + kvh : (size_t)sl.base * a.Hkv + (size_t)kvh * S + s;
@@ -704,7 +707,7 @@ __global__ __launch_bounds__(kScanThreads, 1) void ffd_decode_kernel(FusedArgs a
     if (t >= a.grid_slots) return;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int g = lane >> 4, n = lane & 15;
-    const Slot sl = slot_of(a.seq_lens, a.B, a.S1, a.slots, a.Lcap, t, lane);
+    const Slot sl = slot_of(a.seq_lens, a.B, a.S1, a.round_slots, a.grid_slots, a.Lcap, t, lane);
     if (sl.b < 0) return;                           // uniform: a slot no sequence needs
     const int b = sl.b, s = sl.s, S1 = sl.S, L = sl.L;
     const int G = a.G, hq0 = kvh * G;

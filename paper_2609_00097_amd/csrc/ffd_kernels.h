@@ -56,7 +56,7 @@ struct ScanArgs {
     float* sigma;               // top-k selection: block scores [B*Hkv, Lcap/64, G]
     uint8_t* mask;              // [B, Hq, Lcap/64] or null
     float* m_tilde;             // [B, Hq] or null: the pseudo-max of each head
-    int B, Hq, Hkv, Lcap, G, S1, slots, grid_slots;    // S1 per sequence, or `slots` by the lengths (slot_of)
+    int B, Hq, Hkv, Lcap, G, S1, round_slots, grid_slots;    // S1 per sequence, or by the lengths (slot_of)
     float delta, scale;
     int n_sink, n_local;
 };
@@ -96,7 +96,7 @@ struct FusedArgs {
     int2* table;                // [B*Hkv]: (first, last) row of each group, or null: S1 rows per group
     uint16_t* out;              // bf16 [B, Hq, 128], written by the kernel itself when S1 == 1, else null
     float* lse;                 // [B, Hq] or null (S1 == 1 only)
-    int B, Hq, Hkv, Lcap, G, S1, slots, grid_slots;    // S1 per sequence, or `slots` by the lengths (slot_of)
+    int B, Hq, Hkv, Lcap, G, S1, round_slots, grid_slots;    // S1 per sequence, or by the lengths (slot_of)
     float delta, scale;
     int n_sink, n_local;
 };

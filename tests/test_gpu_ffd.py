@@ -385,3 +385,30 @@ def test_merge_row_counts(num_splits):
     assert torch.equal(mask, ref_mask)
     np.testing.assert_allclose(bf16_to_f64(out), bf16_to_f64(ref_out), rtol=2 ** -7, atol=1e-6)
     np.testing.assert_allclose(lse.cpu().numpy(), ref_lse.cpu().numpy(), rtol=0, atol=1e-5)
+
+
+@pytest.mark.parametrize("lens", [[16448] + [1, 0, 64, 65, 300, 1000, 7, 64], [16448 - 70 * b for b in range(9)], [300] * 9])
+def test_slots_over_several_rounds(lens):
+    """9 sequences x 32 KV heads, 8 slots to a round of workgroups, in a capacity of 257 blocks (one more
+    than a slot holds): lengths that need two rounds of slots, all that the grid has, or one per sequence.
+    Against each sequence by itself, whose slots do not follow the lengths: masks alike, outputs to the
+    rounding of another order of fp32 sums (bf16: one step, 2^-7 of the value)."""
+    from paper_2609_00097_amd import ffd
+    B, Hkv, G, Lcap = 9, 32, 2, 16448
+    gen = torch.Generator("cuda").manual_seed(11)
+    q = torch.randn(B, Hkv * G, 128, dtype=torch.bfloat16, device="cuda", generator=gen)
+    k = torch.randn(B, Hkv, Lcap, 128, dtype=torch.bfloat16, device="cuda", generator=gen)
+    qk = ffd.quantize_keys(k)
+    v = k.normal_(generator=gen)
+    seq_lens = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    print(f"case rounds of slots {lens}", flush=True)
+    got = {kernels: ffd.decode_attention(q, *qk, v, seq_lens, delta=1.0, return_mask=True, kernels=kernels)
+           for kernels in ("split", "fused")}
+    for b in range(B):
+        one = [t[b:b + 1] for t in (q, *qk, v, seq_lens)]
+        out, lse, mask = ffd.decode_attention(*one, delta=1.0, return_mask=True, kernels="split")
+        torch.cuda.synchronize()
+        for o, l, m in got.values():
+            assert torch.equal(m[b], mask[0])
+            np.testing.assert_allclose(bf16_to_f64(o[b]), bf16_to_f64(out[0]), rtol=2 ** -7, atol=1e-6)
+            np.testing.assert_allclose(l[b].cpu().numpy(), lse[0].cpu().numpy(), rtol=0, atol=1e-5)
