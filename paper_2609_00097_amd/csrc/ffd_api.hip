@@ -540,8 +540,7 @@ int ffd_decode_attention_ex(const void* q, const void* k_codes, const void* k_ab
                   num_splits > 0 ? (int)Wr : (int)std::min(max_units, 1LL << 20), nent,
                   scale, thumb_top_level(thumb_bits)};
     TopkArgs ta{sigma, seq_lens, lists, info, table, ticket, block_mask, Hq, Hkv, Lcap, top_k};
-    const dim3 scan_grid = slots_by_eight(thumb_bits) ? dim3(8u * (unsigned)Hkv * (unsigned)((ss.grid + 7) / 8))
-                                                      : slot_grid(Hkv, ss.grid);
+    const dim3 scan_grid = scan_in_order(thumb_bits) ? dim3((unsigned)(ss.grid * Hkv)) : slot_grid(Hkv, ss.grid);
     const dim3 refine_grid((unsigned)Wr);
     auto mark = [&](int i) {
         return stage_events && hipEventRecord(stage_events[i], stream) != hipSuccess ? FFD_ERR_HIP : FFD_OK;

@@ -255,30 +255,42 @@ __device__ __forceinline__ void block_scores(const BlockScan<BITS>& ld, int j, i
 // chain precedes every load of the kernel. Batches of more than kBalanceMaxSeqs keep S1 slots per
 // sequence. Slots past the last one used have b = -1.
 struct Slot {
-    int b;              // sequence
+    int b, kvh;         // sequence, KV head
     int s, S;           // the slot's number among the sequence's S slots
     int base;           // slots of the sequences before it
     int L;              // sequence length, clamped to the capacity
 };
 
-// ceil(n / d) for 0 <= n <= 2^18, 1 <= d <= 2^18, r = 1 / d to an ulp or two
-__device__ __forceinline__ int ceil_div(int n, int d, float r) {
-    const int m = n + d - 1;
-    int q = (int)((float)m * r);                    // off by at most one
-    q -= q * d > m ? 1 : 0;
-    q += (q + 1) * d <= m ? 1 : 0;
+// floor(n / d) and ceil(n / d) for 0 <= n < 2^24, quotients below 2^20; r = 1 / d to an ulp or two
+__device__ __forceinline__ int floor_div(int n, int d, float r) {
+    int q = (int)((float)n * r);                    // off by at most one
+    q -= q * d > n ? 1 : 0;
+    q += (q + 1) * d <= n ? 1 : 0;
     return q;
 }
+__device__ __forceinline__ int ceil_div(int n, int d, float r) { return floor_div(n + d - 1, d, r); }
 
-// t: the workgroup's slot. T is chosen for the fewest rounds of `round` slots (which fill the CUs) that hold
-// the sequences in shares of kFfdMaxScanBlocks, up to the grid's slots (>= B * ceil(capacity blocks /
-// kFfdMaxScanBlocks)): a second round that is begun is then filled with smaller shares (5 sequences of 112K
-// to 150K, 8 KV heads: scan 42.5 us with 42 slots of up to 256 blocks, 38.0 with 50 of up to 210).
-__device__ __forceinline__ Slot slot_of(const int32_t* __restrict__ seq_lens, int B, int S1, int round, int grid_slots,
-                                        int Lcap, int t, int lane) {
+// The workgroup's (sequence, KV head, slot): with the KV heads first, (kvh, at) are its grid position and at
+// is the slot; in order (IN_ORDER), at numbers the workgroups by sequence, KV head and slot. Slots that are not
+// used come last either way, so that a CU is not given two workgroups while another gets an empty one (5
+// ragged sequences, 64 of 70 slots used: scan 25.4 us, with unused ones in between 34.8).
+//
+// T is chosen for the fewest rounds of `round` slots (which fill the CUs) that hold the sequences in shares of
+// kFfdMaxScanBlocks, up to the grid's slots (>= B * ceil(capacity blocks / kFfdMaxScanBlocks)): a second round
+// that is begun is then filled with smaller shares (5 sequences of 112K to 150K, 8 KV heads: scan 42.5 us with
+// 42 slots of up to 256 blocks, 38.0 with 50 of up to 210).
+template <bool IN_ORDER>
+__device__ __forceinline__ Slot slot_of(const int32_t* __restrict__ seq_lens, int B, int Hkv, int S1, int round,
+                                        int grid_slots, int Lcap, int kvh, int at, int lane) {
     if (B == 1 || S1 == 1 || B > kBalanceMaxSeqs) { // uniform
-        const int b = B == 1 ? 0 : (S1 == 1 ? t : t / S1);
-        return Slot{b, t - b * S1, S1, b * S1, min(max(seq_lens[b], 0), Lcap)};
+        int b = B == 1 ? 0 : (S1 == 1 ? at : at / S1), s = at - b * S1;
+        if constexpr (IN_ORDER) {
+            const int x = at / S1;
+            b = x / Hkv;
+            kvh = x - b * Hkv;
+            s = at - x * S1;
+        }
+        return Slot{b, kvh, s, S1, b * S1, min(max(seq_lens[b], 0), Lcap)};
     }
     const int L = lane < B ? min(max(seq_lens[lane], 0), Lcap) : 0;
     const int n = (L + kBlock - 1) / kBlock;
@@ -287,9 +299,7 @@ __device__ __forceinline__ Slot slot_of(const int32_t* __restrict__ seq_lens, in
     const int slots = min(grid_slots, round * ceil_div(least, round, __builtin_amdgcn_rcpf((float)round)));
     // T lies between N / slots and what gives every sequence the same number of slots; candidates
     // lo + i step, one per lane, from coarse to fine
-    int each = (int)((float)slots * __builtin_amdgcn_rcpf((float)B));      // floor(slots / B)
-    each -= each * B > slots ? 1 : 0;
-    each += (each + 1) * B <= slots ? 1 : 0;
+    const int each = floor_div(slots, B, __builtin_amdgcn_rcpf((float)B));
     int hi = min(max(ceil_div(longest, each, __builtin_amdgcn_rcpf((float)each)), 1), kFfdMaxScanBlocks);
     int lo = max(ceil_div(N, slots, __builtin_amdgcn_rcpf((float)slots)), (longest + kFfdMaxScanSplits - 1) / kFfdMaxScanSplits);
     lo = min(max(lo, 1), hi);
@@ -305,11 +315,17 @@ __device__ __forceinline__ Slot slot_of(const int32_t* __restrict__ seq_lens, in
     }
     const int S = lane < B ? max(ceil_div(n, hi, __builtin_amdgcn_rcpf((float)hi)), 1) : 0;
     const int incl = wave_inclusive_scan(S);
-    const uint64_t after = __ballot(incl > t);
-    if (after == 0) return Slot{-1, 0, 1, 0, 0};
+    const int per_slot = IN_ORDER ? Hkv : 1;
+    const uint64_t after = __ballot(incl * per_slot > at);
+    if (after == 0) return Slot{-1, 0, 0, 1, 0, 0};
     const int b = (int)__builtin_ctzll(after);
     const int Sb = __builtin_amdgcn_readlane(S, b), base = __builtin_amdgcn_readlane(incl, b) - Sb;
-    return Slot{b, t - base, Sb, base, __builtin_amdgcn_readlane(L, b)};
+    at -= base * per_slot;
+    if constexpr (IN_ORDER) {
+        kvh = floor_div(at, Sb, __builtin_amdgcn_rcpf((float)Sb));
+        at -= kvh * Sb;
+    }
+    return Slot{b, kvh, at, Sb, base, __builtin_amdgcn_readlane(L, b)};
 }
 
 template <int NT>
@@ -401,9 +417,8 @@ struct RefineLds {
 // ================================================================================================
 // Scan: b-bit thumbnail scan and pseudo-max, then the keep decisions; the kept list (or, for the
 // top-k rule, every block's scores) to the workspace.
-// Grid (Hkv, slots) of kScanWaves-wave workgroups (KV heads first, so that slots that are not used come
-// last and a CU is not given two workgroups while another gets an empty one: 5 ragged sequences, 70
-// slots of which 64 are used: scan 25.4 us, with the slots first 34.8); slot s of the S given to a sequence (slot_of) scans
+// Grid (Hkv, slots) of kScanWaves-wave workgroups, or one dimension where scan_in_order; slot s of the S given
+// to a sequence (slot_of) scans
 // blocks [s * bps, (s + 1) * bps) of one (sequence, KV head), bps = ceil(nblk / S) <= kFfdMaxScanBlocks;
 // its waves take the blocks one at a time from an LDS counter and keep kRing blocks in flight each.
 // ================================================================================================
@@ -446,21 +461,16 @@ __global__ __launch_bounds__(kScanThreads, scan_occupancy<BITS>()) void ffd_scan
     constexpr bool kTopK = MODE == kSelTopK;
     constexpr int kRing = scan_ring<BITS>();
     __shared__ ScanLds<NT> sm;
-    // 4-bit codes: eight slots of a KV head, then of the next (at 4 x 128K, where all strides are powers of
-    // two, the scan takes 52 us this way and 56 with the KV heads first; 2 and 8 bits: 29 and 29, 96 and 93)
-    int kvh = blockIdx.x, t = blockIdx.y + kSlotGridY * blockIdx.z;
-    if constexpr (slots_by_eight(BITS)) {
-        const int turn = blockIdx.x / (8 * a.Hkv), at = blockIdx.x - turn * 8 * a.Hkv;
-        kvh = at >> 3;
-        t = 8 * turn + (at & 7);
-    }
-    if (t >= a.grid_slots) return;
+    constexpr bool kInOrder = scan_in_order(BITS);
+    const int at = kInOrder ? (int)blockIdx.x : (int)(blockIdx.y + kSlotGridY * blockIdx.z);
+    if (!kInOrder && at >= a.grid_slots) return;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int g = lane >> 4, n = lane & 15;
-    const Slot sl = slot_of(a.seq_lens, a.B, a.S1, a.round_slots, a.grid_slots, a.Lcap, t, lane);
-    const int b = sl.b, s = sl.s, S = sl.S, L = sl.L;
+    const Slot sl = slot_of<kInOrder>(a.seq_lens, a.B, a.Hkv, a.S1, a.round_slots, a.grid_slots, a.Lcap, blockIdx.x, at, lane);
+    const int b = sl.b, kvh = sl.kvh, s = sl.s, S = sl.S, L = sl.L;
     // records in (group, split) order; a slot that is not used holds no block and begins no group
-    const size_t rec = b < 0 ? (size_t)t * a.Hkv + kvh : (size_t)sl.base * a.Hkv + (size_t)kvh * S + s;
+    const size_t rec = kInOrder ? (size_t)at : b < 0 ? (size_t)at * a.Hkv + blockIdx.x
+                                                     : (size_t)sl.base * a.Hkv + (size_t)kvh * S + s;
     if (b < 0) {                                    // uniform
         if constexpr (!kTopK) {
             if (tid == 0) a.info[rec] = make_int4(0, 0, 0, 1 | (1 << kInfoSplitBits));
@@ -707,7 +717,7 @@ __global__ __launch_bounds__(kScanThreads, 1) void ffd_decode_kernel(FusedArgs a
     if (t >= a.grid_slots) return;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int g = lane >> 4, n = lane & 15;
-    const Slot sl = slot_of(a.seq_lens, a.B, a.S1, a.round_slots, a.grid_slots, a.Lcap, t, lane);
+    const Slot sl = slot_of<false>(a.seq_lens, a.B, a.Hkv, a.S1, a.round_slots, a.grid_slots, a.Lcap, kvh, t, lane);
     if (sl.b < 0) return;                           // uniform: a slot no sequence needs
     const int b = sl.b, s = sl.s, S1 = sl.S, L = sl.L;
     const int G = a.G, hq0 = kvh * G;

@@ -26,8 +26,13 @@ constexpr int kInfoSplitMask = (1 << kInfoSplitBits) - 1;
 // Most blocks one scan workgroup covers (its kept list is staged in LDS), most scan workgroups per
 // (sequence, KV head).
 constexpr int kFfdMaxScanBlocks = 256;
-// Whether the scan kernel's grid is one-dimensional, eight slots of each KV head in turn.
-__host__ __device__ constexpr bool slots_by_eight(int bits) { return bits == 4; }
+// Whether the scan's workgroups are numbered by sequence, KV head and slot (neighbours read neighbouring
+// ranges) and not with the KV heads first (neighbours read the same range of each head). Steps over six
+// caches in turn, in order / KV heads first: 4 bits, 4 x 128K, 8 KV heads, where the heads' codes are 8
+// MiB apart, 71.8 / 74.5 us, 2 x 256K 70.5 / 71.7, 1 x 512K 69.3 / 69.8, but 4 x 98K 59.5 / 58.8 and 8 x 64K
+// 73.0 / 71.5; 2 bits 49.7 / 49.4, 48.6 / 49.4, 48.1 / 48.1, 43.7 / 42.9, 50.8 / 51.0; 8 bits 117.2 / 113.9,
+// 114.1 / 117.7, 113.4 / 113.6, 93.4 / 92.6, 116.8 / 115.3. So in order for 4 bits, for its worst case.
+__host__ __device__ constexpr bool scan_in_order(int bits) { return bits == 4; }
 constexpr int kSlotGridY = 32768;              // slots along the grid's y (then z)
 constexpr int kBalanceMaxSeqs = 64;            // largest batch whose scan slots follow the lengths
 constexpr int kScanWaves = 8;                  // waves per scan workgroup (one workgroup per CU)
