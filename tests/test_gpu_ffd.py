@@ -412,3 +412,25 @@ def test_slots_over_several_rounds(lens):
             assert torch.equal(m[b], mask[0])
             np.testing.assert_allclose(bf16_to_f64(o[b]), bf16_to_f64(out[0]), rtol=2 ** -7, atol=1e-6)
             np.testing.assert_allclose(l[b].cpu().numpy(), lse[0].cpu().numpy(), rtol=0, atol=1e-5)
+
+
+@pytest.mark.parametrize("B", [200, 300, 520])
+def test_records_of_several_splits(B):
+    """More than 256, 512 and 1024 scan records (B groups of two, in a capacity of 257 blocks), the last
+    number more than the refinement keeps in LDS; short sequences, so that a group's records hold from
+    nothing to a few blocks, empty and one-block ones among them, against the oracle."""
+    from paper_2609_00097_amd import ffd
+    lens = [0 if b % 37 == 5 else 1 + (97 * b) % 640 for b in range(B)]
+    c = I.small_case(seed=171 + B, B=B, Hq=2, Hkv=1, seq_lens=lens, Lcap=640, heavy_frac=0.05)
+    cap = 257 * 64
+    print(f"case records of {B} groups", flush=True)
+    up = Uploaded(c)
+    k = torch.zeros((B, 1, cap, 128), dtype=torch.bfloat16, device="cuda")
+    k[:, :, :640] = up.k
+    qk = ffd.quantize_keys(k)
+    v = k.zero_()
+    v[:, :, :640] = up.v
+    out, lse, mask = ffd.decode_attention(up.q, *qk, v, up.seq_lens, delta=3.0, return_mask=True, kernels="split")
+    torch.cuda.synchronize()
+    assert not mask[:, :, 10:].any()
+    compare_ffd(c, 3.0, out, lse, mask[:, :, :10].contiguous())
