@@ -246,6 +246,13 @@ int auto_kernels(int B, int Hkv, int Lcap, int S1f) {
                ? FFD_KERNELS_FUSED : FFD_KERNELS_SPLIT;
 }
 
+// Refinement workgroups: num_splits per group on average, or one per CU (fewer where the groups have too few
+// blocks for that).
+long long refine_workgroups(long long pairs, int Lcap, int S, int num_splits) {
+    if (num_splits > 0) return S * pairs;
+    return std::min(pairs * (Lcap / FFD_BLOCK / kMinBlocksPerSplit + 1), (long long)device_cus());
+}
+
 // FFD workspace: partial states (for the fused top-delta kernel's B * Hq * S1f rows, or for the split
 // path's refinement units, one row of G heads per unit and group it meets), the per-group (first row,
 // last row) table, the refinement's unit counter (the region called counts), the kept lists, and the
@@ -256,12 +263,19 @@ struct FfdWorkspace {
     size_t table_off, counts_off, lists_off, sigma_off, total;
 };
 
-FfdWorkspace ffd_layout(int B, int Hq, int Hkv, int Lcap, int D, int S, int S1f) {
+FfdWorkspace ffd_layout(int B, int Hq, int Hkv, int Lcap, int D, int S, int S1f, int num_splits) {
     FfdWorkspace w;
     const size_t pairs = (size_t)B * Hkv;
     const size_t nblk_cap = (size_t)(Lcap / FFD_BLOCK);
-    // the split path's refinement rows, or the fused kernel's [B, Hq, S1f] rows
-    w.rows = std::max(((size_t)S * pairs + pairs) * (size_t)(Hq / Hkv), (size_t)B * Hq * (size_t)S1f);
+    // the split path's refinement rows, or the fused kernel's [B, Hq, S1f] rows. Where there is to be more than
+    // S refinement workgroups per group, a row for each of them and the top-k records' place as well: in
+    // (S + 1) * pairs rows 96 groups of 32 blocks (12 x 2K, 8 KV heads, top-k) had room for 97 workgroups,
+    // refinement 29.8 us; 256 of them take 22.5.
+    const size_t G = (size_t)(Hq / Hkv), row_bytes = G * (D + 2) * sizeof(float);
+    size_t group_rows = (size_t)S * pairs;
+    if (const size_t wanted = (size_t)refine_workgroups(pairs, Lcap, S, num_splits); wanted > group_rows)
+        group_rows = wanted + (pairs * sizeof(int4) + row_bytes - 1) / row_bytes;
+    w.rows = std::max((group_rows + pairs) * G, (size_t)B * Hq * (size_t)S1f);
     w.table_off = round_up(w.rows * (D + 2) * sizeof(float), kAlign);
     w.counts_off = w.table_off + round_up(pairs * 2 * sizeof(int), kAlign);
     w.lists_off = w.counts_off + round_up(pairs * (size_t)scan_splits(B, Hkv, Lcap) * sizeof(int), kAlign);
@@ -417,7 +431,7 @@ size_t ffd_workspace_bytes(int B, int Hq, int Hkv, int Lcap, int D, int num_spli
     if (S <= 0 || S1f <= 0) return 0;
     if ((long long)B * Hkv > (1LL << 20) || Lcap / FFD_BLOCK > kFfdMaxScanBlocks * kFfdMaxScanSplits) return 0;
     // enough for the dense entry point with the same num_splits too
-    return std::max(ffd_layout(B, Hq, Hkv, Lcap, D, S, S1f).total,
+    return std::max(ffd_layout(B, Hq, Hkv, Lcap, D, S, S1f, num_splits).total,
                     ffd_dense_workspace_bytes(B, Hq, Hkv, Lcap, D, num_splits));
 }
 
@@ -501,7 +515,7 @@ int ffd_decode_attention_ex(const void* q, const void* k_codes, const void* k_ab
     const int G = Hq / Hkv;
     const float scale = softmax_scale > 0.f ? softmax_scale : 1.0f / std::sqrt((float)D);
     const int S1f = decode_splits(B, Hkv, Lcap, num_splits);
-    const FfdWorkspace W = ffd_layout(B, Hq, Hkv, Lcap, D, S, S1f);
+    const FfdWorkspace W = ffd_layout(B, Hq, Hkv, Lcap, D, S, S1f, num_splits);
     uint8_t* ws = static_cast<uint8_t*>(workspace);
     int2* table = reinterpret_cast<int2*>(ws + W.table_off);
     uint32_t* lists = reinterpret_cast<uint32_t*>(ws + W.lists_off);
@@ -520,10 +534,8 @@ int ffd_decode_attention_ex(const void* q, const void* k_codes, const void* k_ab
     const size_t info_off = in_scores ? W.sigma_off : (part_bytes - info_bytes) & ~(size_t)15;
     int4* info = reinterpret_cast<int4*>(ws + info_off);
     const long long max_rows = (long long)((in_scores ? part_bytes : info_off) / row_bytes);
-    // refinement workgroups: num_splits per group on average, or one per CU; their W + npairs - 1 rows
-    // of partials have to fit
-    long long Wr = num_splits > 0 ? (long long)S * npairs
-                                  : std::min((long long)npairs * (Lcap / FFD_BLOCK / kMinBlocksPerSplit + 1), (long long)device_cus());
+    // the W + npairs - 1 rows of partials have to fit (top-k with a given num_splits: a few workgroups less)
+    long long Wr = refine_workgroups(npairs, Lcap, S, num_splits);
     const long long max_units = max_rows - npairs + 1;
     Wr = std::max(1LL, std::min(Wr, max_units));
     const size_t rows = (size_t)(max_units + npairs - 1) * G;

@@ -186,3 +186,24 @@ def test_extras_kernels_checked_before_launch(so):
     assert so.ffd_decode_attention_ex(*args, ctypes.byref(ffd.DecodeExtras(None, None, 0, 0, 3))) == 1
     assert so.ffd_decode_attention_ex(*args, ctypes.byref(ffd.DecodeExtras(None, None, 0, 0, -1))) == 1
     assert so.ffd_decode_attention_ex(*args, ctypes.byref(ffd.DecodeExtras(None, None, 0, 8, 1))) == 1
+
+
+def test_workspace_holds_a_row_for_every_refinement_workgroup(so):
+    """Automatic splits: one refinement workgroup per CU (256 here without a GPU), or (blocks / 8 + 1) per
+    group where that is less, and the top-k records, also where S per group are fewer; each region as in
+    test_splits_and_workspace_sizes. A given count leaves the size as it is."""
+    up = lambda x: -(-x // 256) * 256
+
+    def size(B, Hkv, G, C, rows, S1s):
+        P = B * Hkv
+        return up(rows * G * 130 * 4) + up(P * 8) + up(P * S1s * 4) + up(P * C * 4) + P * C * G * 4
+
+    # one group of 8 blocks: 2 workgroups, 1 row for the record, 1 for the group (S = 1 alone: 2 rows)
+    assert so.ffd_workspace_bytes(1, 8, 1, 512, 128, 0) == size(1, 1, 8, 8, 2 + 1 + 1, 1)
+    assert so.ffd_workspace_bytes(1, 8, 1, 512, 128, 1) == size(1, 1, 8, 8, 1 + 1, 1)
+    # 96 groups of 32 blocks in what the dense entry point needs (5 rows per head) anyway
+    assert so.ffd_workspace_bytes(12, 32, 8, 2048, 128, 0) == up(12 * 32 * 5 * 130 * 4) + 96 * 8
+    assert size(12, 8, 4, 32, 256 + 1 + 96, 2) <= so.ffd_workspace_bytes(12, 32, 8, 2048, 128, 0)
+    # more groups than CUs: unchanged, so the fixed scratch still holds the largest of these
+    assert so.ffd_workspace_bytes(96, 128, 32, 4096, 128, 0) <= 16 << 20
+    assert so.ffd_workspace_bytes(400, 32, 32, 2048, 128, 0) <= 16 << 20

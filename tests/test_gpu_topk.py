@@ -245,3 +245,17 @@ def test_bins_too_full_to_rank(Hq, Hkv, k):
     out, lse, mask = _run(up, ffd.quantize_keys(up.k), k)
     compare_topk(c, k, out, lse, mask, heads=[(0, 1)], exact=True)
     compare_topk(c, k, out, lse, mask, heads=[(0, 0), (1, 0), (1, 1)])
+
+
+@pytest.mark.parametrize("Hq,k", [(32, 40), (32, 5), (8, 40)])
+def test_more_refinement_workgroups_than_groups(Hq, k):
+    """96 groups of at most 32 blocks: one refinement workgroup per CU, so that shares begin and end inside
+    groups and rows lie up to the end of the partials, next to the groups' records; empty, one-token and
+    whole sequences, all blocks kept or a few, against the oracle."""
+    from paper_2609_00097_amd import ffd
+    c = I.small_case(seed=211 + Hq + k, B=12, Hq=Hq, Hkv=8, seq_lens=[2048, 0, 1, 2000] + [150 * b for b in range(1, 9)],
+                     Lcap=2048, heavy_frac=0.05)
+    print(f"case top-k 96 groups Hq={Hq} k={k}", flush=True)
+    up = Uploaded(c)
+    out, lse, mask = _run(up, ffd.quantize_keys(up.k), k)
+    compare_topk(c, k, out, lse, mask)
