@@ -5,18 +5,19 @@
 // comparison with a per-head constant made while the scan streams, this needs every block score of
 // the head first: the scan kernel writes them, and this kernel, one workgroup per (sequence, KV
 // head), holds the group's scores in registers (as the order-preserving integer image of the fp32
-// score; each wave holds whole 64-block runs of one head), finds each head's k-th largest score in one
-// histogram over the head's score range (512 equal bins in LDS) and an exact ranking of the few keys in
-// the bin where the k-th lies, or, where a bin holds more than 64 (ties, outliers) or scores are not
-// finite, by a most-significant-digit radix select (four 8-bit digits counted in LDS histograms, stopping
-// early once the digit bucket holds exactly the number still needed), marks the blocks above and equal to
-// it in LDS bitmaps, then goes through the blocks in order, keeps those above the threshold and the
-// first ones equal to it, and writes the group's kept list (block | keep bits << 24, the union over
-// the group's heads) and its length in the scan's format, so the refinement kernel runs unchanged.
+// score; each wave holds whole 64-block runs of one head) and finds each head's k-th largest score by
+// narrowing an interval of keys that holds it: a histogram of 512 equal bins in LDS, first over the
+// head's range of scores, shows the bin where the count from the top reaches k; up to 64 keys in it are
+// ranked against each other, of more (outliers that stretch the range, ties) the least and the largest key
+// are the next interval, whose bins are equal in the integer image. It then marks the blocks above and
+// equal to the k-th score in LDS bitmaps, goes through the blocks in order, keeps those above the
+// threshold and the first ones equal to it, and writes the group's kept list (block | keep bits << 24, the
+// union over the group's heads) and its length in the scan's format, so the refinement kernel runs unchanged.
 //
-// Bound: one workgroup per group works alone on its CU; each digit pass is a chain of LDS atomics, a
-// prefix and two barriers. 32 groups of 2048 blocks x 4 heads, k = 67: 12.0 us, with the digit passes
-// alone 17.8.
+// Bound: one workgroup per group works alone on its CU; each round is a chain of LDS atomics, a prefix and
+// a few barriers. Scan and selection of 32 groups of 2048 blocks x 4 heads, k = 67: 40.0 us (45.4 with a radix
+// select of four 8-bit digits in the histogram's place); with one block's scores 300 times the others' 48.4
+// (48.6; 58.0 where the digits followed a crowded bin of the range), with exact ties throughout 42.8 (48.7; 59.3).
 #include <climits>
 
 #include "ffd_device.h"
@@ -26,13 +27,14 @@ namespace ffd {
 
 namespace {
 
-constexpr int kBins = 256;
 constexpr int kSelThreads = kTopkSelectThreads;      // 16 waves: 4 per SIMD hide each other's latency
 constexpr int kSelWaves = kSelThreads / 64;
 constexpr int kSlots = 8;                            // keys held per thread
 constexpr int kTileKeys = kSlots * kSelThreads;      // (block, head) keys per tile
-constexpr int kFine = 2 * kBins;                     // bins of the range histogram (both digit buffers)
+constexpr int kBinBits = 9;
+constexpr int kBins = 1 << kBinBits;                 // bins per histogram
 constexpr int kMaxCand = 64;                         // keys of one bin that are ranked by a wave
+constexpr int kCrowded = 16;                         // lanes of a wave in one bin from which on it adds them up
 
 // Order-preserving image of a float: larger float, larger key. The scan writes +0 for a zero score.
 __device__ __forceinline__ uint32_t order_key(float x) {
@@ -44,17 +46,24 @@ __device__ __forceinline__ float key_value(uint32_t key) {
     return __uint_as_float((key & 0x80000000u) ? key & 0x7fffffffu : ~key);
 }
 
-// hist[bin] += 1 for every active lane, with one LDS atomic per lane at most. Block scores of a head
-// crowd into few buckets of the leading digit, so the two buckets of the first active lanes are
-// counted by one leader lane each (adding the bucket's population in the wave); the remaining lanes
-// add one each. Branch-free, so the cost per key stays a few instructions.
-__device__ __forceinline__ void hist_add(int* hist, int bin, bool active, int lane) {
+// Whether many active lanes of the wave share the first one's bin. Atomics of many lanes on one address go one
+// after the other, so such waves add their counts up first.
+__device__ __forceinline__ bool crowded(int bin, bool active) {
     const uint64_t act = __ballot(active);                              // wave-uniform
-    const int l0 = act ? __ffsll((unsigned long long)act) - 1 : 0;
+    const int b0 = __builtin_amdgcn_readlane(bin, act ? __builtin_ctzll(act) : 0);
+    return __popcll(__ballot(active && bin == b0)) > kCrowded;
+}
+
+// hist[bin] += 1 for every active lane of a crowded wave: the bins of the first active lane and of the first one
+// of another bin are counted by one leader lane each (adding the bin's population in the wave); the remaining
+// lanes add one each.
+__device__ __forceinline__ void hist_add(int* hist, int bin, bool active, int lane) {
+    const uint64_t act = __ballot(active);
+    const int l0 = act ? __builtin_ctzll(act) : 0;
     const int b0 = __builtin_amdgcn_readlane(bin, l0);
     const uint64_t s0 = __ballot(active && bin == b0);
     const uint64_t rest = act & ~s0;
-    const int l1 = rest ? __ffsll((unsigned long long)rest) - 1 : 0;
+    const int l1 = rest ? __builtin_ctzll(rest) : 0;
     const int b1 = __builtin_amdgcn_readlane(bin, l1);                  // != b0 when rest != 0
     const uint64_t s1 = __ballot(active && bin == b1) & rest;
     const bool lead0 = act != 0 && lane == l0;
@@ -77,40 +86,16 @@ struct Slots {
     __device__ static int run(int wave, int i) { return i * WPH + wave / G; }
 };
 
-// Exclusive prefix sum over the workgroup (thread order) of x; *total receives the sum. One
-// barrier: consecutive calls must alternate between the two halves of wsum[2][kSelWaves].
-__device__ __forceinline__ int sel_exclusive_scan(int x, int* wsum, int* total) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int incl = x;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(incl, o);
-        if (lane >= o) incl += y;
-    }
-    if (lane == 63) wsum[wave] = incl;
-    __syncthreads();
-    int before = 0, tot = 0;
-#pragma unroll
-    for (int w = 0; w < kSelWaves; ++w) {
-        const int v = wsum[w];
-        before += w < wave ? v : 0;
-        tot += v;
-    }
-    *total = tot;
-    return before + incl - x;
-}
-
 template <int G>
 struct TopkLds {
-    int hist[2][G][kBins];
+    int hist[G][kBins];
     uint64_t gtmap[G][Slots<G>::RUNS];    // per head and 64-block run: blocks above the threshold
     uint64_t eqmap[G][Slots<G>::RUNS];    // ... and equal to it
-    uint32_t prefix[G];                   // digits of the k-th largest key found so far
-    int rem[G];                           // keys still to take at or below the prefix
-    int done[G];                          // the prefix's bucket holds exactly rem keys: all are taken
-    int found[G];                         // the prefix is the k-th largest key itself
-    uint32_t lo[kSelWaves], hi[kSelWaves];    // each wave's least and largest key
-    int bin[G], above[G], ncand[G];       // bin of the k-th largest key, keys in higher bins, keys in it
+    uint32_t lo[G], hi[G];                // the least and largest key of the interval that holds the k-th largest
+    int rem[G];                           // the k-th largest key is the interval's rem-th largest
+    int bin[G], inbin[G], ncand[G];       // its bin, keys in the bin, candidates written
+    int found[G];                         // lo is the k-th largest key; rem keys equal to it (INT_MAX: all) are taken
+    uint32_t next_lo[G], next_hi[G];      // the bin's least and largest key
     uint32_t cand[G][kMaxCand];
     int wsum[2][kSelWaves];
 };
@@ -158,26 +143,24 @@ __global__ __launch_bounds__(kSelThreads) void ffd_topk_select_kernel(TopkArgs a
 
     // ---- the k-th largest key of each head ---------------------------------------------------
     if (tid < G) {
-        sm.prefix[tid] = 0;
+        sm.lo[tid] = sm.next_lo[tid] = 0xffffffffu;
+        sm.hi[tid] = sm.next_hi[tid] = 0u;
         sm.rem[tid] = keff;
-        sm.done[tid] = 0;
-        sm.found[tid] = 0;
         sm.ncand[tid] = 0;
+        sm.found[tid] = 0;
     }
-    for (int i = tid; i < G * kFine; i += kSelThreads) (&sm.hist[0][0][0])[i] = 0;
+    for (int i = tid; i < G * kBins; i += kSelThreads) (&sm.hist[0][0])[i] = 0;
     __syncthreads();
-    const int hw = S::head(wave);                    // this wave's head
+    const int hw = S::head(wave);                    // this wave's head (wave h < G: head h)
     const bool select = keff < nblk;                 // else every block is kept
-    if (select) {
-        // ---- one histogram over the head's range of scores. The bin (score - least) * 512 / range grows
-        // with the score (each step is monotonic in fp32), so the k-th largest key lies in the bin where the count
-        // from the top reaches k; the keys of that bin are then compared with each other exactly.
+    // The least and largest of the wave's keys that `of` selects, into lo and hi of its head.
+    auto extremes = [&](uint32_t* lo, uint32_t* hi, auto of) {
         uint32_t klo = 0xffffffffu, khi = 0u;
         for (int ti = 0; ti < ntiles; ++ti) {
             use_tile(ti);
 #pragma unroll
             for (int i = 0; i < kSlots; ++i)
-                if (valid(ti, i)) {
+                if (valid(ti, i) && of(key[i])) {
                     klo = min(klo, key[i]);
                     khi = max(khi, key[i]);
                 }
@@ -188,145 +171,128 @@ __global__ __launch_bounds__(kSelThreads) void ffd_topk_select_kernel(TopkArgs a
             khi = max(khi, (uint32_t)__shfl_xor((int)khi, o));
         }
         if (lane == 0) {
-            sm.lo[wave] = klo;
-            sm.hi[wave] = khi;
+            atomicMin(&lo[hw], klo);
+            atomicMax(&hi[hw], khi);
         }
+    };
+    if (select) {                                    // uniform
+        extremes(sm.lo, sm.hi, [](uint32_t) { return true; });
         __syncthreads();
-#pragma unroll
-        for (int w = 0; w < S::WPH; ++w) {
-            klo = min(klo, sm.lo[hw + G * w]);
-            khi = max(khi, sm.hi[hw + G * w]);
-        }
-        const float least = key_value(klo), range = key_value(khi) - least;
-        const float per = (float)kFine / range;
-        // not for scores that are not finite (the extremes show them), nor for an empty or overflowing range
-        const bool fine = __builtin_isfinite(least) && __builtin_isfinite(range) && __builtin_isfinite(per);   // one value per head
-        auto bin_of = [&](uint32_t k) { return min(max((int)((key_value(k) - least) * per), 0), kFine - 1); };
-        int* fhist = &sm.hist[0][0][0] + hw * kFine;
-        for (int ti = 0; ti < ntiles && fine; ++ti) {
-            use_tile(ti);
-#pragma unroll
-            for (int i = 0; i < kSlots; ++i)
-                if (valid(ti, i)) atomicAdd(&fhist[bin_of(key[i])], 1);
-        }
-        __syncthreads();
-        if (wave < G && fine) {                         // wave h: head h; lane l holds bins 8 l .. 8 l + 7
-            constexpr int kPer = kFine / 64;
-            int c[kPer], tot = 0;
-#pragma unroll
-            for (int i = 0; i < kPer; ++i) {
-                c[i] = fhist[kPer * lane + i];
-                tot += c[i];
-            }
-            const int incl = wave_inclusive_scan(tot);
-            int above = __builtin_amdgcn_readlane(incl, 63) - incl;      // keys in the bins of higher lanes
-#pragma unroll
-            for (int i = kPer - 1; i >= 0; --i) {
-                if (above < keff && above + c[i] >= keff) {
-                    sm.bin[wave] = kPer * lane + i;
-                    sm.above[wave] = above;
-                    sm.found[wave] = c[i] <= kMaxCand;
-                }
-                above += c[i];
-            }
-        }
-        __syncthreads();
-        for (int ti = 0; ti < ntiles && sm.found[hw]; ++ti) {
-            use_tile(ti);
-#pragma unroll
-            for (int i = 0; i < kSlots; ++i)
-                if (valid(ti, i) && bin_of(key[i]) == sm.bin[hw]) sm.cand[hw][atomicAdd(&sm.ncand[hw], 1)] = key[i];
-        }
-        __syncthreads();
-        if (wave < G && sm.found[wave]) {
-            const int nc = sm.ncand[wave], r = keff - sm.above[wave];    // the bin's r-th largest key is sought
-            const uint32_t mine = lane < nc ? sm.cand[wave][lane] : 0u;
-            int larger = 0, equal = 0;
-            for (int i = 0; i < nc; ++i) {
-                const uint32_t other = (uint32_t)__builtin_amdgcn_readlane((int)mine, i);
-                larger += other > mine ? 1 : 0;
-                equal += other == mine ? 1 : 0;
-            }
-            if (lane < nc && larger < r && larger + equal >= r) {        // equal keys write the same
-                sm.prefix[wave] = mine;
-                sm.rem[wave] = r - larger;
-            }
-        }
-        __syncthreads();
-        bool all_found = true;
-#pragma unroll
-        for (int h = 0; h < G; ++h) all_found = all_found && sm.found[h];
-        if (!all_found) {                               // uniform
-            for (int i = tid; i < G * kFine; i += kSelThreads) (&sm.hist[0][0][0])[i] = 0;
-            __syncthreads();
-        }
-        uint32_t pmask = 0;
-        for (int pass = 0, shift = 24; shift >= 0 && !all_found; ++pass, shift -= 8) {
-            int (*hist)[kBins] = sm.hist[pass & 1];
-            const uint32_t pre = sm.prefix[hw];
-            const bool live = !sm.done[hw] && !sm.found[hw];
-            for (int ti = 0; ti < ntiles && live; ++ti) {  // uniform in the wave
+        for (bool first = true;; first = false) {
+            // The interval's bins: (score - least) * 512 / range in the first round, which grows with the score
+            // (each step is monotonic in fp32), where range and scores are finite (the extremes show them);
+            // else equal steps of the key, of which the interval after it holds one: every round takes 9 bits
+            // off the interval's length, and a bin of one key is never narrowed, so five rounds are the most.
+            const uint32_t klo = sm.lo[hw], khi = sm.hi[hw];
+            const float least = key_value(klo), range = key_value(khi) - least;
+            const float per = (float)kBins / range;
+            const bool by_score = first && __builtin_isfinite(least) && __builtin_isfinite(range) && __builtin_isfinite(per);
+            const int shift = max(32 - kBinBits - __clz((int)(khi - klo)), 0);
+            auto bin_of = [&](uint32_t k) {
+                return by_score ? min(max((int)((key_value(k) - least) * per), 0), kBins - 1) : (int)((k - klo) >> shift);
+            };
+            auto inside = [&](uint32_t k) { return k >= klo && k <= khi; };
+            const bool live = !sm.found[hw];         // uniform in the wave
+            for (int ti = 0; ti < ntiles && live; ++ti) {
                 use_tile(ti);
+                const bool in0 = valid(ti, 0) && inside(key[0]);
+                const bool adding_up = crowded(in0 ? bin_of(key[0]) : 0, in0);
 #pragma unroll
-                for (int i = 0; i < kSlots; ++i)
-                    hist_add(hist[hw], (int)((key[i] >> shift) & 255u),
-                             valid(ti, i) && (key[i] & pmask) == pre, lane);
+                for (int i = 0; i < kSlots; ++i) {
+                    const bool in = valid(ti, i) && inside(key[i]);
+                    const int at = in ? bin_of(key[i]) : 0;
+                    if (adding_up) hist_add(sm.hist[hw], at, in, lane);  // uniform in the wave
+                    else if (in) atomicAdd(&sm.hist[hw][at], 1);
+                }
             }
             __syncthreads();
-            // wave w: heads w, w + 4. Lane l holds buckets 4l .. 4l + 3; "above" counts the keys in
-            // higher buckets; the bucket where the count reaches rem holds the k-th largest key.
-            for (int h = wave; h < G; h += kSelWaves) {
-                if (sm.done[h] || sm.found[h]) continue;    // uniform in the wave
-                int c[4], tot = 0;
+            if (wave < G && live) {                  // wave h: head h; lane l holds bins 8 l .. 8 l + 7
+                constexpr int kPer = kBins / 64;
+                int c[kPer], tot = 0;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    c[i] = hist[h][4 * lane + i];
+                for (int i = 0; i < kPer; ++i) {
+                    c[i] = sm.hist[wave][kPer * lane + i];
                     tot += c[i];
                 }
-                int incl = tot;                         // keys in buckets of lanes >= this one
+                const int incl = wave_inclusive_scan(tot), rem = sm.rem[wave];
+                int above = __builtin_amdgcn_readlane(incl, 63) - incl;      // keys in the bins of higher lanes
 #pragma unroll
-                for (int o = 1; o < 64; o <<= 1) {
-                    const int y = __shfl_down(incl, o);
-                    if (lane + o < 64) incl += y;
-                }
-                int above = incl - tot;
-                const int rem = sm.rem[h];
-#pragma unroll
-                for (int i = 3; i >= 0; --i) {
+                for (int i = kPer - 1; i >= 0; --i) {
                     if (above < rem && above + c[i] >= rem) {
-                        sm.prefix[h] |= (uint32_t)(4 * lane + i) << shift;
-                        sm.rem[h] = rem - above;
-                        if (above + c[i] == rem) sm.done[h] = 1;
+                        sm.bin[wave] = kPer * lane + i;
+                        sm.inbin[wave] = c[i];
+                        sm.rem[wave] = rem - above;
                     }
                     above += c[i];
                 }
             }
-            // the other buffer is next pass's histogram; its last reader finished before the barrier above
-            int* other = &sm.hist[(pass + 1) & 1][0][0];
-            for (int i = tid; i < G * kBins; i += kSelThreads) other[i] = 0;
-            pmask |= 255u << shift;
             __syncthreads();
-            bool all_done = true;
+            bool again = false;                      // uniform: some head's bin is to be narrowed
 #pragma unroll
-            for (int h = 0; h < G; ++h) all_done = all_done && (sm.done[h] || sm.found[h]);
-            if (all_done) break;                        // uniform: read after the barrier
+            for (int h = 0; h < G; ++h) again = again || (!sm.found[h] && sm.inbin[h] > kMaxCand);
+            const int bin = sm.bin[hw];
+            if (live && sm.inbin[hw] <= kMaxCand) {
+                for (int ti = 0; ti < ntiles; ++ti) {
+                    use_tile(ti);
+#pragma unroll
+                    for (int i = 0; i < kSlots; ++i)
+                        if (valid(ti, i) && inside(key[i]) && bin_of(key[i]) == bin) sm.cand[hw][atomicAdd(&sm.ncand[hw], 1)] = key[i];
+                }
+            } else if (live) {
+                extremes(sm.next_lo, sm.next_hi, [&](uint32_t k) { return inside(k) && bin_of(k) == bin; });
+            }
+            if (again)
+                for (int i = tid; i < G * kBins; i += kSelThreads) (&sm.hist[0][0])[i] = 0;
+            __syncthreads();
+            if (wave < G && live) {
+                const int nc = sm.inbin[wave], r = sm.rem[wave];
+                if (nc <= kMaxCand) {                // the bin's r-th largest key is sought
+                    const uint32_t mine = lane < nc ? sm.cand[wave][lane] : 0u;
+                    int larger = 0, equal = 0;
+                    for (int i = 0; i < nc; ++i) {
+                        const uint32_t other = (uint32_t)__builtin_amdgcn_readlane((int)mine, i);
+                        larger += other > mine ? 1 : 0;
+                        equal += other == mine ? 1 : 0;
+                    }
+                    if (lane < nc && larger < r && larger + equal >= r) {    // equal keys write the same
+                        sm.lo[wave] = mine;
+                        sm.rem[wave] = larger + equal == r ? INT_MAX : r - larger;
+                    }
+                    if (lane == 0) sm.found[wave] = 1;
+                } else if (lane == 0) {
+                    const uint32_t lo = sm.next_lo[wave], hi = sm.next_hi[wave];
+                    sm.lo[wave] = lo;
+                    sm.hi[wave] = hi;
+                    sm.found[wave] = lo == hi;       // all of the bin's keys are equal
+                    if (lo == hi && r == nc) sm.rem[wave] = INT_MAX;
+                    sm.next_lo[wave] = 0xffffffffu;
+                    sm.next_hi[wave] = 0u;
+                }
+            }
+            __syncthreads();
+            bool all_found = true;
+#pragma unroll
+            for (int h = 0; h < G; ++h) all_found = all_found && sm.found[h];
+            if (all_found) break;                    // uniform: read after the barrier
         }
     }
 
     // ---- keep: key > threshold, or key == threshold among the first `need` equal ones ----------
     // keep-all: threshold 0 with no limit on equal keys takes every key
-    const uint32_t thr_w = select ? sm.prefix[hw] : 0u;
+    const uint32_t thr_w = select ? sm.lo[hw] : 0u;
     int need[G], eq_run[G];                          // uniform: kept in scalar registers
+    bool take_equal = true;                          // every head takes all of its equal keys
 #pragma unroll
     for (int h = 0; h < G; ++h) {
-        need[h] = __builtin_amdgcn_readfirstlane(select && !sm.done[h] ? sm.rem[h] : INT_MAX);
+        need[h] = __builtin_amdgcn_readfirstlane(select ? sm.rem[h] : INT_MAX);
         eq_run[h] = 0;
+        take_equal = take_equal && need[h] == INT_MAX;
     }
     uint32_t* list_x = a.lists + (size_t)x * nblk_cap;
     uint8_t* mask_x = a.mask ? a.mask + ((size_t)b * a.Hq + (size_t)kvh * G) * nblk_cap : nullptr;
     int list_run = 0, half = 0;
     auto scan = [&](int v, int* tot) {
-        const int e = sel_exclusive_scan(v, sm.wsum[half], tot);
+        const int e = wg_exclusive_scan<kSelWaves>(v, sm.wsum[half], tot);
         half ^= 1;
         return e;
     };
@@ -355,23 +321,27 @@ __global__ __launch_bounds__(kSelThreads) void ffd_topk_select_kernel(TopkArgs a
         // a tile holds at most 8192 blocks)
         int eq_before[G];
 #pragma unroll
-        for (int h = 0; h < G; h += 2) {
-            const int hi = h + 1 < G ? __popc(eqm[h + 1]) : 0;
-            int tot = 0;
-            const int e = scan(__popc(eqm[h]) | (hi << 16), &tot);
-            tot = __builtin_amdgcn_readfirstlane(tot);
-            eq_before[h] = eq_run[h] + (e & 0xffff);
-            eq_run[h] += tot & 0xffff;
-            if (h + 1 < G) {
-                eq_before[h + 1] = eq_run[h + 1] + (e >> 16);
-                eq_run[h + 1] += tot >> 16;
+        for (int h = 0; h < G; ++h) eq_before[h] = 0;
+        if (!take_equal) {                              // uniform
+#pragma unroll
+            for (int h = 0; h < G; h += 2) {
+                const int hi = h + 1 < G ? __popc(eqm[h + 1]) : 0;
+                int tot = 0;
+                const int e = scan(__popc(eqm[h]) | (hi << 16), &tot);
+                tot = __builtin_amdgcn_readfirstlane(tot);
+                eq_before[h] = eq_run[h] + (e & 0xffff);
+                eq_run[h] += tot & 0xffff;
+                if (h + 1 < G) {
+                    eq_before[h + 1] = eq_run[h + 1] + (e >> 16);
+                    eq_run[h + 1] += tot >> 16;
+                }
             }
         }
         uint32_t take[G], any = 0u;
 #pragma unroll
         for (int h = 0; h < G; ++h) {
-            take[h] = gtm[h];
-            uint32_t e = eqm[h];
+            take[h] = gtm[h] | (take_equal ? eqm[h] : 0u);
+            uint32_t e = take_equal ? 0u : eqm[h];
             int rank = eq_before[h];
             while (e != 0u && rank < need[h]) {         // the first `need` equal keys, in block order
                 const uint32_t lowbit = e & (0u - e);

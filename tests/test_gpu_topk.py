@@ -259,3 +259,50 @@ def test_more_refinement_workgroups_than_groups(Hq, k):
     up = Uploaded(c)
     out, lse, mask = _run(up, ffd.quantize_keys(up.k), k)
     compare_topk(c, k, out, lse, mask)
+
+
+@pytest.mark.parametrize("Hq,Hkv,L", [(4, 4, 20000), (8, 2, 20000), (16, 2, 150000)])
+def test_scores_over_many_scales(Hq, Hkv, L):
+    """Block scores over 70 powers of two, a few hundred of them alike: every round of the threshold's search
+    narrows a crowded bin further, over one tile of blocks and three. Exactly min(k, blocks) blocks are
+    kept, those of the largest scores but for scores within fp32 rounding (2^-18) of the k-th."""
+    from paper_2609_00097_amd import ffd
+    c = I.small_case(seed=303 + Hq, B=1, Hq=Hq, Hkv=Hkv, seq_lens=(L,), heavy_frac=0.0)
+    nb = -(-L // 64)
+    rng = np.random.default_rng(3)
+    scale = 2.0 ** np.where(np.arange(nb) < 300, -30.0, rng.integers(-40, 30, nb))
+    k = O.bf16_to_f64(c.k[0, :, :L]) * np.repeat(rng.permutation(scale), 64)[None, :L, None]
+    c.k[0, :, :L] = O.f64_to_bf16_bits(k)
+    up = Uploaded(c)
+    qk = ffd.quantize_keys(up.k)
+    sigma = O.decode_batch(c.q, c.k, c.v, c.seq_lens, delta=5.0, n_sink=c.n_sink, n_local=c.n_local)["sigma"][0, :, :nb]
+    for budget in (3, nb // 3, nb - 5):
+        print(f"case top-k scales Hq={Hq} L={L} k={budget}", flush=True)
+        mask = _run(up, qk, budget)[2][0, :, :nb].cpu().numpy().astype(bool)
+        kth = np.sort(sigma, axis=-1)[:, ::-1][:, budget - 1:budget]
+        assert (mask.sum(-1) == budget).all()
+        near = np.abs(sigma - kth) <= 2.0 ** -18 * np.abs(kth)
+        assert not ((mask != (sigma >= kth)) & ~near).any()
+
+
+def test_scores_that_overflow():
+    """Three blocks whose scores overflow to infinity: they tie, the first ones in block order go first, and
+    the finite scores after them are ranked as ever."""
+    from paper_2609_00097_amd import ffd
+    c = I.small_case(seed=311, B=1, Hq=4, Hkv=1, seq_lens=(13000,), heavy_frac=0.0)
+    c.q[:] = O.f64_to_bf16_bits(64.0 * O.bf16_to_f64(c.q))
+    plain = O.decode_batch(c.q, c.k, c.v, c.seq_lens, delta=5.0, n_sink=c.n_sink, n_local=c.n_local)["sigma"][0, :, :204]
+    huge = [9, 77, 130]
+    for j in huge:
+        c.k[0, 0, 64 * j:64 * j + 64] = O.f64_to_bf16_bits(2.0 ** 125 * np.clip(O.bf16_to_f64(c.k[0, 0, 64 * j:64 * j + 64]), -4, 4))
+    up = Uploaded(c)
+    qk = ffd.quantize_keys(up.k)
+    rest = plain.copy()
+    rest[:, huge] = -np.inf
+    order = np.argsort(-rest, axis=-1, kind="stable")
+    for budget in (2, 3, 5):
+        print(f"case top-k overflow k={budget}", flush=True)
+        mask = _run(up, qk, budget)[2][0, :, :204].cpu().numpy().astype(bool)
+        for h in range(4):
+            want = sorted(huge[:budget] + list(order[h, :max(budget - 3, 0)]))
+            assert np.nonzero(mask[h])[0].tolist() == want
