@@ -197,19 +197,21 @@ int decode_splits(int B, int Hkv, int Lcap, int num_splits) {
     return (int)s;
 }
 
-// The fused kernel's workgroups per (sequence, KV head) as launched, at most decode_splits: with eight
-// query heads per KV head or 8-bit codes its registers (150 and 134 a lane) leave room for one workgroup
-// per CU, so an automatic count of two per CU would run in two rounds; it is one per CU then (2 sequences
-// of 60K, G = 8, b = 4: step 41.3 us with 512 workgroups, 32.3 with 256; 1 x 62K, G = 4, b = 8: 32.9 and
-// 25.9 us), as long as that leaves at most kFusedMaxBlocks blocks each: with more, the kept blocks of the
-// workgroups differ too much and two rounds of smaller ones end sooner (32 x 6.7K, 8 KV heads, G = 8,
-// delta 7: 92 us with 512 workgroups of 53 blocks, 108 with 256 of 105).
+// The fused kernel's workgroups per (sequence, KV head) as launched, at most decode_splits: with 8-bit codes its
+// registers (134 and 158 a lane) leave room for one workgroup per CU, so an automatic count of two per CU would
+// run in two rounds; it is one per CU then (1 x 62K, G = 4: 25.9 us, two rounds 32.9), as long as that leaves
+// few enough blocks each: with more, the workgroups' kept blocks differ too much and two rounds of smaller ones
+// end sooner. With 64 blocks one per CU is between 0.99 and 1.14 times as fast up to four query heads per KV head
+// (2, 8 and 16 sequences, half of them without structure or not, delta 5, 7 and infinite); with eight 2 x 64K, one
+// sequence without structure, 84.1 us in two rounds and 89.1 in one, with 32 blocks 49.9 and 50.8 (and 34.5 and
+// 28.7 at delta 7).
 int fused_launch_splits(int S1f, int B, int Hkv, int Lcap, int G, int bits, int num_splits) {
     const long long pairs = (long long)B * Hkv, cus = device_cus();
-    if (num_splits > 0 || (G <= 4 && bits != 8) || S1f * pairs <= cus) return S1f;
+    if (num_splits > 0 || bits != 8 || S1f * pairs <= cus) return S1f;
     const long long need = (Lcap / FFD_BLOCK + kFfdMaxScanBlocks - 1) / kFfdMaxScanBlocks;
     const long long s = std::min((long long)S1f, std::max({1LL, need, cus / pairs}));
-    return (int)((Lcap / FFD_BLOCK + s - 1) / s <= kFusedMaxBlocks ? s : S1f);
+    const long long most = G <= 4 ? kFusedMaxBlocks : kFusedMaxBlocks / 2;
+    return (int)((Lcap / FFD_BLOCK + s - 1) / s <= most ? s : S1f);
 }
 
 // Slots (workgroups per KV head) of the scan and of the fused kernel. Where they follow the lengths, a round
@@ -327,19 +329,39 @@ void launch_scan(int bits, int nt, int mode, dim3 grid, hipStream_t stream, cons
     else launch_scan_bits<8>(nt, mode, grid, stream, sa);
 }
 
-// The fused top-delta kernel for this depth, head tiling and pseudo-max source.
-template <int NT, int BITS>
-void launch_fused_nt(int mode, dim3 grid, hipStream_t stream, const FusedArgs& fa) {
+// The fused top-delta kernel for this depth, head tiling, pseudo-max source and refinement tiles in flight.
+template <int NT, int BITS, int RING>
+void launch_fused_ring(int mode, dim3 grid, hipStream_t stream, const FusedArgs& fa) {
     if (mode == kSelRefinedPM)
-        hipLaunchKernelGGL((ffd_decode_kernel<NT, BITS, kSelRefinedPM>), grid, dim3(kScanThreads), 0, stream, fa);
+        hipLaunchKernelGGL((ffd_decode_kernel<NT, BITS, kSelRefinedPM, RING>), grid, dim3(kScanThreads), 0, stream, fa);
     else
-        hipLaunchKernelGGL((ffd_decode_kernel<NT, BITS, kSelThumbnailPM>), grid, dim3(kScanThreads), 0, stream, fa);
+        hipLaunchKernelGGL((ffd_decode_kernel<NT, BITS, kSelThumbnailPM, RING>), grid, dim3(kScanThreads), 0, stream, fa);
 }
 
+template <int BITS>
+void launch_fused_bits(int nt, bool two_per_cu, int mode, dim3 grid, hipStream_t stream, const FusedArgs& fa) {
+    if (nt == 1) {
+        launch_fused_ring<1, BITS, 2>(mode, grid, stream, fa);
+        return;
+    }
+    if constexpr (BITS != 8) {
+        if (two_per_cu) {
+            launch_fused_ring<2, BITS, 1>(mode, grid, stream, fa);
+            return;
+        }
+    }
+    launch_fused_ring<2, BITS, 2>(mode, grid, stream, fa);
+}
+
+// With eight query heads per KV head two workgroups fit a CU only with one tile in flight per wave, so the grid
+// decides: beyond one workgroup per CU, one tile (8 x 16K, 512 workgroups, delta 5 and 7: 28.2 and 34.1 us; two
+// tiles 38.4 and 40.7), else two (32 x 4K, half of the sequences without structure, 256 workgroups: 72.0 us; one
+// tile 79.1).
 void launch_fused(int bits, int nt, int mode, dim3 grid, hipStream_t stream, const FusedArgs& fa) {
-    if (bits == 2) nt == 1 ? launch_fused_nt<1, 2>(mode, grid, stream, fa) : launch_fused_nt<2, 2>(mode, grid, stream, fa);
-    else if (bits == 4) nt == 1 ? launch_fused_nt<1, 4>(mode, grid, stream, fa) : launch_fused_nt<2, 4>(mode, grid, stream, fa);
-    else nt == 1 ? launch_fused_nt<1, 8>(mode, grid, stream, fa) : launch_fused_nt<2, 8>(mode, grid, stream, fa);
+    const bool two_per_cu = (long long)grid.x * grid.y * grid.z > device_cus();
+    if (bits == 2) launch_fused_bits<2>(nt, two_per_cu, mode, grid, stream, fa);
+    else if (bits == 4) launch_fused_bits<4>(nt, two_per_cu, mode, grid, stream, fa);
+    else launch_fused_bits<8>(nt, two_per_cu, mode, grid, stream, fa);
 }
 
 // The refinement kernel, recomputing the scan scores from rbits-bit codes.

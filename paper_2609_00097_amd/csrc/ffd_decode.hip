@@ -56,7 +56,7 @@ namespace {
 #define FFD_REFINE_RING 2
 #endif
 constexpr int kRing2 = FFD_SCAN_RING;         // 2-bit scan loads in flight per wave (blocks)
-constexpr int kRefineRing = FFD_REFINE_RING;  // refinement tiles in flight per wave
+constexpr int kRefineRing = FFD_REFINE_RING;  // refinement tiles in flight per wave (fused: RING)
 
 __device__ __forceinline__ int limb_of(int Q, int which) {
     const int l0 = ((Q + 128) & 255) - 128;
@@ -688,7 +688,7 @@ __global__ __launch_bounds__(kScanThreads, scan_occupancy<BITS>()) void ffd_scan
 //  2. decides per (head, block): keep iff sigma >= m~ - delta (Eq. 1), the kept blocks (with their
 //     keep bits) forming a list in LDS, in block order;
 //  3. refines and attends its own kept blocks (Eq. 4; online softmax and PV): wave w takes tile
-//     w % 4 of the kept entries w / 4, w / 4 + 2, ..., with kRefineRing tiles in flight; the
+//     w % 4 of the kept entries w / 4, w / 4 + 2, ..., with RING tiles in flight; the
 //     thumbnail term of each kept tile is recomputed from its codes with the same integer MFMA and
 //     fp32 operations as in step 1, so it equals the value the decision used;
 //  4. combines the eight waves' states into one partial state per head, or,
@@ -708,8 +708,10 @@ struct FusedLds {
     EpilogueLds<NT, kScanWaves> epi;
 };
 
-template <int NT, int BITS, int MODE>
-__global__ __launch_bounds__(kScanThreads, 1) void ffd_decode_kernel(FusedArgs a) {
+// RING refinement tiles in flight per wave. With one, a workgroup of eight heads (NT = 2; 2- and 4-bit codes) needs
+// 117 to 124 registers a lane, so that two fit a CU (four waves per SIMD); with two, 147 to 150, and one does.
+template <int NT, int BITS, int MODE, int RING>
+__global__ __launch_bounds__(kScanThreads, RING == 1 ? 4 : 1) void ffd_decode_kernel(FusedArgs a) {
     static_assert(MODE == kSelThumbnailPM || MODE == kSelRefinedPM, "top-delta modes only");
     constexpr int kRing = scan_ring<BITS>();
     __shared__ FusedLds<NT> sm;
@@ -928,14 +930,14 @@ __global__ __launch_bounds__(kScanThreads, 1) void ffd_decode_kernel(FusedArgs a
         wave_lds_fence();
     };
     if (mine > 0) {                                 // wave-uniform
-        RefineTile<NT, BITS> rr[kRefineRing];
+        RefineTile<NT, BITS> rr[RING];
 #pragma unroll
-        for (int r = 0; r < kRefineRing; ++r)
+        for (int r = 0; r < RING; ++r)
             rr[r] = load_refine_tile<NT, BITS>(resid_bh, v_bh, codes_bh, absmax_bh,
                                                (int)(entry(r) & 0xffffffu), T4, lane, L);
-        for (int k0 = 0; k0 < mine; k0 += kRefineRing) {
+        for (int k0 = 0; k0 < mine; k0 += RING) {
 #pragma unroll
-            for (int r = 0; r < kRefineRing; ++r) {
+            for (int r = 0; r < RING; ++r) {
                 const int k = k0 + r;
                 if (k < mine) {
                     const uint32_t e = entry(k);
@@ -943,7 +945,7 @@ __global__ __launch_bounds__(kScanThreads, 1) void ffd_decode_kernel(FusedArgs a
                 }
                 // the last round's refills re-read the wave's last tile (clamped): still cached
                 rr[r] = load_refine_tile<NT, BITS>(resid_bh, v_bh, codes_bh, absmax_bh,
-                                                   (int)(entry(k + kRefineRing) & 0xffffffu), T4, lane, L);
+                                                   (int)(entry(k + RING) & 0xffffffu), T4, lane, L);
             }
         }
     }
@@ -1243,18 +1245,22 @@ template __global__ void ffd_scan_kernel<1, 4, kSelTopK>(ScanArgs);
 template __global__ void ffd_scan_kernel<2, 4, kSelTopK>(ScanArgs);
 template __global__ void ffd_scan_kernel<1, 8, kSelTopK>(ScanArgs);
 template __global__ void ffd_scan_kernel<2, 8, kSelTopK>(ScanArgs);
-template __global__ void ffd_decode_kernel<1, 2, kSelThumbnailPM>(FusedArgs);
-template __global__ void ffd_decode_kernel<2, 2, kSelThumbnailPM>(FusedArgs);
-template __global__ void ffd_decode_kernel<1, 4, kSelThumbnailPM>(FusedArgs);
-template __global__ void ffd_decode_kernel<2, 4, kSelThumbnailPM>(FusedArgs);
-template __global__ void ffd_decode_kernel<1, 8, kSelThumbnailPM>(FusedArgs);
-template __global__ void ffd_decode_kernel<2, 8, kSelThumbnailPM>(FusedArgs);
-template __global__ void ffd_decode_kernel<1, 2, kSelRefinedPM>(FusedArgs);
-template __global__ void ffd_decode_kernel<2, 2, kSelRefinedPM>(FusedArgs);
-template __global__ void ffd_decode_kernel<1, 4, kSelRefinedPM>(FusedArgs);
-template __global__ void ffd_decode_kernel<2, 4, kSelRefinedPM>(FusedArgs);
-template __global__ void ffd_decode_kernel<1, 8, kSelRefinedPM>(FusedArgs);
-template __global__ void ffd_decode_kernel<2, 8, kSelRefinedPM>(FusedArgs);
+template __global__ void ffd_decode_kernel<1, 2, kSelThumbnailPM, 2>(FusedArgs);
+template __global__ void ffd_decode_kernel<2, 2, kSelThumbnailPM, 2>(FusedArgs);
+template __global__ void ffd_decode_kernel<2, 2, kSelThumbnailPM, 1>(FusedArgs);
+template __global__ void ffd_decode_kernel<1, 4, kSelThumbnailPM, 2>(FusedArgs);
+template __global__ void ffd_decode_kernel<2, 4, kSelThumbnailPM, 2>(FusedArgs);
+template __global__ void ffd_decode_kernel<2, 4, kSelThumbnailPM, 1>(FusedArgs);
+template __global__ void ffd_decode_kernel<1, 8, kSelThumbnailPM, 2>(FusedArgs);
+template __global__ void ffd_decode_kernel<2, 8, kSelThumbnailPM, 2>(FusedArgs);
+template __global__ void ffd_decode_kernel<1, 2, kSelRefinedPM, 2>(FusedArgs);
+template __global__ void ffd_decode_kernel<2, 2, kSelRefinedPM, 2>(FusedArgs);
+template __global__ void ffd_decode_kernel<2, 2, kSelRefinedPM, 1>(FusedArgs);
+template __global__ void ffd_decode_kernel<1, 4, kSelRefinedPM, 2>(FusedArgs);
+template __global__ void ffd_decode_kernel<2, 4, kSelRefinedPM, 2>(FusedArgs);
+template __global__ void ffd_decode_kernel<2, 4, kSelRefinedPM, 1>(FusedArgs);
+template __global__ void ffd_decode_kernel<1, 8, kSelRefinedPM, 2>(FusedArgs);
+template __global__ void ffd_decode_kernel<2, 8, kSelRefinedPM, 2>(FusedArgs);
 template __global__ void ffd_refine_kernel<1, 2>(RefineArgs);
 template __global__ void ffd_refine_kernel<2, 2>(RefineArgs);
 template __global__ void ffd_refine_kernel<1, 4>(RefineArgs);

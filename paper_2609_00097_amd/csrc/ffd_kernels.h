@@ -170,7 +170,7 @@ enum ScanMode { kSelThumbnailPM = 0, kSelRefinedPM = 1, kSelTopK = 2 };
 template <int NT, int BITS, int MODE> __global__ void ffd_scan_kernel(ScanArgs a);
 // MODE kSelThumbnailPM or kSelRefinedPM; the scan scores of the kept tiles are recomputed from the
 // codes the kernel has just streamed (bit for bit the values the decisions used).
-template <int NT, int BITS, int MODE> __global__ void ffd_decode_kernel(FusedArgs a);
+template <int NT, int BITS, int MODE, int RING> __global__ void ffd_decode_kernel(FusedArgs a);
 // The scan scores of the kept tiles (Eq. 4's first term) are recomputed from the RBITS-bit codes with
 // the scan kernel's own integer MFMA and fp32 operations, so they equal the scan's bit for bit.
 template <int NT, int RBITS> __global__ void ffd_refine_kernel(RefineArgs a);

@@ -434,3 +434,20 @@ def test_records_of_several_splits(B):
     torch.cuda.synchronize()
     assert not mask[:, :, 10:].any()
     compare_ffd(c, 3.0, out, lse, mask[:, :, :10].contiguous())
+
+
+@pytest.mark.parametrize("pm_source", ["thumbnail", "refined"])
+@pytest.mark.parametrize("bits", [2, 4, 8])
+def test_eight_heads_with_two_workgroups_per_cu(bits, pm_source):
+    """Eight query heads per KV head in more fused workgroups than CUs (one refinement tile in flight per wave
+    at 2 and 4 bits), and in fewer (two): shares of three blocks, of one, none and of 16, against the oracle."""
+    from paper_2609_00097_amd import ffd
+    c = I.small_case(seed=401 + bits, B=3, Hq=16, Hkv=2, seq_lens=(8150, 333, 0), heavy_frac=0.2)
+    print(f"case eight heads bits={bits} {pm_source}", flush=True)
+    up = Uploaded(c)
+    qk = ffd.quantize_keys(up.k, bits=bits)
+    for num_splits in (50, 8):                       # 300 and 48 workgroups
+        out, lse, mask = ffd.decode_attention(up.q, *qk, up.v, up.seq_lens, delta=6.0, return_mask=True, num_splits=num_splits,
+                                              kernels="fused", pseudo_max=pm_source)
+        torch.cuda.synchronize()
+        compare_ffd(c, 6.0, out, lse, mask, bits=bits, pm_source=pm_source)
