@@ -112,8 +112,9 @@ int launch_status() {
     return e == hipSuccess ? FFD_OK : FFD_ERR_HIP;
 }
 
-// Workspace: split partials m [B,Hq,S], l [B,Hq,S], acc [B,Hq,S,D] (fp32); the FFD path adds the
-// scan kernel's kept lists and counts and the top-k rule's block scores.
+// Partial states of `rows` heads, at the start of a workspace: acc [rows, D], then m [rows], l [rows] (fp32). acc
+// comes first because the merge reads it four floats at a time: after an odd number of m and l (one query head
+// per KV head, odd counts) its rows would lie on 8 bytes only.
 struct Partials {
     float* m;
     float* l;
@@ -123,14 +124,13 @@ struct Partials {
 constexpr size_t kAlign = 256;
 size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-size_t partials_bytes(int B, int Hq, int S, int D) { return (size_t)B * Hq * S * (D + 2) * sizeof(float); }
+size_t partials_bytes(size_t rows) { return rows * (kD + 2) * sizeof(float); }
 
-Partials carve(void* ws, int B, int Hq, int S) {
-    const size_t rows = (size_t)B * Hq * S;
-    float* base = static_cast<float*>(ws);
-    return Partials{base, base + rows, base + 2 * rows};
+Partials carve(void* ws, size_t rows) {
+    static_assert(kD * sizeof(float) % 16 == 0, "rows of acc on 16 bytes, like the workspace");
+    float* acc = static_cast<float*>(ws);
+    return Partials{acc + rows * kD, acc + rows * (kD + 1), acc};
 }
-
 
 // Workgroups of the scan kernel per (sequence, KV head): about one per CU in all (one 8-wave
 // workgroup per CU: 8 waves x 4 blocks of 2 KiB in flight cover a CU's share of the HBM bandwidth at
@@ -441,9 +441,9 @@ size_t ffd_dense_workspace_bytes(int B, int Hq, int Hkv, int Lcap, int D, int nu
     if (check_shapes(B, Hq, Hkv, Lcap, D) != FFD_OK) return 0;
     const int S = resolve_splits(B > 0 ? B : 1, Hkv, Lcap, num_splits, true);
     if (S <= 0) return 0;
-    if (B > kDenseBalanceMaxSeqs) return partials_bytes(B, Hq, S, D);
+    if (B > kDenseBalanceMaxSeqs) return partials_bytes((size_t)B * Hq * S);
     // balanced mode: (S + 1) partial rows per head, then the per-(sequence, KV head) table
-    return round_up(partials_bytes(B, Hq, S + 1, D), kAlign) + (size_t)B * Hkv * sizeof(int2);
+    return round_up(partials_bytes((size_t)B * Hq * (S + 1)), kAlign) + (size_t)B * Hkv * sizeof(int2);
 }
 
 size_t ffd_workspace_bytes(int B, int Hq, int Hkv, int Lcap, int D, int num_splits) {
@@ -562,15 +562,13 @@ int ffd_decode_attention_ex(const void* q, const void* k_codes, const void* k_ab
     Wr = std::max(1LL, std::min(Wr, max_units));
     const size_t rows = (size_t)(max_units + npairs - 1) * G;
     int* ticket = reinterpret_cast<int*>(ws + W.counts_off);
-    float* part_m = reinterpret_cast<float*>(ws);
-    float* part_l = part_m + rows;
-    float* part_acc = part_l + rows;
+    const Partials P = carve(ws, rows);
     ScanArgs sa{static_cast<const uint16_t*>(q), static_cast<const uint32_t*>(k_codes),
                 static_cast<const uint16_t*>(k_absmax), static_cast<const int8_t*>(k_resid), seq_lens, lists,
                 info, table, ticket, sigma, block_mask, m_tilde, B, Hq, Hkv, Lcap, G, S1, ss.round, ss.grid, delta, scale, n_sink, n_local};
     RefineArgs ra{static_cast<const uint16_t*>(q), static_cast<const uint32_t*>(k_codes),
                   static_cast<const uint16_t*>(k_absmax), static_cast<const int8_t*>(k_resid),
-                  static_cast<const uint16_t*>(v), lists, info, table, ticket, part_m, part_l, part_acc, Lcap, G, (int)Wr,
+                  static_cast<const uint16_t*>(v), lists, info, table, ticket, P.m, P.l, P.acc, Lcap, G, (int)Wr,
                   num_splits > 0 ? (int)Wr : (int)std::min(max_units, 1LL << 20), nent,
                   scale, thumb_top_level(thumb_bits)};
     TopkArgs ta{sigma, seq_lens, lists, info, table, ticket, block_mask, Hq, Hkv, Lcap, top_k};
@@ -589,20 +587,17 @@ int ffd_decode_attention_ex(const void* q, const void* k_codes, const void* k_ab
         const int S1l = fused_launch_splits(S1f, B, Hkv, Lcap, G, thumb_bits, num_splits);
         const Slots fs = num_splits > 0 ? Slots{B * S1l, B * S1l} : slots_of(B, Hkv, Lcap, S1l, 2);
         const bool direct = S1l == 1;
-        const size_t frows = (size_t)B * Hq * S1l;
-        float* fpart_m = reinterpret_cast<float*>(ws);
-        float* fpart_l = fpart_m + frows;
-        float* fpart_acc = fpart_l + frows;
+        const Partials F = carve(ws, (size_t)B * Hq * S1l);
         int2* ftable = !direct && B > 1 && B <= kBalanceMaxSeqs ? table : nullptr;      // rows follow the lengths
         FusedArgs fa{static_cast<const uint16_t*>(q), static_cast<const uint32_t*>(k_codes),
                      static_cast<const uint16_t*>(k_absmax), static_cast<const int8_t*>(k_resid),
-                     static_cast<const uint16_t*>(v), seq_lens, block_mask, m_tilde, fpart_m, fpart_l, fpart_acc,
+                     static_cast<const uint16_t*>(v), seq_lens, block_mask, m_tilde, F.m, F.l, F.acc,
                      ftable, direct ? static_cast<uint16_t*>(out) : nullptr, direct ? lse : nullptr,
                      B, Hq, Hkv, Lcap, G, S1l, fs.round, fs.grid, delta, scale, n_sink, n_local};
         launch_fused(thumb_bits, G <= 4 ? 1 : 2, mode, slot_grid(Hkv, fs.grid), stream, fa);
         if ((st = launch_status()) != FFD_OK || (st = mark(1)) != FFD_OK || (st = mark(2)) != FFD_OK) return st;
         if (!direct) {
-            launch_merge(B * Hq, stream, fpart_m, fpart_l, fpart_acc, S1l, ftable, G, static_cast<uint16_t*>(out), lse);
+            launch_merge(B * Hq, stream, F.m, F.l, F.acc, S1l, ftable, G, static_cast<uint16_t*>(out), lse);
             if ((st = launch_status()) != FFD_OK) return st;
         }
         return mark(3);
@@ -626,7 +621,7 @@ int ffd_decode_attention_ex(const void* q, const void* k_codes, const void* k_ab
     if (G <= 4) launch_refine_nt<1>(thumb_bits, refine_grid, stream, ra);
     else launch_refine_nt<2>(thumb_bits, refine_grid, stream, ra);
     if ((st = launch_status()) != FFD_OK || (st = mark(2)) != FFD_OK) return st;
-    launch_merge(B * Hq, stream, part_m, part_l, part_acc, 0, table, G, static_cast<uint16_t*>(out), lse);
+    launch_merge(B * Hq, stream, P.m, P.l, P.acc, 0, table, G, static_cast<uint16_t*>(out), lse);
     if ((st = launch_status()) != FFD_OK) return st;
     return mark(3);
 }
@@ -676,9 +671,9 @@ int ffd_dense_decode_attention(const void* q, const void* k, const void* v, cons
     const int G = Hq / Hkv;
     const float scale = softmax_scale > 0.f ? softmax_scale : 1.0f / std::sqrt((float)D);
     const bool balanced = B <= kDenseBalanceMaxSeqs;
-    const Partials P = carve(workspace, B, Hq, balanced ? S + 1 : S);
+    const Partials P = carve(workspace, (size_t)B * Hq * (balanced ? S + 1 : S));
     int2* table = balanced ? reinterpret_cast<int2*>(static_cast<uint8_t*>(workspace) +
-                                                     round_up(partials_bytes(B, Hq, S + 1, D), kAlign))
+                                                     round_up(partials_bytes((size_t)B * Hq * (S + 1)), kAlign))
                            : nullptr;
     DenseArgs a{static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
                 static_cast<const uint16_t*>(v), seq_lens, P.m, P.l, P.acc, table, B, Hq, Hkv, Lcap, G, S, scale};

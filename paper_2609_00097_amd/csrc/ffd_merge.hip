@@ -93,7 +93,7 @@ __global__ __launch_bounds__(64 * NW) void lse_merge_kernel(const float* __restr
                                                              const int2* __restrict__ table, int G,
                                                              uint16_t* __restrict__ out, float* __restrict__ lse) {
     constexpr int kRowLanes = 8 * NW;               // rows in parallel
-    __shared__ float part[NW][8][8];                // each wave's state per d4
+    alignas(16) __shared__ float part[NW][8][8];    // each wave's state per d4
     const int tid = threadIdx.x, d4 = tid & 7, r = tid >> 3, wave = tid >> 6, lane = tid & 63;
     const size_t x = blockIdx.x / G;                        // blockIdx.x = b * Hq + h
     size_t first = x * S;

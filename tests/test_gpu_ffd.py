@@ -451,3 +451,21 @@ def test_eight_heads_with_two_workgroups_per_cu(bits, pm_source):
                                               kernels="fused", pseudo_max=pm_source)
         torch.cuda.synchronize()
         compare_ffd(c, 6.0, out, lse, mask, bits=bits, pm_source=pm_source)
+
+
+def test_odd_numbers_of_partial_rows():
+    """One query head per KV head and odd counts, so that the partials have an odd number of rows: fused, split
+    and dense kernels (the last in both of its modes) against the oracle."""
+    from paper_2609_00097_amd import ffd
+    from tests.gpu_util import compare_dense
+    c = I.small_case(seed=419, B=3, Hq=1, Hkv=1, seq_lens=(1500, 64, 700), heavy_frac=0.2)
+    print("case odd partial rows", flush=True)
+    up = Uploaded(c)
+    qk = _quant(up)
+    for kernels, num_splits in [("fused", 3), ("fused", 5), ("split", 2), ("split", 4)]:
+        out, lse, mask = _ffd(up, qk, 5.0, num_splits=num_splits, kernels=kernels)
+        compare_ffd(c, 5.0, out, lse, mask)
+    compare_dense(c, *ffd.dense_decode_attention(up.q, up.k, up.v, up.seq_lens, num_splits=4))
+    many = I.small_case(seed=421, B=257, Hq=1, Hkv=1, seq_lens=[1 + (37 * b) % 128 for b in range(257)], Lcap=128)
+    up = Uploaded(many)
+    compare_dense(many, *ffd.dense_decode_attention(up.q, up.k, up.v, up.seq_lens, num_splits=3))
