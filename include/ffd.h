@@ -167,9 +167,9 @@ int ffd_decode_attention(const void* q, const void* k_codes, const void* k_absma
                                  of the capacity (128 when there is at most one workgroup per compute
                                  unit), or a sequence fits one workgroup (ffd_select_kernels), else
                                  FFD_KERNELS_SPLIT */
-#define FFD_KERNELS_FUSED 1   /* one kernel: each of S1 = ffd_fused_splits(...) workgroups per
+#define FFD_KERNELS_FUSED 1   /* one kernel: each of S1 = ffd_fused_launch_splits(...) workgroups per
                                  (sequence, KV head) (in a batch of 2 to 64 sequences as many as the
-                                 length's share of B * S1) scans the blocks j = s + S1 i, decides, refines
+                                 length's share of at most B * S1) scans the blocks j = s + S1 i, decides, refines
                                  and attends its own kept blocks; then the merge of the S1 partial states
                                  per head (no merge when S1 == 1: the kernel writes the outputs) */
 #define FFD_KERNELS_SPLIT 2   /* scan + selection kernel (contiguous block ranges), refinement kernel
@@ -250,20 +250,28 @@ int ffd_dense_decode_attention(const void* q, const void* k, const void* v, cons
                                float softmax_scale, void* out, float* lse,
                                void* workspace, size_t workspace_bytes, hipStream_t stream);
 
-/* Number of splits an ffd_decode_attention call with this num_splits (0 = automatic) will use: the
- * automatic count gives the refinement up to (S + 1) * B * Hkv workgroups, at most one per compute unit of
- * the current device (its CU count is queried once per device and cached; 256, an MI355X's, if the
- * query fails). The workspace size depends on it, so size and call on the same device.
+/* The split count S for this num_splits (0 = automatic), which sizes the workspace: num_splits itself, or
+ * automatically the largest with (S + 1) * B * Hkv at most one per compute unit of the current device
+ * (its CU count is queried once per device and cached; 256, an MI355X's, if the query fails), from 1 to an
+ * eighth of the capacity's blocks. Size and call on the same device. The refinement of the split kernels
+ * runs num_splits * B * Hkv workgroups, automatically min(B * Hkv * (Lcap / 512 + 1), compute units).
  * 0 on invalid input. */
 int ffd_resolve_splits(int B, int Hkv, int Lcap, int num_splits);
 
-/* Workgroups per (sequence, KV head) of the fused top-delta kernel for this num_splits: num_splits
- * itself, or automatically 1 when the capacity has at most 64 blocks, else about 16 blocks of the
+/* Workgroups per (sequence, KV head) that the fused top-delta kernel has partial states for in the
+ * workspace, for this num_splits: num_splits itself, or automatically 1 when the capacity has at most 64 blocks, else about 16 blocks of the
  * capacity per workgroup with at most two workgroups per compute unit in all, or one per compute
  * unit when that cap would leave 64 or more blocks per workgroup and one per unit leaves at most
  * 128; raised to ceil((Lcap / 64) / 256) when smaller (a workgroup covers at most 256 blocks).
  * 0 on invalid input. */
 int ffd_fused_splits(int B, int Hkv, int Lcap, int num_splits);
+
+/* The workgroups per (sequence, KV head) that the fused kernel is launched with, at most
+ * ffd_fused_splits(...): an automatic count of more than one workgroup per compute unit in all is one per
+ * unit for 8-bit codes (whose registers allow no second) where that leaves at most 64 blocks of the
+ * capacity per workgroup, 32 with eight query heads per KV head. In a batch of 2 to 64 sequences this is
+ * the mean of an automatic count: each sequence is given workgroups by its length. 0 on invalid input. */
+int ffd_fused_launch_splits(int B, int Hq, int Hkv, int Lcap, int thumb_bits, int num_splits);
 
 /* The kernels FFD_KERNELS_AUTO uses for these arguments: FFD_KERNELS_FUSED or FFD_KERNELS_SPLIT;
  * 0 on invalid input. */
@@ -275,15 +283,17 @@ int ffd_dense_resolve_splits(int B, int Hkv, int Lcap, int num_splits);
 
 /* Workspace bytes needed by ffd_decode_attention for these arguments: the larger of the layout below
  * and ffd_dense_workspace_bytes(...), so it serves the dense entry point too. With
- * S = ffd_resolve_splits(...), P = B * Hkv KV groups, G = Hq / Hkv, C = Lcap / 64
- * blocks and S1 scan splits per group (chosen by the library from B, Hkv, Lcap), the regions, each
- * starting on a 256-byte boundary, are: partials (S * P + P) * G * (D + 2) * 4 bytes, table P * 8,
- * kept counts P * S1 * 4, kept lists P * C * 4, block scores P * C * G * 4.
- * 0 on invalid or unsupported input. */
+ * S = ffd_resolve_splits(...), S1f = ffd_fused_splits(...), P = B * Hkv KV groups, G = Hq / Hkv,
+ * C = Lcap / 64 blocks and S1 scan splits per group (chosen by the library from B, Hkv, Lcap), the
+ * regions, each starting on a 256-byte boundary, are: partials max(R + P, P * S1f) * G * (D + 2) * 4 bytes,
+ * R = S * P, or, where the automatic refinement has W > S * P workgroups, W rows and those that P 16-byte
+ * records take; table P * 8; the unit counter and spare, P * S1 * 4; kept lists P * C * 4; block scores
+ * P * C * G * 4. 0 on invalid or unsupported input. */
 size_t ffd_workspace_bytes(int B, int Hq, int Hkv, int Lcap, int D, int num_splits);
 
-/* Workspace bytes needed by ffd_dense_decode_attention: B * Hq * S * (D + 2) * 4 (fp32 partials
- * m, l, acc) with S = ffd_dense_resolve_splits(...). 0 on invalid input. */
+/* Workspace bytes needed by ffd_dense_decode_attention: fp32 partials acc, m, l of B * Hq * (S + 1) rows,
+ * (D + 2) * 4 bytes each, rounded up to 256, and a table of B * Hkv * 8 bytes; beyond 256 sequences B * Hq * S
+ * rows alone; S = ffd_dense_resolve_splits(...). 0 on invalid input. */
 size_t ffd_dense_workspace_bytes(int B, int Hq, int Hkv, int Lcap, int D, int num_splits);
 
 /* Static, human-readable name of a status code. */

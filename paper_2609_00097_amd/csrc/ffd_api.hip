@@ -427,6 +427,12 @@ int ffd_fused_splits(int B, int Hkv, int Lcap, int num_splits) {
     return decode_splits(B, Hkv, Lcap, num_splits);
 }
 
+int ffd_fused_launch_splits(int B, int Hq, int Hkv, int Lcap, int thumb_bits, int num_splits) {
+    const int S1f = decode_splits(B, Hkv, Lcap, num_splits);
+    if (S1f <= 0 || check_shapes(B, Hq, Hkv, Lcap, FFD_HEAD_DIM) != FFD_OK || check_bits(thumb_bits) != FFD_OK) return 0;
+    return fused_launch_splits(S1f, B, Hkv, Lcap, Hq / Hkv, thumb_bits, num_splits);
+}
+
 int ffd_select_kernels(int B, int Hkv, int Lcap, int num_splits) {
     const int S1f = decode_splits(B, Hkv, Lcap, num_splits);
     if (S1f <= 0) return 0;
