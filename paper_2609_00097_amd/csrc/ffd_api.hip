@@ -64,9 +64,10 @@ void* device_scratch() {
     return p;
 }
 
-// Automatic split counts. The FFD refinement grid has at most (S + 1) * B*Hkv workgroups of equal work
-// and at most one per CU, because a CU serves its older workgroup's memory requests first, so a second
-// workgroup on a CU finishes its share about 3 us later. The dense path keeps two workgroups per CU for up to 63 KV groups
+// Automatic split counts. The FFD path's S sizes the workspace, (S + 1) * B*Hkv rows at most one per CU; its
+// refinement has one workgroup per CU (refine_workgroups), because a CU serves its older workgroup's memory
+// requests first, so a second workgroup on a CU finishes its share about 3 us later. The dense path keeps two
+// workgroups per CU for up to 63 KV groups
 // (4 x 128K: S = 15, 512 workgroups, against S = 23 or 31 about 2 % slower; B = 1: more splits are
 // slower still) and three from 64 groups on (the ragged batch of 16 sequences, 128 groups: 512
 // workgroups 873 us, 768 workgroups 833 us, 1024 workgroups 832 us).
@@ -257,12 +258,12 @@ long long refine_workgroups(long long pairs, int Lcap, int S, int num_splits) {
 
 // FFD workspace: partial states (for the fused top-delta kernel's B * Hq * S1f rows, or for the split
 // path's refinement units, one row of G heads per unit and group it meets), the per-group (first row,
-// last row) table, the refinement's unit counter (the region called counts), the kept lists, and the
+// last row) table, the refinement's unit counter, the kept lists, and the
 // block scores [P, C, G] the top-k rule selects from; the records of the kept lists take the block
 // scores' place or the end of the partials.
 struct FfdWorkspace {
     size_t rows;                      // partial rows
-    size_t table_off, counts_off, lists_off, sigma_off, total;
+    size_t table_off, ticket_off, lists_off, sigma_off, total;
 };
 
 FfdWorkspace ffd_layout(int B, int Hq, int Hkv, int Lcap, int D, int S, int S1f, int num_splits) {
@@ -279,8 +280,9 @@ FfdWorkspace ffd_layout(int B, int Hq, int Hkv, int Lcap, int D, int S, int S1f,
         group_rows = wanted + (pairs * sizeof(int4) + row_bytes - 1) / row_bytes;
     w.rows = std::max((group_rows + pairs) * G, (size_t)B * Hq * (size_t)S1f);
     w.table_off = round_up(w.rows * (D + 2) * sizeof(float), kAlign);
-    w.counts_off = w.table_off + round_up(pairs * 2 * sizeof(int), kAlign);
-    w.lists_off = w.counts_off + round_up(pairs * (size_t)scan_splits(B, Hkv, Lcap) * sizeof(int), kAlign);
+    w.ticket_off = w.table_off + round_up(pairs * 2 * sizeof(int), kAlign);
+    // the counter takes 4 bytes; the rest once held the scan's counts and is spare, so that sizes stay
+    w.lists_off = w.ticket_off + round_up(pairs * (size_t)scan_splits(B, Hkv, Lcap) * sizeof(int), kAlign);
     w.sigma_off = w.lists_off + round_up(pairs * nblk_cap * sizeof(uint32_t), kAlign);
     w.total = w.sigma_off + pairs * nblk_cap * (size_t)(Hq / Hkv) * sizeof(float);
     return w;
@@ -567,11 +569,12 @@ int ffd_decode_attention_ex(const void* q, const void* k_codes, const void* k_ab
     const long long max_units = max_rows - npairs + 1;
     Wr = std::max(1LL, std::min(Wr, max_units));
     const size_t rows = (size_t)(max_units + npairs - 1) * G;
-    int* ticket = reinterpret_cast<int*>(ws + W.counts_off);
+    int* ticket = reinterpret_cast<int*>(ws + W.ticket_off);
     const Partials P = carve(ws, rows);
     ScanArgs sa{static_cast<const uint16_t*>(q), static_cast<const uint32_t*>(k_codes),
                 static_cast<const uint16_t*>(k_absmax), static_cast<const int8_t*>(k_resid), seq_lens, lists,
-                info, table, ticket, sigma, block_mask, m_tilde, B, Hq, Hkv, Lcap, G, S1, ss.round, ss.grid, delta, scale, n_sink, n_local};
+                info, table, ticket, sigma, block_mask, m_tilde, B, Hq, Hkv, Lcap, G, S1, ss.round, ss.grid,
+                delta, scale, n_sink, n_local};
     RefineArgs ra{static_cast<const uint16_t*>(q), static_cast<const uint32_t*>(k_codes),
                   static_cast<const uint16_t*>(k_absmax), static_cast<const int8_t*>(k_resid),
                   static_cast<const uint16_t*>(v), lists, info, table, ticket, P.m, P.l, P.acc, Lcap, G, (int)Wr,

@@ -301,7 +301,8 @@ __device__ __forceinline__ Slot slot_of(const int32_t* __restrict__ seq_lens, in
     // lo + i step, one per lane, from coarse to fine
     const int each = floor_div(slots, B, __builtin_amdgcn_rcpf((float)B));
     int hi = min(max(ceil_div(longest, each, __builtin_amdgcn_rcpf((float)each)), 1), kFfdMaxScanBlocks);
-    int lo = max(ceil_div(N, slots, __builtin_amdgcn_rcpf((float)slots)), (longest + kFfdMaxScanSplits - 1) / kFfdMaxScanSplits);
+    int lo = max(ceil_div(N, slots, __builtin_amdgcn_rcpf((float)slots)),
+                 (longest + kFfdMaxScanSplits - 1) / kFfdMaxScanSplits);
     lo = min(max(lo, 1), hi);
     while (lo < hi) {
         const int step = (hi - lo + 63) >> 6, T = min(lo + lane * step, hi);
@@ -417,9 +418,9 @@ struct RefineLds {
 // ================================================================================================
 // Scan: b-bit thumbnail scan and pseudo-max, then the keep decisions; the kept list (or, for the
 // top-k rule, every block's scores) to the workspace.
-// Grid (Hkv, slots) of kScanWaves-wave workgroups, or one dimension where scan_in_order; slot s of the S given
-// to a sequence (slot_of) scans
-// blocks [s * bps, (s + 1) * bps) of one (sequence, KV head), bps = ceil(nblk / S) <= kFfdMaxScanBlocks;
+// Grid (Hkv, slots) of kScanWaves-wave workgroups, or slots * Hkv in one dimension where scan_in_order; slot s
+// of the S given to a sequence (slot_of) scans blocks [s * bps, (s + 1) * bps) of one (sequence, KV head),
+// bps = ceil(nblk / S) <= kFfdMaxScanBlocks;
 // its waves take the blocks one at a time from an LDS counter and keep kRing blocks in flight each.
 // ================================================================================================
 // Blocks in flight per wave, fewer for the wider thumbnails (whose blocks are 2x and 4x larger).
@@ -466,7 +467,8 @@ __global__ __launch_bounds__(kScanThreads, scan_occupancy<BITS>()) void ffd_scan
     if (!kInOrder && at >= a.grid_slots) return;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int g = lane >> 4, n = lane & 15;
-    const Slot sl = slot_of<kInOrder>(a.seq_lens, a.B, a.Hkv, a.S1, a.round_slots, a.grid_slots, a.Lcap, blockIdx.x, at, lane);
+    const Slot sl = slot_of<kInOrder>(a.seq_lens, a.B, a.Hkv, a.S1, a.round_slots, a.grid_slots, a.Lcap, blockIdx.x, at,
+                                      lane);
     const int b = sl.b, kvh = sl.kvh, s = sl.s, S = sl.S, L = sl.L;
     // records in (group, split) order; a slot that is not used holds no block and begins no group
     const size_t rec = kInOrder ? (size_t)at : b < 0 ? (size_t)at * a.Hkv + blockIdx.x
@@ -1000,9 +1002,10 @@ __global__ __launch_bounds__(kRefineThreads, 1) void ffd_refine_kernel(RefineArg
     const int nblk_cap = a.Lcap / kBlock;
 
     // ---- the line: records and their prefix. Every wave loads all records (64 neighbouring ones at a time:
-    // with a run of 16 records per lane, so that each request met 64 cache lines, 400 records cost 1.1 us
-    // more: 6 x 128K, 8 KV heads, 27.1 -> 26.1 us; 32 and 256 records: the same) and writes them to LDS with their prefix: identical values, so each wave reads back its own
-    // writes and no workgroup barrier is needed.
+    // with a run of 16 records per lane, so that each request met 64 cache lines, 400 records cost 1.1 us more:
+    // 6 x 128K, 8 KV heads, 27.1 -> 26.1 us; up to 256 records, four per lane, the same) and writes them to LDS
+    // with their prefix: identical values, so each wave reads back its own writes and no workgroup barrier is
+    // needed.
     const bool cached = nent <= kRefineRecords;
     int T = 0;
     auto load_records = [&](auto per) {
@@ -1034,7 +1037,8 @@ __global__ __launch_bounds__(kRefineThreads, 1) void ffd_refine_kernel(RefineArg
     // U units on the line, usually one of equal length per workgroup (fewer where the line is shorter
     // than that). Long shares are worked as units from a counter: the chip's memory serves its XCDs at
     // rates that differ by up to a fifth (workgroups of equal shares of 310 blocks ended between 324 and
-    // 411 us), and a fixed share ends with the slowest. The first W units, one per workgroup, then cover
+    // 411 us), and a fixed share ends with the slowest; but only where there is room for two units per workgroup
+    // (kUnitBlocks). The first W units, one per workgroup, then cover
     // kFirstShare of the line, and the rest shrinks linearly to a ninth of its first length, so that the
     // workgroups end together. Which workgroup takes a unit does not enter the results.
     if (T == 0) return;                             // uniform

@@ -53,14 +53,6 @@ __device__ __forceinline__ float row16_sum(float x) {
     x += dpp_f<kDppRor8>(x);
     return x;
 }
-__device__ __forceinline__ float wave_max(float x) {
-    for (int o = 1; o < 64; o <<= 1) x = fmaxf(x, __shfl_xor(x, o));
-    return x;
-}
-__device__ __forceinline__ int wave_sum_i(int x) {
-    for (int o = 1; o < 64; o <<= 1) x += __shfl_xor(x, o);
-    return x;
-}
 
 // Wave-wide reductions through DPP within each 16-lane row and four readlanes across the rows
 // (cheaper than a chain of LDS permutes; the same results, max and integer sums being exact).

@@ -12,11 +12,17 @@ constexpr int kRefineChunk = 256;
 constexpr int kRefineRecords = 1024;
 constexpr int kOffsetThreads = 1024;
 // Line positions that a group's beginning counts for, in blocks: at 4 x 128K, 15 blocks per workgroup,
-// a step takes 59.0 us with 0, 57.8 with 2, 56.8 with 5 and 6, 57.1 with 8, 57.4 with 12.
+// a step takes 59.0 us with 0, 57.8 with 2, 56.8 with 5 and 6, 57.1 with 8, 57.4 with 12. Over 27 other shapes
+// (1 to 64 sequences, 7 to 60 blocks per workgroup) the refinement's times with 2, 3, 4 and 6 lie within 2 % of
+// each other, 3 or 6 being the best; with 12 and 20 they are up to 5 and 15 % longer.
 constexpr int kGroupCost = 6;
 // Units where workgroups take several: blocks per unit on average, at least, and the share of all blocks
 // in the workgroups' first units. Ragged batch of 16, 310 blocks per workgroup, 897 units: 446 us per
-// step; first share 0.7: 448, 0.9: 448; at least 96 blocks per unit: 450.
+// step; first share 0.7: 448, 0.9: 448; at least 96 blocks per unit: 450. Taken from two units per workgroup
+// on, by the blocks and by the rows that the workspace has for partials (units + groups - 1): with fewer, those
+// after the first are too long to even out what the first ones differ by. 16 x 64K, half of the sequences
+// without structure, rows for 385 units on 256 CUs: 434 us a step with them, 367 with equal shares; 8 x 64K,
+// 449: 207 and 188; 6 x 128K, 465: 317 and 285.
 constexpr int kUnitBlocks = 48;
 constexpr double kFirstShare = 0.82;
 // A record int4 describes one kept list: (kept blocks, sequence length, KV group, split | splits <<
@@ -55,7 +61,7 @@ struct ScanArgs {
     const int8_t* resid;        // [B, Hkv, Lcap/16, 2, 64, 16]: read for the refined pseudo-max only
     const int32_t* seq_lens;    // [B]
     uint32_t* lists;            // [B*Hkv, Lcap/64]: kept blocks j | keep bits << 24, per scan split
-    int4* info;                 // [B*Hkv, S1]: one record per kept list
+    int4* info;                 // [grid_slots * Hkv]: one record per kept list, in (group, split) order
     int2* table;                // [B*Hkv]: set to (0, -1)
     int* ticket;                // the refinement's unit counter: set to 0
     float* sigma;               // top-k selection: block scores [B*Hkv, Lcap/64, G]

@@ -186,7 +186,8 @@ __global__ __launch_bounds__(kSelThreads) void ffd_topk_select_kernel(TopkArgs a
             const uint32_t klo = sm.lo[hw], khi = sm.hi[hw];
             const float least = key_value(klo), range = key_value(khi) - least;
             const float per = (float)kBins / range;
-            const bool by_score = first && __builtin_isfinite(least) && __builtin_isfinite(range) && __builtin_isfinite(per);
+            const bool by_score =
+                first && __builtin_isfinite(least) && __builtin_isfinite(range) && __builtin_isfinite(per);
             const int shift = max(32 - kBinBits - __clz((int)(khi - klo)), 0);
             auto bin_of = [&](uint32_t k) {
                 return by_score ? min(max((int)((key_value(k) - least) * per), 0), kBins - 1) : (int)((k - klo) >> shift);
@@ -236,7 +237,8 @@ __global__ __launch_bounds__(kSelThreads) void ffd_topk_select_kernel(TopkArgs a
                     use_tile(ti);
 #pragma unroll
                     for (int i = 0; i < kSlots; ++i)
-                        if (valid(ti, i) && inside(key[i]) && bin_of(key[i]) == bin) sm.cand[hw][atomicAdd(&sm.ncand[hw], 1)] = key[i];
+                        if (valid(ti, i) && inside(key[i]) && bin_of(key[i]) == bin)
+                            sm.cand[hw][atomicAdd(&sm.ncand[hw], 1)] = key[i];
                 }
             } else if (live) {
                 extremes(sm.next_lo, sm.next_hi, [&](uint32_t k) { return inside(k) && bin_of(k) == bin; });

@@ -103,8 +103,8 @@ def _ptr(t) -> int | None:
 
 # A call's checks, allocations and argument conversion cost more than its kernels at short contexts, so
 # each is the cheapest form that keeps its meaning (decode_attention with its defaults: 10 us of host time a
-# call with one launch, 18 us in the plain form): the usual tensor passes one expression, and only one that does not goes through
-# the checks that name what is wrong.
+# call with one launch, 18 us in the plain form): the usual tensor passes one expression, and only one that
+# does not goes through the checks that name what is wrong.
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 

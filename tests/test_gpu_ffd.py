@@ -287,8 +287,8 @@ def test_maximum_capacity(kernels):
 
 
 def test_allocation_for_more_than_1024_kv_groups():
-    """More than 1024 (sequence, KV head) groups: the refinement sums the scan counts per group in
-    passes with LDS atomics instead of its per-wave allocation; outputs against the oracle."""
+    """More than 1024 (sequence, KV head) groups of one block: more scan records than the refinement keeps in
+    LDS, so that their prefix comes from a kernel of its own; outputs against the oracle."""
     lens = [1 + (37 * b) % 64 for b in range(1030)]
     c = I.small_case(seed=61, B=1030, Hq=1, Hkv=1, seq_lens=lens, Lcap=64, heavy_frac=0.0)
     print("case 1030 groups of one block", flush=True)
@@ -302,9 +302,9 @@ def test_allocation_for_more_than_1024_kv_groups():
 
 @pytest.mark.parametrize("B", [200, 300])
 def test_allocation_fills_the_grid_with_many_groups(B):
-    """Many KV groups and one refinement split (W <= 2 B*Hkv): the allocation grows its effective W
-    until the grid is full, in the per-wave allocation (200 groups) and in the LDS-cached one (300
-    groups); ragged lengths, empty sequences among them, both through the oracle."""
+    """About as many KV groups as refinement workgroups, and more: shares that cross groups, a group's
+    beginning and end in the middle of a share, with ragged lengths, empty sequences among them; through the
+    oracle."""
     from paper_2609_00097_amd import ffd
     lens = [0 if b % 37 == 5 else 1 + (97 * b) % 2000 for b in range(B)]
     c = I.small_case(seed=71 + B, B=B, Hq=4, Hkv=1, seq_lens=lens, Lcap=2048, heavy_frac=0.03)
@@ -318,7 +318,7 @@ def test_allocation_fills_the_grid_with_many_groups(B):
 
 def test_share_longer_than_the_per_wave_staging():
     """One split: a single refinement workgroup refines all 1094 kept blocks of the group, staged in
-    two chunks with workgroup barriers (shares of up to 256 blocks are staged by each wave alone)."""
+    five chunks of up to 256 with workgroup barriers between them."""
     c = I.small_case(seed=62, B=1, Hq=4, Hkv=1, seq_lens=(70000,), heavy_frac=0.02)
     print("case one workgroup, 1094 kept blocks", flush=True)
     up = Uploaded(c)
@@ -343,6 +343,10 @@ def test_refinement_units_from_the_counter():
     v = k.normal_(generator=gen)
     lens = torch.tensor([0, 1] + [13600 + 61 * b for b in range(B - 2)], dtype=torch.int32, device="cuda")
     ws = ffd.new_workspace(B, Hkv * G, Hkv, Lcap)
+    # the counter is used: 96 positions per workgroup (one per CU), and rows for two units each beside the groups
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert Hkv * int(((lens + 63) // 64).sum()) >= 96 * cus
+    assert B * Hkv * ffd.fused_splits(B, Hkv, Lcap) - B * Hkv + 1 >= 2 * cus
     print("case refinement units", flush=True)
     runs = [ffd.decode_attention(q, *qk, v, lens, delta=float("inf"), workspace=ws, kernels="split") for _ in range(3)]
     ref, ref_lse, _ = ffd.decode_attention(q, *qk, v, lens, delta=float("inf"), num_splits=1, kernels="split")
