@@ -296,10 +296,11 @@ def decode_attention(q, codes, absmax, resid, v, seq_lens, *, delta: float, n_si
         ev = (ctypes.c_void_p * 4)(*[e.cuda_event for e in stage_events])
     if kernels not in KERNELS:
         raise ValueError(f"kernels must be one of {tuple(KERNELS)}")
+    top_k = int(top_k)
     extras = None               # the library's defaults
     if ev is not None or m_tilde is not None or pseudo_max != "thumbnail" or top_k or kernels != "auto":
         extras = ctypes.byref(DecodeExtras(ctypes.cast(ev, P) if ev is not None else None, _ptr(m_tilde),
-                                           PSEUDO_MAX[pseudo_max], int(top_k), KERNELS[kernels]))
+                                           PSEUDO_MAX[pseudo_max], top_k, KERNELS[kernels]))
     _check("ffd_decode_attention", lib().ffd_decode_attention_ex(
         _ptr(q), _ptr(codes), _ptr(absmax), _ptr(resid), _ptr(v), _ptr(seq_lens), B, Hq, Hkv, Lcap,
         D, bits, BLOCK, float(delta), n_sink, n_local, num_splits, float(softmax_scale), _ptr(out),

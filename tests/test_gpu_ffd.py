@@ -343,9 +343,10 @@ def test_refinement_units_from_the_counter():
     v = k.normal_(generator=gen)
     lens = torch.tensor([0, 1] + [13600 + 61 * b for b in range(B - 2)], dtype=torch.int32, device="cuda")
     ws = ffd.new_workspace(B, Hkv * G, Hkv, Lcap)
-    # the counter is used: 96 positions per workgroup (one per CU), and rows for two units each beside the groups
+    # the counter is used: 96 positions per workgroup (one per CU; a block is one, a group's beginning six), and rows
+    # for two units each beside the groups
     cus = torch.cuda.get_device_properties(0).multi_processor_count
-    assert Hkv * int(((lens + 63) // 64).sum()) >= 96 * cus
+    assert Hkv * (int(((lens + 63) // 64).sum()) + 6 * B) >= 96 * cus
     assert B * Hkv * ffd.fused_splits(B, Hkv, Lcap) - B * Hkv + 1 >= 2 * cus
     print("case refinement units", flush=True)
     runs = [ffd.decode_attention(q, *qk, v, lens, delta=float("inf"), workspace=ws, kernels="split") for _ in range(3)]

@@ -185,6 +185,9 @@ def test_empty_sequence_and_argument_errors():
     with pytest.raises(ffd.FfdError) as e:
         ffd.decode_attention(up.q, *qk, up.v, up.seq_lens, delta=5.0, top_k=-2)
     assert e.value.status == 1
+    for top_k in (None, ""):                         # no number: refused, not taken as 0
+        with pytest.raises((TypeError, ValueError)):
+            ffd.decode_attention(up.q, *qk, up.v, up.seq_lens, delta=5.0, top_k=top_k)
 
 
 @pytest.mark.parametrize("wl,k,heads", [(3, 57, [(0, 0), (1, 3), (3, 7)]), (4, 41, [(0, 0), (0, 5)]),
