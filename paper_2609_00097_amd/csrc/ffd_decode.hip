@@ -295,8 +295,12 @@ __device__ __forceinline__ Slot slot_of(const int32_t* __restrict__ seq_lens, in
     const int L = lane < B ? min(max(seq_lens[lane], 0), Lcap) : 0;
     const int n = (L + kBlock - 1) / kBlock;
     const int N = wave_sum_dpp(n), longest = (int)wave_max_dpp((float)n);
-    const int least = wave_sum_dpp(lane < B ? max((n + kFfdMaxScanBlocks - 1) / kFfdMaxScanBlocks, 1) : 0);
-    const int slots = min(grid_slots, round * ceil_div(least, round, __builtin_amdgcn_rcpf((float)round)));
+    int slots = grid_slots;
+    if (grid_slots > round) {                       // uniform
+        const int full = (int)((uint32_t)(n + kFfdMaxScanBlocks - 1) / kFfdMaxScanBlocks);
+        const int least = wave_sum_dpp(lane < B ? max(full, 1) : 0);
+        slots = min(grid_slots, round * ceil_div(least, round, __builtin_amdgcn_rcpf((float)round)));
+    }
     // T lies between N / slots and what gives every sequence the same number of slots; candidates
     // lo + i step, one per lane, from coarse to fine
     const int each = floor_div(slots, B, __builtin_amdgcn_rcpf((float)B));
