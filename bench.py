@@ -124,16 +124,11 @@ def dense_bytes(case, S):
         2 * case.B * case.Hq * S * (case.D + 2) * 4
 
 
-def fused_workgroups(r, bits=2):
-    """The fused kernel's workgroups per KV group as launched."""
-    return r.ffd.fused_launch_splits(r.case.B, r.case.Hq, r.case.Hkv, r.case.Lcap, bits, r.splits)
-
-
-def partial_rows(r, kernels, bits=2):
+def partial_rows(r, kernels):
     """Partial states per head of a step with these kernels: the fused kernel's S1 (none when
     S1 == 1), or about S + 1 for the split kernels (W refinement workgroups over B*Hkv groups)."""
     if kernels == "fused":
-        s1 = fused_workgroups(r, bits)
+        s1 = r.ffd.fused_splits(r.case.B, r.case.Hkv, r.case.Lcap, r.splits)
         return s1 if s1 > 1 else 0
     return r.S + 1
 
@@ -518,7 +513,7 @@ def depth_sweep(r, delta, depths, steps, dense_us):
             ffd.quantize_keys(r.k[layer], out=r.qk[layer])
         keep = r.mask_for(delta)
         kern = r.kernels
-        nb = algorithmic_bytes(c, keep, partial_rows(r, kern, bits), bits)
+        nb = algorithmic_bytes(c, keep, partial_rows(r, kern), bits)
         us, _ = r.rotate(lambda layer: r.ffd_step(delta, layer), steps, 5)
         su = r.rotate_stages(lambda layer, ev: r.ffd_step(delta, layer, events=ev), steps).mean(axis=0)
         names, sbytes = stage_table(kern, nb, c)
@@ -818,7 +813,8 @@ def main():
                    "q_heads": case.Hq, "kv_heads": case.Hkv, "head_dim": case.D, "kv_block": 64,
                    "delta": delta, "n_sink": case.n_sink, "n_local": case.n_local,
                    "kernels": kern,
-                   "num_splits": fused_workgroups(r) if kern == "fused" else r.S,
+                   "num_splits": r.ffd.fused_splits(case.B, case.Hkv, case.Lcap, args.splits)
+                   if kern == "fused" else r.S,
                    "io": "q/v/out bf16, k as 2-bit codes + int8 residual",
                    "launch": "hip graph replay" if args.graph else "direct (stream-ordered) launches",
                    "protocol": f"layer-averaged: {args.layers} distinct caches, steps back to back, "

@@ -167,9 +167,9 @@ int ffd_decode_attention(const void* q, const void* k_codes, const void* k_absma
                                  of the capacity (128 when there is at most one workgroup per compute
                                  unit), or a sequence fits one workgroup (ffd_select_kernels), else
                                  FFD_KERNELS_SPLIT */
-#define FFD_KERNELS_FUSED 1   /* one kernel: each of S1 = ffd_fused_launch_splits(...) workgroups per
+#define FFD_KERNELS_FUSED 1   /* one kernel: each of S1 = ffd_fused_splits(...) workgroups per
                                  (sequence, KV head) (in a batch of 2 to 64 sequences as many as the
-                                 length's share of at most B * S1) scans the blocks j = s + S1 i, decides, refines
+                                 length's share of B * S1) scans the blocks j = s + S1 i, decides, refines
                                  and attends its own kept blocks; then the merge of the S1 partial states
                                  per head (no merge when S1 == 1: the kernel writes the outputs) */
 #define FFD_KERNELS_SPLIT 2   /* scan + selection kernel (contiguous block ranges), refinement kernel
@@ -258,20 +258,13 @@ int ffd_dense_decode_attention(const void* q, const void* k, const void* v, cons
  * 0 on invalid input. */
 int ffd_resolve_splits(int B, int Hkv, int Lcap, int num_splits);
 
-/* Workgroups per (sequence, KV head) that the fused top-delta kernel has partial states for in the
- * workspace, for this num_splits: num_splits itself, or automatically 1 when the capacity has at most 64 blocks, else about 16 blocks of the
+/* Workgroups per (sequence, KV head) of the fused top-delta kernel for this num_splits (in a batch of 2 to 64
+ * sequences the mean; each is given workgroups by its length): num_splits itself, or automatically 1 when the capacity has at most 64 blocks, else about 16 blocks of the
  * capacity per workgroup with at most two workgroups per compute unit in all, or one per compute
  * unit when that cap would leave 64 or more blocks per workgroup and one per unit leaves at most
  * 128; raised to ceil((Lcap / 64) / 256) when smaller (a workgroup covers at most 256 blocks).
  * 0 on invalid input. */
 int ffd_fused_splits(int B, int Hkv, int Lcap, int num_splits);
-
-/* The workgroups per (sequence, KV head) that the fused kernel is launched with, at most
- * ffd_fused_splits(...): an automatic count of more than one workgroup per compute unit in all is one per
- * unit for 8-bit codes (whose registers allow no second) where that leaves at most 64 blocks of the
- * capacity per workgroup, 32 with eight query heads per KV head. In a batch of 2 to 64 sequences this is
- * the mean of an automatic count: each sequence is given workgroups by its length. 0 on invalid input. */
-int ffd_fused_launch_splits(int B, int Hq, int Hkv, int Lcap, int thumb_bits, int num_splits);
 
 /* The kernels FFD_KERNELS_AUTO uses for these arguments: FFD_KERNELS_FUSED or FFD_KERNELS_SPLIT;
  * 0 on invalid input. */

@@ -198,23 +198,6 @@ int decode_splits(int B, int Hkv, int Lcap, int num_splits) {
     return (int)s;
 }
 
-// The fused kernel's workgroups per (sequence, KV head) as launched, at most decode_splits: with 8-bit codes its
-// registers (134 and 158 a lane) leave room for one workgroup per CU, so an automatic count of two per CU would
-// run in two rounds; it is one per CU then (1 x 62K, G = 4: 25.9 us, two rounds 32.9), as long as that leaves
-// few enough blocks each: with more, the workgroups' kept blocks differ too much and two rounds of smaller ones
-// end sooner. With 64 blocks one per CU is between 0.99 and 1.14 times as fast up to four query heads per KV head
-// (2, 8 and 16 sequences, half of them without structure or not, delta 5, 7 and infinite); with eight 2 x 64K, one
-// sequence without structure, 84.1 us in two rounds and 89.1 in one, with 32 blocks 49.9 and 50.8 (and 34.5 and
-// 28.7 at delta 7).
-int fused_launch_splits(int S1f, int B, int Hkv, int Lcap, int G, int bits, int num_splits) {
-    const long long pairs = (long long)B * Hkv, cus = device_cus();
-    if (num_splits > 0 || bits != 8 || S1f * pairs <= cus) return S1f;
-    const long long need = (Lcap / FFD_BLOCK + kFfdMaxScanBlocks - 1) / kFfdMaxScanBlocks;
-    const long long s = std::min((long long)S1f, std::max({1LL, need, cus / pairs}));
-    const long long most = G <= 4 ? kFusedMaxBlocks : kFusedMaxBlocks / 2;
-    return (int)((Lcap / FFD_BLOCK + s - 1) / s <= most ? s : S1f);
-}
-
 // Slots (workgroups per KV head) of the scan and of the fused kernel. Where they follow the lengths, a round
 // of them fills the CUs `per_cu` times and no more (shares are equal, so a few workgroups over would double
 // the time: 5 sequences of 87K to 219K x 4 KV heads, all 70 slots = 280 workgroups used: scan 33.9 us, 64
@@ -429,12 +412,6 @@ int ffd_fused_splits(int B, int Hkv, int Lcap, int num_splits) {
     return decode_splits(B, Hkv, Lcap, num_splits);
 }
 
-int ffd_fused_launch_splits(int B, int Hq, int Hkv, int Lcap, int thumb_bits, int num_splits) {
-    const int S1f = decode_splits(B, Hkv, Lcap, num_splits);
-    if (S1f <= 0 || check_shapes(B, Hq, Hkv, Lcap, FFD_HEAD_DIM) != FFD_OK || check_bits(thumb_bits) != FFD_OK) return 0;
-    return fused_launch_splits(S1f, B, Hkv, Lcap, Hq / Hkv, thumb_bits, num_splits);
-}
-
 int ffd_select_kernels(int B, int Hkv, int Lcap, int num_splits) {
     const int S1f = decode_splits(B, Hkv, Lcap, num_splits);
     if (S1f <= 0) return 0;
@@ -593,20 +570,22 @@ int ffd_decode_attention_ex(const void* q, const void* k_codes, const void* k_ab
     if (top_k == 0 && kernels == FFD_KERNELS_FUSED) {
         // top-delta, fused: one kernel, then the merge of its partial states per head (none with one
         // workgroup per group: the kernel writes the outputs itself)
-        const int S1l = fused_launch_splits(S1f, B, Hkv, Lcap, G, thumb_bits, num_splits);
-        const Slots fs = num_splits > 0 ? Slots{B * S1l, B * S1l} : slots_of(B, Hkv, Lcap, S1l, 2);
-        const bool direct = S1l == 1;
-        const Partials F = carve(ws, (size_t)B * Hq * S1l);
+        const Slots fs = num_splits > 0 ? Slots{B * S1f, B * S1f} : slots_of(B, Hkv, Lcap, S1f, 2);
+        const bool direct = S1f == 1;
+        // workgroup i + 256 comes 256 + 4 + turn heads after workgroup i: half of the heads, but where the heads
+        // are a multiple of the XCDs (the 4 alone then; any turn would put a head on some XCDs twice)
+        const int turn = Hkv % 8 == 0 ? 0 : ((Hkv / 2 - 260) % Hkv + Hkv) % Hkv;
+        const Partials F = carve(ws, (size_t)B * Hq * S1f);
         int2* ftable = !direct && B > 1 && B <= kBalanceMaxSeqs ? table : nullptr;      // rows follow the lengths
         FusedArgs fa{static_cast<const uint16_t*>(q), static_cast<const uint32_t*>(k_codes),
                      static_cast<const uint16_t*>(k_absmax), static_cast<const int8_t*>(k_resid),
                      static_cast<const uint16_t*>(v), seq_lens, block_mask, m_tilde, F.m, F.l, F.acc,
-                     ftable, direct ? static_cast<uint16_t*>(out) : nullptr, direct ? lse : nullptr,
-                     B, Hq, Hkv, Lcap, G, S1l, fs.round, fs.grid, delta, scale, n_sink, n_local};
+                     ftable, direct ? static_cast<uint16_t*>(out) : nullptr, direct ? lse : nullptr, turn,
+                     B, Hq, Hkv, Lcap, G, S1f, fs.round, fs.grid, delta, scale, n_sink, n_local};
         launch_fused(thumb_bits, G <= 4 ? 1 : 2, mode, slot_grid(Hkv, fs.grid), stream, fa);
         if ((st = launch_status()) != FFD_OK || (st = mark(1)) != FFD_OK || (st = mark(2)) != FFD_OK) return st;
         if (!direct) {
-            launch_merge(B * Hq, stream, F.m, F.l, F.acc, S1l, ftable, G, static_cast<uint16_t*>(out), lse);
+            launch_merge(B * Hq, stream, F.m, F.l, F.acc, S1f, ftable, G, static_cast<uint16_t*>(out), lse);
             if ((st = launch_status()) != FFD_OK) return st;
         }
         return mark(3);

@@ -684,10 +684,10 @@ __global__ __launch_bounds__(kScanThreads, scan_occupancy<BITS>()) void ffd_scan
 }
 
 // ================================================================================================
-// Fused top-delta decode: one workgroup per (sequence, KV head, split s) of kScanWaves waves; grid (Hkv,
-// slots), the slots given to the sequences by their lengths (slot_of). Workgroup s of a sequence's S1
-// owns the blocks j = s + S1 i (i < cnt) of its group, an interleaved share, so the kept
-// blocks of a group (windows, planted clusters) spread evenly over its S1 workgroups. It
+// Fused top-delta decode: one workgroup per (sequence, KV head, split s) of kScanWaves waves, the splits given to
+// the sequences by their lengths (slot_of). Workgroup s of the S1 of a (sequence, KV head) owns the blocks j = s +
+// S1 i (i < cnt) of its group, an interleaved share, so the kept blocks of a group (windows, planted clusters)
+// spread evenly over its S1 workgroups. It
 //  1. streams the thumbnail codes of its blocks (waves take block numbers i from an LDS counter,
 //     kRing blocks in flight each) and keeps each block's per-head maximum score in LDS, while each
 //     wave also scores its share of the pseudo-max window blocks (Alg. 1; Eq. 3);
@@ -715,13 +715,23 @@ struct FusedLds {
 };
 
 // RING refinement tiles in flight per wave. With one, a workgroup of eight heads (NT = 2; 2- and 4-bit codes) needs
-// 117 to 124 registers a lane, so that two fit a CU (four waves per SIMD); with two, 147 to 150, and one does.
+// 117 to 124 registers a lane, so that two fit a CU (four waves per SIMD); with two, 147 to 150, and one does. Up to
+// four heads two workgroups fit with two tiles (120 to 122 registers; 8-bit codes, 134, are held to 128: 16 x 8K, 512
+// workgroups, 37.3 -> 32.3 us).
 template <int NT, int BITS, int MODE, int RING>
-__global__ __launch_bounds__(kScanThreads, RING == 1 ? 4 : 1) void ffd_decode_kernel(FusedArgs a) {
+__global__ __launch_bounds__(kScanThreads, RING == 1 || (NT == 1 && BITS == 8) ? 4 : 1) void ffd_decode_kernel(FusedArgs a) {
     static_assert(MODE == kSelThumbnailPM || MODE == kSelRefinedPM, "top-delta modes only");
     constexpr int kRing = scan_ring<BITS>();
     __shared__ FusedLds<NT> sm;
-    const int kvh = blockIdx.x, t = blockIdx.y + kSlotGridY * blockIdx.z;
+    // KV heads first, turned by one with every 64 workgroups and so that workgroups i and i + 256, which share a CU,
+    // are of heads far apart: workgroups go to the XCDs in turn, so with eight heads unturned each XCD would hold one
+    // head, and a head that keeps most of its blocks would end late on the 32 CUs it has (one such head: 1 x 64K
+    // 34.3 us, turned 23.5, in (sequence, KV head, slot) order 21.6 to 23.5; 4 x 32K 58.4, 35.2, 43.0). Eight
+    // neighbouring slots of a head still share an XCD's L2 for its window blocks: with even heads the order makes
+    // 16 x 8K 20.7 us, unturned 20.8, in (sequence, KV head, slot) order 22.9.
+    const int t = blockIdx.y + kSlotGridY * blockIdx.z, i = t * a.Hkv;
+    int kvh = (int)blockIdx.x + (int)(((unsigned)i / 64 + (unsigned)a.turn * ((unsigned)i / 256)) % (unsigned)a.Hkv);
+    kvh -= kvh >= a.Hkv ? a.Hkv : 0;
     if (t >= a.grid_slots) return;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int g = lane >> 4, n = lane & 15;

@@ -107,6 +107,7 @@ struct FusedArgs {
     int2* table;                // [B*Hkv]: (first, last) row of each group, or null: S1 rows per group
     uint16_t* out;              // bf16 [B, Hq, 128], written by the kernel itself when S1 == 1, else null
     float* lse;                 // [B, Hq] or null (S1 == 1 only)
+    int turn;                   // KV heads turned with every 256 workgroups, beside one with every 64
     int B, Hq, Hkv, Lcap, G, S1, round_slots, grid_slots;    // S1 per sequence, or by the lengths (slot_of)
     float delta, scale;
     int n_sink, n_local;

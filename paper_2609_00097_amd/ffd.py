@@ -76,7 +76,6 @@ def lib() -> ctypes.CDLL:
     so.ffd_dense_decode_attention.argtypes = [P, P, P, P, I, I, I, I, I, I, F, P, P, P, SZ, P]
     so.ffd_resolve_splits.argtypes = [I, I, I, I]
     so.ffd_fused_splits.argtypes = [I, I, I, I]
-    so.ffd_fused_launch_splits.argtypes = [I, I, I, I, I, I]
     so.ffd_select_kernels.argtypes = [I, I, I, I]
     so.ffd_dense_resolve_splits.argtypes = [I, I, I, I]
     for name in ("ffd_workspace_bytes", "ffd_dense_workspace_bytes"):
@@ -86,7 +85,7 @@ def lib() -> ctypes.CDLL:
     so.ffd_status_string.restype = ctypes.c_char_p
     for name in ("ffd_quantize_keys", "ffd_append_kv", "ffd_decode_attention", "ffd_decode_attention_ex",
                  "ffd_decode_attention_noalloc", "ffd_dense_decode_attention", "ffd_resolve_splits",
-                 "ffd_fused_splits", "ffd_fused_launch_splits", "ffd_select_kernels", "ffd_dense_resolve_splits"):
+                 "ffd_fused_splits", "ffd_select_kernels", "ffd_dense_resolve_splits"):
         getattr(so, name).restype = I
     _lib = so
     return so
@@ -136,15 +135,9 @@ def resolve_splits(B: int, Hkv: int, Lcap: int, num_splits: int = 0) -> int:
 
 
 def fused_splits(B: int, Hkv: int, Lcap: int, num_splits: int = 0) -> int:
-    """Workgroups per KV group of the fused top-delta kernel that the workspace is sized for, for this
-    ``num_splits``; at least what is launched."""
+    """Workgroups per KV group of the fused top-delta kernel for this ``num_splits`` (in a batch of 2 to 64
+    sequences, which are given workgroups by their lengths, on average at most)."""
     return lib().ffd_fused_splits(B, Hkv, Lcap, num_splits)
-
-
-def fused_launch_splits(B: int, Hq: int, Hkv: int, Lcap: int, bits: int = 2, num_splits: int = 0) -> int:
-    """Workgroups per KV group that the fused top-delta kernel is launched with (in a batch of 2 to 64
-    sequences, on average at most)."""
-    return lib().ffd_fused_launch_splits(B, Hq, Hkv, Lcap, bits, num_splits)
 
 
 def select_kernels(B: int, Hkv: int, Lcap: int, num_splits: int = 0) -> str:

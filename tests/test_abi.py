@@ -188,24 +188,6 @@ def test_extras_kernels_checked_before_launch(so):
     assert so.ffd_decode_attention_ex(*args, ctypes.byref(ffd.DecodeExtras(None, None, 0, 8, 1))) == 1
 
 
-def test_fused_workgroups_as_launched(so):
-    """ffd_fused_launch_splits: the launched count, below ffd_fused_splits only for 8-bit codes in automatic
-    counts of more than one workgroup per CU, and only down to 64 (eight heads: 32) blocks each."""
-    for Hq in (8, 32, 64):
-        for bits in (2, 4):
-            for B, Lcap in ((1, 4096), (1, 131072), (2, 65536), (4, 131072), (16, 8192)):
-                assert so.ffd_fused_launch_splits(B, Hq, 8, Lcap, bits, 0) == so.ffd_fused_splits(B, 8, Lcap, 0)
-    assert so.ffd_fused_splits(1, 8, 62016, 0) == 61
-    assert so.ffd_fused_launch_splits(1, 32, 8, 62016, 8, 0) == 32           # 256 workgroups of 31 blocks
-    assert so.ffd_fused_launch_splits(1, 32, 8, 62016, 8, 61) == 61          # a given count stays
-    assert so.ffd_fused_launch_splits(2, 32, 8, 65536, 8, 0) == 16           # 64 blocks each ...
-    assert so.ffd_fused_launch_splits(2, 64, 8, 65536, 8, 0) == 32           # ... too many with eight heads
-    assert so.ffd_fused_launch_splits(2, 64, 8, 32768, 8, 0) == 16           # 32
-    assert so.ffd_fused_launch_splits(1, 32, 8, 32768, 8, 0) == so.ffd_fused_splits(1, 8, 32768, 0) == 32
-    assert so.ffd_fused_launch_splits(1, 30, 8, 32768, 8, 0) == 0
-    assert so.ffd_fused_launch_splits(1, 32, 8, 32768, 3, 0) == 0
-
-
 def test_workspace_holds_a_row_for_every_refinement_workgroup(so):
     """Automatic splits: one refinement workgroup per CU (256 here without a GPU), or (blocks / 8 + 1) per
     group where that is less, and the top-k records, also where S per group are fewer; each region as in

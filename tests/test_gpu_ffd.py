@@ -474,3 +474,17 @@ def test_odd_numbers_of_partial_rows():
     many = I.small_case(seed=421, B=257, Hq=1, Hkv=1, seq_lens=[1 + (37 * b) % 128 for b in range(257)], Lcap=128)
     up = Uploaded(many)
     compare_dense(many, *ffd.dense_decode_attention(up.q, up.k, up.v, up.seq_lens, num_splits=3))
+
+
+@pytest.mark.parametrize("Hkv", [1, 3, 5, 6, 8, 16])
+def test_every_head_has_its_fused_workgroups(Hkv):
+    """The fused kernel's order of KV heads turns along the grid: numbers of heads that divide 64 and 256 and that
+    do not, over several turns (80 Hkv workgroups), one head keeping every block; against the oracle."""
+    c = I.small_case(seed=431 + Hkv, B=2, Hq=Hkv, Hkv=Hkv, seq_lens=(3000, 1111), heavy_frac=0.05)
+    c.q[:, Hkv // 2] = O.f64_to_bf16_bits(0.05 * O.bf16_to_f64(c.q[:, Hkv // 2]))
+    print(f"case turned heads Hkv={Hkv}", flush=True)
+    up = Uploaded(c)
+    qk = _quant(up)
+    for num_splits in (40, 7):
+        out, lse, mask = _ffd(up, qk, 5.0, num_splits=num_splits, kernels="fused")
+        compare_ffd(c, 5.0, out, lse, mask)
